@@ -543,8 +543,8 @@ size_t partial_need(rbe_ctx *c, int chunk)
 }
 
 // Real-space tiles: runs of RL_PPB cell-sorted slots for systems with at least
-// three cells per side (aux = 0), runs of 256 particles in original order for
-// the all-pairs systems (aux = 1).
+// three cells per side (aux = 0), runs of real_allpairs_per_tile() particles in
+// original order for the all-pairs systems (aux = 1).
 void build_real_tiles(rbe_ctx *c, std::vector<Tile> &out, std::vector<int> &tile_sys)
 {
     out.clear();
@@ -855,9 +855,13 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     ALLOC(w.step_base, sizeof(uint64_t));
     if (any_diam) ALLOC(w.diam, sizeof(double) * ntot);
     {
-        // list-pass tiles: at most one per 32 slots (the 8-lane shape)
+        // list-pass tiles: at most one per 32 slots (the 8-lane shape), or the
+        // all-pairs tiles of a one-cell system
         int64_t nl = 0;
-        for (int r = 0; r < R; ++r) nl += (c->sysh[r].n + 31) / 32;
+        for (int r = 0; r < R; ++r) {
+            const int step = c->sysh[r].nc == 1 ? real_allpairs_per_tile() : 32;
+            nl += (c->sysh[r].n + step - 1) / step;
+        }
         const int64_t nlist = g.list_on ? ntot : 1;
         ALLOC(w.list_tiles, sizeof(Tile) * (g.list_on ? nl : 1));
         ALLOC(w.slot_of, sizeof(int32_t) * nlist);

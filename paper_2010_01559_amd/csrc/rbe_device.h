@@ -290,6 +290,28 @@ __device__ __forceinline__ KM load_mode(const __attribute__((address_space(4))) 
     return k;
 }
 
+// The term of one mode.
+__device__ __forceinline__ void fourier_term(const KModeF &k, const float h[3], const float lo[3], float f[3])
+{
+    const float rf = phase_split(k.m[0], k.m[1], k.m[2], h[0], h[1], h[2], lo[0], lo[1], lo[2]);
+    const float sn = __builtin_amdgcn_sinf(rf), cs = __builtin_amdgcn_cosf(rf);
+    const float im = cs * k.S - sn * k.C;
+    f[0] = fmaf(im, k.a[0], f[0]);
+    f[1] = fmaf(im, k.a[1], f[1]);
+    f[2] = fmaf(im, k.a[2], f[2]);
+}
+
+__device__ __forceinline__ void fourier_term(const KModeD &k, const double s[3], double f[3])
+{
+    const double ph = wrap_rev(fma(k.m[0], s[0], fma(k.m[1], s[1], k.m[2] * s[2])));
+    double sn, cs;
+    sincospi(2.0 * ph, &sn, &cs);
+    const double im = cs * k.S - sn * k.C;
+    f[0] = fma(im, k.a[0], f[0]);
+    f[1] = fma(im, k.a[1], f[1]);
+    f[2] = fma(im, k.a[2], f[2]);
+}
+
 __device__ __forceinline__ void fourier_range(const KModeF *kk0, int l0, int l1, const float h[3], const float lo[3],
                                               float f[3])
 {
@@ -297,15 +319,7 @@ __device__ __forceinline__ void fourier_range(const KModeF *kk0, int l0, int l1,
     l0 = __builtin_amdgcn_readfirstlane(l0);
     l1 = __builtin_amdgcn_readfirstlane(l1);
 #pragma unroll 4
-    for (int l = l0; l < l1; ++l) {
-        const KModeF k = load_mode(kk, l);
-        const float rf = phase_split(k.m[0], k.m[1], k.m[2], h[0], h[1], h[2], lo[0], lo[1], lo[2]);
-        const float sn = __builtin_amdgcn_sinf(rf), cs = __builtin_amdgcn_cosf(rf);
-        const float im = cs * k.S - sn * k.C;
-        f[0] = fmaf(im, k.a[0], f[0]);
-        f[1] = fmaf(im, k.a[1], f[1]);
-        f[2] = fmaf(im, k.a[2], f[2]);
-    }
+    for (int l = l0; l < l1; ++l) fourier_term(load_mode(kk, l), h, lo, f);
 }
 
 __device__ __forceinline__ void fourier_range(const KModeD *kk0, int l0, int l1, const double s[3], double f[3])
@@ -314,16 +328,7 @@ __device__ __forceinline__ void fourier_range(const KModeD *kk0, int l0, int l1,
     l0 = __builtin_amdgcn_readfirstlane(l0);
     l1 = __builtin_amdgcn_readfirstlane(l1);
 #pragma unroll 2
-    for (int l = l0; l < l1; ++l) {
-        const KModeD k = load_mode(kk, l);
-        const double ph = wrap_rev(fma(k.m[0], s[0], fma(k.m[1], s[1], k.m[2] * s[2])));
-        double sn, cs;
-        sincospi(2.0 * ph, &sn, &cs);
-        const double im = cs * k.S - sn * k.C;
-        f[0] = fma(im, k.a[0], f[0]);
-        f[1] = fma(im, k.a[1], f[1]);
-        f[2] = fma(im, k.a[2], f[2]);
-    }
+    for (int l = l0; l < l1; ++l) fourier_term(load_mode(kk, l), s, f);
 }
 
 // ---------------------------------------------------------------------------

@@ -28,7 +28,8 @@
 // qterm); the nine row sums are added in a fixed order, so the result does not
 // depend on the order of the particles inside a cell (which comes from atomic
 // counters) nor on the path (cell or list pass).  Systems with fewer than
-// three cells per side use all-pairs tiles.
+// three cells per side use all-pairs tiles, one particle per wave
+// (allpairs_wave).
 //
 // List pass: LPP lanes per particle walk its list in strides of LPP; the
 // LPP partial sums are combined by a fixed butterfly.
@@ -44,7 +45,7 @@ namespace rbe {
 constexpr int RL_BS = 256;                  // threads per block: 4 waves
 constexpr int RL_PPW = 7;                   // particles per wave (9 lanes each)
 constexpr int RL_PPB = 4 * RL_PPW;          // particles per block
-constexpr int RL_ALLPAIRS = 256;            // particles per all-pairs tile
+constexpr int RL_ALLPAIRS = 4;              // particles per all-pairs tile: one per wave
 
 int real_rows_per_tile() { return RL_PPB; }
 int real_allpairs_per_tile() { return RL_ALLPAIRS; }
@@ -566,59 +567,163 @@ __device__ __forceinline__ void add_fourier(Four<T> s4, int k, T qi, double &fx,
     fz += (double)(-qi * g[2]);
 }
 
-// All-pairs tile: particles [start, start + count) of a one-cell system, one
-// per thread, partners in original index order.  DIAM compiles the
-// per-particle-diameter LJ (only launches of contexts with diameters).
-template <typename T, bool ENERGY, bool DIAM>
+// Partner queue of the all-pairs waves of a block: the records (and, with
+// per-particle diameters, the indices) of a wave's partners inside the search
+// radius that have not been evaluated yet.
+constexpr int kApUnroll = 2;                     // candidates per lane and round
+constexpr int kApQueue = 64 * (kApUnroll + 1);   // at most 63 left over plus one round
+
+template <typename T, bool DIAM>
+struct PairQueue {
+    typename RBT<T>::Rec r[RL_BS / 64][kApQueue];
+    int32_t j[DIAM ? RL_BS / 64 : 1][DIAM ? kApQueue : 1];
+};
+
+// Orders the LDS accesses of one wave (its LDS instructions execute in order;
+// this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <typename V>
+__device__ __forceinline__ V wave_sum(V v)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// Fourier force of one particle (record pa) with a mode per lane, summed over
+// the wave.
+template <typename T>
+__device__ __forceinline__ void fourier_lanes(const RealArgs<T> &a, const SysDev &S, const typename RBT<T>::Rec &pa,
+                                              T g[3])
+{
+    using KM = typename KMT<T>::type;
+    const KM *kk = reinterpret_cast<const KM *>(a.km) + S.moff;
+    g[0] = g[1] = g[2] = 0;
+    if constexpr (sizeof(T) == 4) {
+        float h[3], lo[3];
+        split_fix(pa.x, S, h[0], lo[0]);
+        split_fix(pa.y, S, h[1], lo[1]);
+        split_fix(pa.z, S, h[2], lo[2]);
+        for (int l = threadIdx.x & 63; l < S.p; l += 64) fourier_term(kk[l], h, lo, g);
+    } else {
+        const double s3[3] = {pa.x, pa.y, pa.z};
+        for (int l = threadIdx.x & 63; l < S.p; l += 64) fourier_term(kk[l], s3, g);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) g[d] = wave_sum(g[d]);
+}
+
+// All-pairs tile of a one-cell system: wave w takes particle start + w, its
+// lanes 64 partners at a time in original order.  The partners inside the
+// search radius go through the wave's LDS queue and are evaluated 64 at a
+// time, so the pair terms run on full waves whatever share of the partners is
+// inside.  With one particle per thread instead (256 per block, each walking
+// all partners alone, two blocks at N = 300) the launch lasted as long as N
+// dependent loads and pair terms of one lane: 79 us at N = 300 in single and
+// 122 us at N = 200 in double precision, against about 5 us each now (a step
+// of the 300 ions 105 -> 30 us).  FOURIER adds the Fourier force (a
+// mode per lane).  DIAM compiles the per-particle-diameter LJ (only launches
+// of contexts with diameters).
+template <typename T, bool ENERGY, bool DIAM, bool FOURIER>
 __device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, const Tile &t, const SysDev &S, double *ev,
-                                              Four<T> s4 = nullptr)
+                                              PairQueue<T, DIAM> &qu)
 {
     using Rec = typename RBT<T>::Rec;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (wave >= t.count) return;
     const Geo geo = make_geo<T>(S);
     const auto pc = pair_consts<T>(S);
     const Rec *pk = reinterpret_cast<const Rec *>(a.packed) + S.off;
-    if ((int)threadIdx.x >= t.count) return;
-    const int il = t.start + threadIdx.x;
+    const int il = t.start + wave, n = S.n;
     const Rec pa = pk[il];
     const double da = DIAM && S.diam_on ? a.diam[S.off + il] : 0.0;
     double fx = 0, fy = 0, fz = 0;
     PairE e{0, 0};
-    for (int j = 0; j < S.n; ++j) {
-        if (j == il) continue;
-        const Rec pb = pk[j];
-        if (!near_test(pa, pb, geo)) continue;
+    Rec *qr = qu.r[wave];
+    int32_t *qj = qu.j[DIAM ? wave : 0];
+    int nq = 0;   // queued partners
+    auto pair = [&](int k) {
+        const Rec pb = qr[k];
         T dx, dy, dz, r2;
         displacement(pa, pb, geo, dx, dy, dz, r2);
         T phi = pair_phi<ENERGY>(pc, (T)pa.q, (T)pb.q, r2, e);
-        if (DIAM && S.diam_on) phi += (T)lj_offset<ENERGY>(S, da, a.diam[S.off + j], r2_double(pa, pb, S.L), e);
+        if (DIAM && S.diam_on) phi += (T)lj_offset<ENERGY>(S, da, a.diam[S.off + qj[k]], r2_double(pa, pb, S.L), e);
         const T ph = qphi(phi);
         fx += qterm(ph * dx);
         fy += qterm(ph * dy);
         fz += qterm(ph * dz);
         if constexpr (ENERGY) ev[2] += 0.5 * (double)(phi * r2);
+    };
+    for (int j0 = 0; j0 < n; j0 += 64 * kApUnroll) {
+        Rec pb[kApUnroll];
+#pragma unroll
+        for (int u = 0; u < kApUnroll; ++u) pb[u] = pk[min(j0 + 64 * u + lane, n - 1)];
+#pragma unroll
+        for (int u = 0; u < kApUnroll; ++u) {
+            const int j = j0 + 64 * u + lane;
+            const bool in = j < n && j != il && near_test(pa, pb[u], geo);
+            const uint64_t m = __ballot(in);
+            if (in) {
+                const int k = nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+                qr[k] = pb[u];
+                if constexpr (DIAM) qj[k] = j;
+            }
+            nq += __builtin_popcountll(m);
+        }
+        wave_lds_order();
+        while (nq >= 64) {
+            nq -= 64;
+            pair(nq + lane);
+        }
+        wave_lds_order();
     }
+    if (lane < nq) pair(lane);
     if constexpr (ENERGY) {
         ev[0] += e.e_real;
         ev[1] += e.e_lj;
     }
     if constexpr (sizeof(T) == 4) range_check(fx, fy, fz, a.flag);
+    fx = wave_sum(fx);
+    fy = wave_sum(fy);
+    fz = wave_sum(fz);
+    T g[3];
+    if constexpr (FOURIER) fourier_lanes<T>(a, S, pa, g);
+    if (lane != 0) return;
+    if constexpr (sizeof(T) == 4) range_check(fx, fy, fz, a.flag);
     fx *= qscale<T>();
     fy *= qscale<T>();
     fz *= qscale<T>();
-    add_fourier<T>(s4, (int)threadIdx.x, (T)pa.q, fx, fy, fz);
+    if constexpr (FOURIER) {
+        fx += (double)(-(T)pa.q * g[0]);
+        fy += (double)(-(T)pa.q * g[1]);
+        fz += (double)(-(T)pa.q * g[2]);
+    }
     finish_particle<T, ENERGY>(a, S, S.off + il, fx, fy, fz, ev);
 }
 
 // Row-lane tile on the cell list.  With BUILD the rows are scanned with the
 // list radius and every hit is also written to the particle's list: the nine
 // row counts are prefixed in LDS so that the list keeps row order.
+template <bool ENERGY, bool BUILD>
+struct RowsLds {
+    double red[ENERGY ? 6 : 3][RL_BS];
+    int cnt[BUILD ? RL_BS : 1];
+};
+
 template <typename T, bool ENERGY, bool BUILD, bool DIAM>
 __device__ __forceinline__ void rows_body(const RealArgs<T> &a, const ListArgs *la, const Tile &t, const SysDev &S,
-                                          double *ev, Four<T> s4 = nullptr)
+                                          double *ev, RowsLds<ENERGY, BUILD> &lds, Four<T> s4 = nullptr)
 {
     using Rec = typename RBT<T>::Rec;
-    __shared__ double s_red[ENERGY ? 6 : 3][RL_BS];
-    __shared__ int s_cnt[BUILD ? RL_BS : 1];
+    auto &s_red = lds.red;
+    auto &s_cnt = lds.cnt;
     const Geo geo = BUILD ? list_geo(S) : make_geo<T>(S);
     const auto pc = pair_consts<T>(S);
     const int tid = threadIdx.x;
@@ -744,11 +849,16 @@ __global__ __launch_bounds__(RL_BS) void k_real_rows(RealArgs<T> a)
 {
     const Tile t = a.tiles[blockIdx.x];
     const SysDev S = a.sys[t.sys];
+    // a block runs one of the two bodies
+    __shared__ union {
+        PairQueue<T, DIAM> pairs;
+        RowsLds<ENERGY, false> rows;
+    } lds;
     double ev[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if (t.aux == 1)
-        allpairs_body<T, ENERGY, DIAM>(a, t, S, ev);
+        allpairs_body<T, ENERGY, DIAM, false>(a, t, S, ev, lds.pairs);
     else
-        rows_body<T, ENERGY, false, DIAM>(a, nullptr, t, S, ev);
+        rows_body<T, ENERGY, false, DIAM>(a, nullptr, t, S, ev, lds.rows);
     if constexpr (ENERGY) energy_block(ev, a.epart + 8 * blockIdx.x);
 }
 
@@ -895,7 +1005,14 @@ __device__ __forceinline__ int wave_slot() { return __builtin_amdgcn_s_getreg((4
 template <typename T, int LPP, bool DIAM, bool SINGLE>
 __global__ __launch_bounds__(RL_BS) void k_real_step(RealArgs<T> a, ListArgs la)
 {
-    __shared__ T s4[4][FT_MAX][3];
+    __shared__ union {
+        struct {
+            T s4[4][FT_MAX][3];
+            RowsLds<false, true> rows;
+        } c;
+        PairQueue<T, DIAM> pairs;
+    } lds;
+    auto &s4 = lds.c.s4;
     // both flags are read before anything is stored, so that neither read
     // waits for the other
     const int poison = *la.ls.poison;
@@ -943,12 +1060,13 @@ __global__ __launch_bounds__(RL_BS) void k_real_step(RealArgs<T> a, ListArgs la)
         list_finish<T, LPP>(a, t, S, h, s4, fx, fy, fz);
         return;
     }
-    fourier_tile<T>(a, S, allpairs ? a.packed : a.sorted, S.off + t.start, t.count, s4);
+    if (allpairs) {
+        allpairs_body<T, false, DIAM, true>(a, t, S, nullptr, lds.pairs);
+        return;
+    }
+    fourier_tile<T>(a, S, a.sorted, S.off + t.start, t.count, s4);
     __syncthreads();
-    if (allpairs)
-        allpairs_body<T, false, DIAM>(a, t, S, nullptr, s4);
-    else
-        rows_body<T, false, true, DIAM>(a, &la, t, S, nullptr, s4);
+    rows_body<T, false, true, DIAM>(a, &la, t, S, nullptr, lds.c.rows, s4);
 }
 
 // Stand-alone scatter into cell order (force and energy calls; a time step
@@ -1034,14 +1152,16 @@ __global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__re
         gpos[2 * ntot + i] = (T)rz;
     };
     if (t.aux == 1) {
+        // a particle per wave (as in allpairs_body), a partner per lane
         const Rec *pk = reinterpret_cast<const Rec *>(a.packed) + S.off;
-        if (tid < t.count) {
-            const int il = t.start + tid;
+        const int w = tid >> 6;
+        if (w < t.count) {
+            const int il = t.start + w;
             const int64_t i = S.off + il;
             const Rec pa = pk[il];
             const T Gix = gF[i], Giy = gF[ntot + i], Giz = gF[2 * ntot + i];
             double dq = 0, rx = 0, ry = 0, rz = 0;
-            for (int j = 0; j < S.n; ++j) {
+            for (int j = tid & 63; j < S.n; j += 64) {
                 if (j == il) continue;
                 const Rec pb = pk[j];
                 if (!near_test(pa, pb, geo)) continue;
@@ -1051,7 +1171,11 @@ __global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__re
                 vjp_pair<T>(S, (T)pa.q, (T)pb.q, dx, dy, dz, r2, Gix - gF[jj], Giy - gF[ntot + jj],
                             Giz - gF[2 * ntot + jj], dq, rx, ry, rz);
             }
-            finish(i, dq, rx, ry, rz);
+            dq = wave_sum(dq);
+            rx = wave_sum(rx);
+            ry = wave_sum(ry);
+            rz = wave_sum(rz);
+            if ((tid & 63) == 0) finish(i, dq, rx, ry, rz);
         }
         return;
     }
