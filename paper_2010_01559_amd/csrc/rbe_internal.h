@@ -202,6 +202,7 @@ struct LaunchCfg {
     int max_p;
     int max_table;   // largest cumulative table (2M + 1)
     int list_on;     // some system uses the neighbour list
+    int all_pairs;   // every system has one cell: steps run without any list or cell work
     int kmax;        // list capacity per particle
     int n_list_tiles;
     int wait_limit;  // spin bound of the device-side waits of a list rebuild
@@ -233,7 +234,8 @@ struct StageRequest {
     uint64_t step;         // integrator noise index
     uint64_t sample_step;  // mode sample index
     int integrate, bin, sample, rho;
-    const ListStep *list;  // integrate in list mode: update cell-order records, test displacements
+    const ListStep *list;  // integrate in list mode: update cell-order records, test displacements (an
+                           // all-pairs context only stores the records)
     int kick = 0;          // integrate: first apply the previous step's closing half kick (deferred)
     int mode_split = 1;    // no integration/binning/sampling: split the modes over this many blocks per chunk
 };

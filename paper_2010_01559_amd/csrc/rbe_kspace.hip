@@ -148,7 +148,8 @@ struct StageArgs {
     int kick;   // deferred closing half kick of the previous step
     int chunk;
     int single_n;          // single-system context (SINGLE launches): its particle count
-    int single_p;          // and its mode count
+    int single_p;          // its mode count
+    int single_list;       // and whether it uses the neighbour list
     int tab_max;           // LDS doubles reserved for the table
     // neighbour-list mode of a time step
     int list_mode;
@@ -264,13 +265,13 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
     const Tile t = SINGLE ? Tile{0, bx * a.chunk, min(a.chunk, a.single_n - bx * a.chunk), bx} : a.tiles[bx];
     SysDev S = a.sys[SINGLE ? 0 : t.sys];
     if constexpr (SINGLE) {
-        // the single system's offsets are 0, its mode count comes with the
-        // launch, and a list step implies that it uses the list: no particle,
-        // list or mode load waits for the system constants
+        // the single system's offsets are 0, its mode count and whether it
+        // uses the list come with the launch: no particle, list or mode load
+        // waits for the system constants
         S.off = 0;
         S.moff = 0;
         S.p = a.single_p;
-        if (a.list_mode) S.use_list = 1;
+        if (a.list_mode) S.use_list = a.single_list;
     }
     using RR = typename RhoRec<T>::type;
     RR *sp = reinterpret_cast<RR *>(smem);
@@ -967,6 +968,7 @@ static hipError_t stage_dispatch(const LaunchCfg &c, const Workspace &w, const S
     a.tab_max = tab_max;
     a.single_n = c.R == 1 ? (int)c.ntot : 0;
     a.single_p = c.R == 1 ? c.max_p : 0;
+    a.single_list = c.list_on;
     dim3 g(c.n_rho_tiles, rq.mode_split > 1 ? rq.mode_split : 1);
     const int var = (rq.integrate || rq.bin || rq.list) ? 2 : (rq.sample ? 1 : 0);
     if (c.R == 1)

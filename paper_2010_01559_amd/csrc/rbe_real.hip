@@ -1069,6 +1069,26 @@ __global__ __launch_bounds__(RL_BS) void k_real_step(RealArgs<T> a, ListArgs la)
     rows_body<T, false, true, DIAM>(a, &la, t, S, nullptr, lds.c.rows, s4);
 }
 
+// Force pass of a time step of a context that has only one-cell systems:
+// Fourier and all-pairs real-space force in one launch (there is no list and
+// nothing to rebuild).
+template <typename T, bool DIAM>
+__global__ __launch_bounds__(RL_BS) void k_pairs_step(RealArgs<T> a, int single_n, int single_p)
+{
+    __shared__ PairQueue<T, DIAM> qu;
+    const int b = (int)blockIdx.x;
+    // a single system's tile, offsets and mode count come with the launch
+    const Tile t = single_n ? Tile{0, b * RL_ALLPAIRS, min(RL_ALLPAIRS, single_n - b * RL_ALLPAIRS), 1} : a.tiles[b];
+    SysDev S = a.sys[t.sys];
+    if (single_n) {
+        S.off = 0;
+        S.moff = 0;
+        S.n = single_n;
+        S.p = single_p;
+    }
+    allpairs_body<T, false, DIAM, true>(a, t, S, nullptr, qu);
+}
+
 // Stand-alone scatter into cell order (force and energy calls; a time step
 // on the neighbour list scatters inside the totals launch).
 template <typename Rec>
@@ -1312,6 +1332,11 @@ static void real_step_launch(const LaunchCfg &c, const RealArgs<T> &a, const Lis
 template <typename T>
 static void real_step_dispatch(const LaunchCfg &c, const RealArgs<T> &a, const ListArgs &la)
 {
+    if (c.all_pairs) {
+        launch_k(a.diam ? k_pairs_step<T, true> : k_pairs_step<T, false>, c.n_real_tiles, RL_BS, 0, c.stream, a,
+                 la.single_n, la.single_p);
+        return;
+    }
     switch (c.real_split) {
     case 1:
         real_step_launch<T, 1>(c, a, la);
