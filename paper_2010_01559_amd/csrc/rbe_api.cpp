@@ -135,6 +135,26 @@ void fourier_constants(const rbe_params &p, SysDev &s)
     s.hi_inv = std::ldexp(1.0f, -s.hi_bits);
 }
 
+// The single-precision pair constants from the double ones.
+void pair_constants(SysDev &s)
+{
+    PairConstF &c = s.pair;
+    c.rc2 = (float)s.rc2;
+    c.lj_rc2 = (float)s.lj_rc2;
+    c.beta = (float)s.beta;
+    c.nalpha_log2e = (float)(-s.alpha * 1.4426950408889634074);
+    c.two_beta_rsqrtpi = (float)(2.0 * s.beta / 1.7724538509055160273);
+    c.coulomb = (float)s.coulomb;
+    c.lj_sig2 = (float)s.lj_sig2;
+    c.eps4 = (float)(4.0 * s.lj_eps);
+    c.lj_shift = (float)s.lj_shift;
+    c.lj_on = s.lj_on && !s.diam_on;
+    c.scale = (float)(s.L * (1.0 / 4294967296.0));
+    c.rmax2u = (float)(s.rsearch2 / ((double)c.scale * (double)c.scale));
+    c.rsearch2_box = (float)(s.rsearch2 / (s.L * s.L) * (1.0 + 1e-6));
+    c.rlist2_box = (float)(s.rlist2 / (s.L * s.L) * (1.0 + 1e-6));
+}
+
 // Default tile shapes for ntot particles: one structure-factor block per
 // compute unit when the particles allow (the block's registers leave room
 // for one 1024-thread block per CU); four waves share a 64-particle tile in
@@ -353,7 +373,6 @@ struct rbe_ctx {
     std::vector<rbe_params> prm;
     std::vector<SysDev> sysh;
     std::vector<int> ntiles_rho;   // per system
-    std::vector<int> real_sys;     // system of each real-space tile
     int64_t ntot = 0;
     int mtot = 0;                  // active modes in total
     int mcap = 0;                  // capacity of the mode arrays
@@ -542,21 +561,17 @@ size_t partial_need(rbe_ctx *c, int chunk)
     return (size_t)run * 2;
 }
 
-// Real-space tiles: runs of RL_PPB cell-sorted slots for systems with at least
+// Real-space tiles: runs of real_rows_per_tile() cell-sorted slots for systems with at least
 // three cells per side (aux = 0), runs of real_allpairs_per_tile() particles in
 // original order for the all-pairs systems (aux = 1).
-void build_real_tiles(rbe_ctx *c, std::vector<Tile> &out, std::vector<int> &tile_sys)
+void build_real_tiles(rbe_ctx *c, std::vector<Tile> &out)
 {
     out.clear();
-    tile_sys.clear();
     for (int r = 0; r < c->R; ++r) {
         const SysDev &s = c->sysh[r];
         const int aux = s.nc == 1 ? 1 : 0;
         const int step = aux ? real_allpairs_per_tile() : real_rows_per_tile();
-        for (int k = 0; k < s.n; k += step) {
-            out.push_back(Tile{r, k, std::min(step, s.n - k), aux});
-            tile_sys.push_back(r);
-        }
+        for (int k = 0; k < s.n; k += step) out.push_back(Tile{r, k, std::min(step, s.n - k), aux});
     }
 }
 
@@ -713,8 +728,22 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         const double rmax = std::max(p.r_cut, p.lj_eps > 0.0 ? lj_reach(p) : 0.0);
         const double rlist = rmax + p.skin;
         int nc = (int)std::floor(p.box / rlist);
-        nc = std::min(nc, 128);
-        if (nc < 3) nc = 1;   // fewer than 3 cells along the box: one cell, all pairs
+        s.nh = 1;
+        if (nc < 3) {
+            nc = 1;   // fewer than 3 cells along the box: one cell, all pairs
+        } else {
+            // Cells of side radius / nh.  Where a cell of one radius would hold
+            // many particles, finer ones keep the candidates of the cell pass
+            // close to the search sphere (27 radius^3 against its 4.2 with
+            // nh = 1, about 10 with nh = 3); where it holds few, a wave's sixteen
+            // particles span several cells anyway and finer ones only add rows.
+            const double occ = (double)p.n * std::pow(rlist / p.box, 3.0);
+            s.nh = std::min(3, std::max(1, (int)std::cbrt(occ / 6.0)));
+            nc = std::min((int)std::floor(s.nh * p.box / rlist), 128);
+            // a wave takes sixteen particles of one row of cells at a time: at
+            // least about eight particles per row of a sparse system
+            nc = std::min(nc, std::max(3 * s.nh, (int)std::sqrt(p.n / 8.0)));
+        }
         s.nc = nc;
         s.ncell = nc * nc * nc;
         s.cell_off = cell_off;   // kept a multiple of 4 for vector loads of the counts
@@ -748,6 +777,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         s.use_list = (all_skin && nc >= 3) ? 1 : 0;
         s.rlist2 = rlist * rlist;
         s.half_skin2 = 0.25 * p.skin * p.skin;
+        pair_constants(s);
         if (s.use_list) {
             const double dens = (double)p.n / (p.box * p.box * p.box);
             const double mean = dens * 4.0 / 3.0 * kPi * rlist * rlist * rlist;
@@ -803,8 +833,35 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     g.n_force_tiles = (int)ftiles.size();
     g.n_part_tiles = (int)ptiles.size();
     std::vector<Tile> rtiles;
-    build_real_tiles(c, rtiles, c->real_sys);
+    build_real_tiles(c, rtiles);
     g.n_real_tiles = (int)rtiles.size();
+
+    // wave tiles of force, energy and adjoint calls: eight particles per wave
+    // while sixteen would leave most of the chip's 1024 SIMDs with fewer than
+    // four waves; the entries of all-pairs systems are fixed, the others are
+    // written with each cell list
+    g.cell_ppw = ntot < 65536 ? 8 : 16;
+    std::vector<Tile> ctiles, rowtiles;
+    bool any_pairs = false;
+    for (int r = 0; r < R; ++r) any_pairs = any_pairs || c->sysh[r].nc == 1;
+    int64_t nct = 0;
+    for (int r = 0; r < R; ++r) {
+        SysDev &s = c->sysh[r];
+        s.ctile_off = (int32_t)nct;
+        if (s.nc == 1) {
+            for (int k = 0; k < s.n; ++k) ctiles.push_back(Tile{r, k, 1, 1});
+            nct += s.n;
+        } else {
+            const int rows = s.nc * s.nc;
+            nct += s.n / g.cell_ppw + rows;
+            for (int k = 0; k < rows; k += 256) rowtiles.push_back(Tile{r, k, std::min(256, rows - k), 0});
+        }
+        // the four waves of a block share one system (and one use of the LDS)
+        nct = (nct + 3) & ~(int64_t)3;
+        if (any_pairs) ctiles.resize(nct, Tile{r, 0, 0, 0});
+    }
+    g.n_cell_tiles = (int)nct;
+    g.n_row_tiles = (int)rowtiles.size();
 
     // ---- device memory ----
     const size_t esz = c->prec == RBE_FP64 ? 8 : 4;
@@ -829,9 +886,21 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     } while (0)
     ALLOC(w.sys, sizeof(SysDev) * R);
     ALLOC(w.rho_tiles, sizeof(Tile) * max_rho_tiles);
-    ALLOC(w.force_tiles, sizeof(Tile) * ftiles.size());
-    ALLOC(w.part_tiles, sizeof(Tile) * ptiles.size());
-    ALLOC(w.real_tiles, sizeof(Tile) * rtiles.size());
+    // the tile lists that never change shape: one allocation, one upload
+    std::vector<Tile> tiles;
+    // (the wave tiles start as zeros, but for the entries of all-pairs systems)
+    Tile **const lists[] = {&w.force_tiles, &w.part_tiles, &w.real_tiles, &w.row_tiles};
+    size_t at[4], nt = 0;
+    for (const std::vector<Tile> *v : {&ftiles, &ptiles, &rtiles, &rowtiles}) {
+        at[nt++] = tiles.size();
+        tiles.insert(tiles.end(), v->begin(), v->end());
+    }
+    const size_t n_up = tiles.size();
+    if (any_pairs) tiles.insert(tiles.end(), ctiles.begin(), ctiles.end());
+    Tile *tile_base = nullptr;
+    ALLOC(tile_base, sizeof(Tile) * (n_up + (size_t)g.n_cell_tiles));
+    for (int k = 0; k < 4; ++k) *lists[k] = tile_base + at[k];
+    w.cell_tiles = tile_base + n_up;
     ALLOC(w.modes, sizeof(int32_t) * 3 * c->mcap);
     ALLOC(w.mode_w, sizeof(double) * c->mcap);
     ALLOC(w.partial, sizeof(double) * c->partial_cap);
@@ -853,7 +922,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     ALLOC(w.sorted, pack_sz * (ntot + 1));
     ALLOC(w.modes_alt, sizeof(int32_t) * 3 * c->mcap);
     ALLOC(w.mode_w_alt, sizeof(double) * c->mcap);
-    ALLOC(w.energy_part, sizeof(double) * 8 * rtiles.size());
+    ALLOC(w.energy_part, sizeof(double) * 8 * ((size_t)g.n_cell_tiles + R));
     ALLOC(w.flag, sizeof(int32_t) * 4);
     ALLOC(w.lflag, sizeof(int32_t) * 8);
     ALLOC(w.step_base, sizeof(uint64_t));
@@ -874,15 +943,14 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         ALLOC(w.nnb, sizeof(int32_t) * nlist);
     }
 #undef ALLOC
-    c->epart_h.resize(8 * rtiles.size());
+    c->epart_h.resize(8 * (size_t)R);
 
     auto up = [&](void *dst, const void *src, size_t bytes) -> bool {
         return hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) == hipSuccess;
     };
     bool ok = up(w.sys, c->sysh.data(), sizeof(SysDev) * R) &&
-              up(w.force_tiles, ftiles.data(), sizeof(Tile) * ftiles.size()) &&
-              up(w.part_tiles, ptiles.data(), sizeof(Tile) * ptiles.size()) &&
-              up(w.real_tiles, rtiles.data(), sizeof(Tile) * rtiles.size()) &&
+              up(tile_base, tiles.data(), sizeof(Tile) * tiles.size()) &&
+              (any_pairs || hipMemset(w.cell_tiles, 0, sizeof(Tile) * (size_t)g.n_cell_tiles) == hipSuccess) &&
               up(w.cdf, cdf.data(), sizeof(double) * cdf.size()) &&
               hipMemset(w.mh_state, 0, sizeof(int32_t) * 3 * R) == hipSuccess &&
               hipMemset(w.cell_count, 0, sizeof(int32_t) * cell_off) == hipSuccess &&
@@ -1551,10 +1619,12 @@ rbe_status rbe_energy(rbe_ctx *c, const void *pos, const void *q, const void *ve
     if (s != RBE_OK) return s;
     if ((s = cells_impl(c, pos, q)) != RBE_OK) return s;
     RUN(c, K_ENERGY, launch_energy(c->cfg, c->w, q, vel));
+    RUN(c, K_ENERGY, launch_energy_sum(c->cfg, c->w));
     std::vector<double> rho(2 * (size_t)c->mtot), wts(c->mtot);
     std::vector<int32_t> modes(3 * (size_t)c->mcap);
     int32_t flag[4] = {0, 0, 0, 0};
-    HIPCHK(c, hipMemcpyAsync(c->epart_h.data(), c->w.energy_part, sizeof(double) * c->epart_h.size(),
+    HIPCHK(c, hipMemcpyAsync(c->epart_h.data(), c->w.energy_part + 8 * (size_t)c->cfg.n_cell_tiles,
+                             sizeof(double) * c->epart_h.size(),
                              hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipMemcpyAsync(rho.data(), c->w.rho, sizeof(double) * rho.size(), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipMemcpyAsync(wts.data(), c->w.mode_w, sizeof(double) * wts.size(), hipMemcpyDeviceToHost, c->stream));
@@ -1565,11 +1635,7 @@ rbe_status rbe_energy(rbe_ctx *c, const void *pos, const void *q, const void *ve
         rbe_status es = take_device_errors(c, &flag[0]);
         if (es != RBE_OK) return es;
     }
-    std::vector<double> acc(8 * (size_t)c->R, 0.0);
-    for (size_t tile = 0; tile < c->real_sys.size(); ++tile) {
-        const int r = c->real_sys[tile];
-        for (int j = 0; j < 8; ++j) acc[8 * r + j] += c->epart_h[8 * tile + j];
-    }
+    const std::vector<double> &acc = c->epart_h;
     rbe_status ret = RBE_OK;
     for (int r = 0; r < c->R; ++r) {
         const SysDev &S = c->sysh[r];

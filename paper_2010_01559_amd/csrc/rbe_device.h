@@ -517,16 +517,63 @@ __device__ __forceinline__ bool record_update(const SysDev &S, int64_t i, double
     return moved;
 }
 
-// Inclusive prefix sum across the 64 lanes of a wave.
+// Inclusive prefix sum across the 64 lanes of a wave, with data-parallel
+// primitives (within rows of 16, then row ends broadcast to later rows): no
+// LDS round trips.
 __device__ __forceinline__ int wave_incl_scan(int v)
 {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(v, off, 64);
-        if (lane >= off) v += t;
-    }
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
     return v;
+}
+
+// v of the lane's own half (quarter pair) and of the other one, the lower
+// lanes' first: lanes l and l ^ 32 (l ^ 16) get the same two values.
+template <int XOR>
+__device__ __forceinline__ void lane_pair(uint32_t v, uint32_t &lower, uint32_t &upper)
+{
+    if constexpr (XOR == 32) {
+        const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        lower = r[0];
+        upper = r[1];
+    } else {
+        static_assert(XOR == 16, "rows of 16 or halves");
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        lower = r[0];
+        upper = r[1];
+    }
+}
+
+// v plus v of lane l ^ XOR (8, 16 or 32), the same value on both lanes.
+template <int XOR>
+__device__ __forceinline__ int lane_xor_sum(int v)
+{
+    if constexpr (XOR == 8) {
+        return v + __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false);   // row_ror:8
+    } else {
+        uint32_t a, b;
+        lane_pair<XOR>((uint32_t)v, a, b);
+        return (int)(a + b);
+    }
+}
+
+template <int XOR>
+__device__ __forceinline__ double lane_xor_sum(double v)
+{
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    if constexpr (XOR == 8) {
+        return v + __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, 0x128, 0xf, 0xf, false),
+                                    __builtin_amdgcn_update_dpp(0, lo, 0x128, 0xf, 0xf, false));
+    } else {
+        uint32_t la, lb, ha, hb;
+        lane_pair<XOR>((uint32_t)lo, la, lb);
+        lane_pair<XOR>((uint32_t)hi, ha, hb);
+        return __hiloint2double((int)ha, (int)la) + __hiloint2double((int)hb, (int)lb);
+    }
 }
 
 }  // namespace rbe

@@ -49,6 +49,16 @@ constexpr int32_t kFlagRange = 8;       // a single-precision real-space partial
 // Default bound on the spin iterations of a device-side wait.
 constexpr int32_t kWaitLimit = 1 << 24;
 
+// Single-precision constants of one system's pair terms, formed on the host so
+// that kernels read them by scalar loads and hold them in scalar registers.
+struct PairConstF {
+    float rc2, lj_rc2, beta, nalpha_log2e, two_beta_rsqrtpi, coulomb, lj_sig2, eps4, lj_shift;
+    int32_t lj_on;      // 0 with diameters: the LJ term is then formed in double (lj_offset)
+    float scale;        // box length of one 32-bit fixed-point unit
+    float rmax2u;       // search radius squared in fixed-point units
+    float rsearch2_box, rlist2_box;   // search and list radius squared in units of L^2, rounded up
+};
+
 // Per-system constants, resident in device memory and read by every kernel.
 struct SysDev {
     int32_t n;          // particles
@@ -58,6 +68,7 @@ struct SysDev {
     int32_t cdf_off;    // first entry of this system's cumulative table
     int32_t M;          // table covers m = -M..M
     int32_t nc;         // cells per box side (1 => all-pairs real space)
+    int32_t nh;         // cells that the search radius (cutoff + skin) reaches, 1 to 3: nc >= 3 nh
     int32_t cell_off;   // first cell of this system
     int32_t lj_on;
     int32_t integrator;
@@ -66,6 +77,8 @@ struct SysDev {
     int32_t use_list;      // neighbour list in rbe_step (skin > 0 and nc >= 3)
     int32_t hi_bits;       // FP32 phases: box fractions split as hi (multiple of 2^-hi_bits) + lo
     float hi_scale, hi_inv;  // 2^hi_bits, 2^-hi_bits
+    int32_t ctile_off;     // first wave tile of this system (Workspace::cell_tiles)
+    int32_t pad0;
     int32_t n_fixed;       // particles 0 .. n_fixed-1 never move
     int32_t diam_on;       // per-particle diameters: LJ with r_off = (d_i + d_j)/2 - sigma
     double L, invL;
@@ -84,6 +97,7 @@ struct SysDev {
     double rlist2;          // (largest cutoff + skin)^2
     double half_skin2;      // (skin / 2)^2
     uint64_t seed;
+    PairConstF pair;
 };
 
 // A contiguous run of particles of one system processed by one block.
@@ -151,7 +165,9 @@ struct Workspace {
     Tile *rho_tiles;       // structure-factor tiles
     Tile *force_tiles;     // force-pass tiles (64 particles)
     Tile *part_tiles;      // 256-particle tiles for elementwise kernels
-    Tile *real_tiles;      // real-space tiles (aux 0: cell-sorted rows, 1: all pairs)
+    Tile *real_tiles;      // real-space tiles of a step (aux 0: cell-sorted slots, 1: all pairs)
+    Tile *cell_tiles;      // wave tiles of force, energy and adjoint calls (see write_row_tiles)
+    Tile *row_tiles;       // runs of up to 256 rows of cells of one system
     int32_t *modes;        // [3][Mcap]
     double *mode_w;        // [Mcap] weights (S/p or explicit)
     double *partial;       // structure-factor tile partials
@@ -171,7 +187,7 @@ struct Workspace {
     void *sorted;          // [Ntot] same, sorted by cell
     int32_t *modes_alt;    // the next step's modes and weights when the totals launch draws them
     double *mode_w_alt;
-    double *energy_part;   // [real tiles][8]
+    double *energy_part;   // [wave tiles][8], then [R][8] sums
     int32_t *flag;         // [4] word 0: kFlag* error bits
     // neighbour list of rbe_step (allocated when some system uses it)
     Tile *list_tiles;      // list-pass tiles (aux 2: cell-sorted slots, 1: all pairs)
@@ -194,7 +210,9 @@ struct LaunchCfg {
     int prec;
     int64_t ntot;
     int mcap;
-    int n_rho_tiles, n_force_tiles, n_part_tiles, n_real_tiles;
+    int n_rho_tiles, n_force_tiles, n_part_tiles, n_real_tiles, n_row_tiles;
+    int n_cell_tiles;        // wave tiles (a multiple of four)
+    int cell_ppw;            // most particles of a wave tile: 16 or 8
     int max_sys_rho_tiles;   // most structure-factor tiles of one system
     int rho_chunk, rho_block, force_split, real_split;
     int ncell_tot;
@@ -259,6 +277,7 @@ hipError_t launch_real_step(const LaunchCfg &c, const Workspace &w, const ListSt
 hipError_t launch_real(const LaunchCfg &c, const Workspace &w, void *force, int accumulate, void *vel_kick,
                        uint64_t kick_step = 0);
 hipError_t launch_energy(const LaunchCfg &c, const Workspace &w, const void *q, const void *vel);
+hipError_t launch_energy_sum(const LaunchCfg &c, const Workspace &w);
 hipError_t launch_vjp_reduce(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q,
                              const void *gF);
 hipError_t launch_vjp_final(const LaunchCfg &c, const Workspace &w);

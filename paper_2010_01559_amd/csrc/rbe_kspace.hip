@@ -512,6 +512,8 @@ struct ForceArgs {
     const void *packed;
     int32_t *sorted_idx;
     void *sorted;
+    int n_blocks;          // force blocks; with scatter on, row-tile blocks follow
+    RowTileArgs rt;
     // gridDim.y > 1: the mode list is split over y; partial sums go to
     // fpart[y][3][ntot] and k_fsum finishes the particles
     T *fpart;
@@ -523,6 +525,10 @@ template <typename T, typename KM, int SPLIT, bool SINGLE>
 __global__ __launch_bounds__(256) void k_kforce(ForceArgs<T, KM> a)
 {
     __shared__ T red[4][3][64];
+    if (a.do_scatter && (int)blockIdx.x >= a.n_blocks) {
+        write_row_tiles(a.rt, blockIdx.x - a.n_blocks);
+        return;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int group = wave / SPLIT, part = wave % SPLIT;
@@ -1081,17 +1087,20 @@ hipError_t launch_mid(const LaunchCfg &c, const Workspace &w, int do_final, int 
 }
 
 template <typename T, typename KM, bool SINGLE>
-static void kforce_launch(int split, int n, int ys, hipStream_t st, const ForceArgs<T, KM> &a)
+static void kforce_launch(int split, int n, int ys, hipStream_t st, ForceArgs<T, KM> &a)
 {
+    const int rows = a.do_scatter ? a.rt.n : 0;
+    a.n_blocks = split == 1 ? (n + 3) / 4 : (split == 2 ? (n + 1) / 2 : n);
+    const dim3 g(a.n_blocks + rows, ys);
     switch (split) {
     case 1:
-        launch_k(k_kforce<T, KM, 1, SINGLE>, dim3((n + 3) / 4, ys), 256, 0, st, a);
+        launch_k(k_kforce<T, KM, 1, SINGLE>, g, 256, 0, st, a);
         break;
     case 2:
-        launch_k(k_kforce<T, KM, 2, SINGLE>, dim3((n + 1) / 2, ys), 256, 0, st, a);
+        launch_k(k_kforce<T, KM, 2, SINGLE>, g, 256, 0, st, a);
         break;
     default:
-        launch_k(k_kforce<T, KM, 4, SINGLE>, dim3(n, ys), 256, 0, st, a);
+        launch_k(k_kforce<T, KM, 4, SINGLE>, g, 256, 0, st, a);
         break;
     }
 }
@@ -1119,6 +1128,7 @@ static hipError_t kforce_dispatch(const LaunchCfg &c, const Workspace &w, const 
     a.packed = w.packed;
     a.sorted_idx = w.sorted_idx;
     a.sorted = w.sorted;
+    a.rt = row_tile_args(c, w);
     const int n = c.n_force_tiles;
     const int ys = mode_split > 1 && w.fpart ? mode_split : 1;
     a.single_n = c.R == 1 ? (int)c.ntot : 0;

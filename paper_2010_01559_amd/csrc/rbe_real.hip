@@ -16,20 +16,18 @@
 //         + 4 eps (6 (sigma/r)^6 - 12 (sigma/r)^12) / r^2        (r < R_c)
 // with beta = sqrt(alpha); the Coulomb part acts for r <= r_c.
 //
-// Work decomposition ("row lanes"): the 27-cell stencil of a particle is
-// nine rows of three x-adjacent cells, and each row is one lane.  A wave
-// holds seven particles x nine rows; the rows are contiguous ranges of the
-// cell-sorted particle array (two ranges where the row wraps in x), read
-// straight from global memory, where the array stays cache-resident.  A lane
-// first marks the partners within the largest cutoff in a 64-bit mask (a
-// cheap distance test, no branches) and then evaluates the pair terms over
-// the set bits, so the expensive terms do not diverge on the cutoff test.
-// Each lane accumulates its FP32 pair terms exactly (on a fixed grid, see
-// qterm); the nine row sums are added in a fixed order, so the result does not
-// depend on the order of the particles inside a cell (which comes from atomic
-// counters) nor on the path (cell or list pass).  Systems with fewer than
-// three cells per side use all-pairs tiles, one particle per wave
-// (allpairs_wave).
+// Work decomposition of the cell pass (cell_pairs): a wave takes sixteen
+// cell-sorted particles; the cells around them are nine rows of consecutive
+// cells, contiguous ranges of the cell-sorted array (two where a row wraps in
+// x).  The squared distances of the sixteen to their candidates come from the
+// matrix cores (a conservative test in single precision); the partners that
+// pass are listed in LDS and evaluated by four lanes per particle from the
+// exact records, so the pair terms do not diverge on the distance test.  Each
+// lane accumulates its FP32 pair terms exactly (on a fixed grid, see qterm),
+// so the result does not depend on the order of the particles inside a cell
+// (which comes from atomic counters) nor on the path (cell or list pass).
+// Systems with fewer than three cells per side use all-pairs tiles, one
+// particle per wave (allpairs_body).
 //
 // List pass: LPP lanes per particle walk its list in strides of LPP; the
 // LPP partial sums are combined by a fixed butterfly.
@@ -39,12 +37,12 @@
 
 #include "rbe_device.h"
 #include "rbe_internal.h"
+#include "rbe_roles.h"
 
 namespace rbe {
 
 constexpr int RL_BS = 256;                  // threads per block: 4 waves
-constexpr int RL_PPW = 7;                   // particles per wave (9 lanes each)
-constexpr int RL_PPB = 4 * RL_PPW;          // particles per block
+constexpr int RL_PPB = 64;                  // particles per cell-pass tile of a step (16 per wave)
 constexpr int RL_ALLPAIRS = 4;              // particles per all-pairs tile: one per wave
 
 int real_rows_per_tile() { return RL_PPB; }
@@ -96,28 +94,6 @@ template <typename T>
 __device__ __forceinline__ double qscale()
 {
     return sizeof(T) == 4 ? 0x1p-32 : 1.0;
-}
-
-// Single-precision constants of one system's pair terms, held in registers.
-struct PairConstF {
-    float rc2, lj_rc2, beta, nalpha_log2e, two_beta_rsqrtpi, coulomb, lj_sig2, eps4, lj_shift;
-    int lj_on;
-};
-
-__device__ __forceinline__ PairConstF pair_const_f(const SysDev &S)
-{
-    PairConstF c;
-    c.rc2 = (float)S.rc2;
-    c.lj_rc2 = (float)S.lj_rc2;
-    c.beta = (float)S.beta;
-    c.nalpha_log2e = (float)(-S.alpha * 1.4426950408889634074);
-    c.two_beta_rsqrtpi = (float)(2.0 * S.beta / 1.7724538509055160273);
-    c.coulomb = (float)S.coulomb;
-    c.lj_sig2 = (float)S.lj_sig2;
-    c.eps4 = (float)(4.0 * S.lj_eps);
-    c.lj_shift = (float)S.lj_shift;
-    c.lj_on = S.lj_on && !S.diam_on;   // with diameters the LJ term is formed in double (lj_offset)
-    return c;
 }
 
 // erfc(x) exp(x^2) = t * sum_k c_k t^k with t = 1/(1 + 0.47047 x), x >= 0: the
@@ -235,24 +211,7 @@ struct Geo {
 template <typename T>
 __device__ __forceinline__ Geo make_geo(const SysDev &S)
 {
-    Geo g;
-    const double rmax2 = S.rsearch2;
-    g.scale = (float)(S.L * (1.0 / 4294967296.0));
-    g.rmax2u = (float)(rmax2 / ((double)g.scale * (double)g.scale));
-    g.rmax2 = rmax2;
-    g.L = S.L;
-    return g;
-}
-
-// The same with the list radius (cutoff + skin) as search radius.
-__device__ __forceinline__ Geo list_geo(const SysDev &S)
-{
-    Geo g;
-    g.scale = (float)(S.L * (1.0 / 4294967296.0));
-    g.rmax2u = (float)(S.rlist2 / ((double)g.scale * (double)g.scale));
-    g.rmax2 = S.rlist2;
-    g.L = S.L;
-    return g;
+    return Geo{S.pair.scale, S.pair.rmax2u, S.rsearch2, S.L};
 }
 
 __device__ __forceinline__ bool near_test(const PackF &pa, const PackF &pb, const Geo &g)
@@ -308,104 +267,12 @@ __device__ __forceinline__ void cell_coords(const PartD &p, int nc, int &cx, int
     cz = cell_of_frac(p.z, nc);
 }
 
-// One stencil row of a particle: cells cx-1..cx+1 of row (yy, zz), x taken
-// modulo nc, as one or two contiguous ranges of cell-sorted slots.  Ranges of
-// at most 64 slots are scanned into hit masks (records within the search
-// radius, self excluded); longer ranges are left for a direct walk.
-struct RowScan {
-    int b0[2], b1[2];
-    uint64_t m[2];
-    int nseg;
-    bool walk;   // some range exceeds 64 slots
-};
-
-template <typename Rec>
-__device__ __forceinline__ void row_scan(const Rec &pa, int self, int cx, int yy, int zz, int nc,
-                                         const int32_t *st, const Rec *gs, const Geo &geo, RowScan &rs, int lo,
-                                         int hi)
-{
-    const int base = (zz * nc + yy) * nc;
-    if (cx >= 1 && cx + 1 < nc) {
-        rs.b0[0] = st[base + cx - 1];
-        rs.b1[0] = st[base + cx + 2];
-        rs.nseg = 1;
-    } else if (cx == 0) {
-        rs.b0[0] = st[base];
-        rs.b1[0] = st[base + 2];
-        rs.b0[1] = st[base + nc - 1];
-        rs.b1[1] = st[base + nc];
-        rs.nseg = 2;
-    } else {
-        rs.b0[0] = st[base + nc - 2];
-        rs.b1[0] = st[base + nc];
-        rs.b0[1] = st[base];
-        rs.b1[1] = st[base + 1];
-        rs.nseg = 2;
-    }
-    rs.walk = false;
-    rs.m[0] = rs.m[1] = 0;
-    if (rs.nseg == 1) rs.b0[1] = rs.b1[1] = lo;
-    // cell starts come from the last complete scan; clamped to the system's
-    // slots [lo, hi) every range stays in bounds whatever they hold
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        rs.b0[s] = min(max(rs.b0[s], lo), hi);
-        rs.b1[s] = min(max(rs.b1[s], rs.b0[s]), hi);
-    }
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int b0 = rs.b0[s], b1 = rs.b1[s];
-        uint64_t m = 0;
-        if (b1 - b0 <= 64) {
-            // two candidates per round, both loaded and tested without
-            // branches; their two bits enter the mask with one shift.  The
-            // second record is read even one past the segment (the record
-            // array ends with a padding record) and its bit dropped there;
-            // the particle itself is dropped once, after the loop
-            for (int b = b0; b < b1; b += 2) {
-                const Rec p0 = gs[b];
-                const Rec p1 = gs[b + 1];
-                const uint32_t h0 = (uint32_t)near_test(pa, p0, geo);
-                const uint32_t h1 = (uint32_t)near_test(pa, p1, geo) & (uint32_t)(b + 1 < b1);
-                m |= (uint64_t)(h0 | (h1 << 1)) << (b - b0);
-            }
-            if (self >= b0 && self < b1) m &= ~(1ull << (self - b0));
-        } else {
-            rs.walk = true;
-        }
-        rs.m[s] = m;
-    }
-}
-
-// Calls f(pb, b) for every hit of a scanned row (masks, then direct walks).
-template <typename Rec, typename F>
-__device__ __forceinline__ void row_visit(const Rec &pa, int self, const RowScan &rs, const Rec *gs, const Geo &geo,
-                                          F &&f)
-{
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int b0 = rs.b0[s], b1 = rs.b1[s];
-        if (b1 - b0 <= 64) {
-            uint64_t m = rs.m[s];
-            while (m) {
-                const int o = __builtin_ctzll(m);
-                m &= m - 1;
-                f(gs[b0 + o], b0 + o);
-            }
-        } else {
-            for (int b = b0; b < b1; ++b) {
-                if (b == self) continue;
-                const Rec pb = gs[b];
-                if (near_test(pa, pb, geo)) f(pb, b);
-            }
-        }
-    }
-}
-
 template <typename T>
 struct RealArgs {
     const SysDev *sys;
-    const Tile *tiles;       // aux = 0: row-lane tile of RL_PPB sorted slots; 1: all-pairs tile
+    const Tile *tiles;       // steps: block tiles (aux = 0: RL_PPB sorted slots; 1: all pairs); calls: wave tiles
+    const Tile *wave_tiles;
+    int single;              // single-system context
     const int32_t *start;
     const int32_t *sorted_idx;
     const void *sorted;
@@ -416,7 +283,7 @@ struct RealArgs {
     int accumulate;
     T *vel;                  // kick target (may be NULL); velocities for kinetic energy when ENERGY
     int32_t *flag;
-    double *epart;           // ENERGY: [tiles][8]
+    double *epart;           // ENERGY: [wave tiles][8]
     const void *km;          // per-mode force constants (KModeF / KModeD) for the fused Fourier force
     uint64_t kick_step;      // index of the step whose closing half kick is applied (its time step)
     const double *diam;      // per-particle diameters (original order) when some system has them
@@ -490,7 +357,7 @@ __device__ __forceinline__ typename PairCT<T>::type pair_consts(const SysDev &S)
 template <>
 __device__ __forceinline__ PairConstF pair_consts<float>(const SysDev &S)
 {
-    return pair_const_f(S);
+    return S.pair;
 }
 template <>
 __device__ __forceinline__ SysDev pair_consts<double>(const SysDev &S)
@@ -559,7 +426,6 @@ __device__ __forceinline__ void fourier_tile(const RealArgs<T> &a, const SysDev 
 template <typename T>
 __device__ __forceinline__ void add_fourier(Four<T> s4, int k, T qi, double &fx, double &fy, double &fz)
 {
-    if (!s4) return;
     T g[3];
     for (int d = 0; d < 3; ++d) g[d] = ((s4[0][k][d] + s4[1][k][d]) + s4[2][k][d]) + s4[3][k][d];
     fx += (double)(-qi * g[0]);
@@ -619,7 +485,7 @@ __device__ __forceinline__ void fourier_lanes(const RealArgs<T> &a, const SysDev
     for (int d = 0; d < 3; ++d) g[d] = wave_sum(g[d]);
 }
 
-// All-pairs tile of a one-cell system: wave w takes particle start + w, its
+// All-pairs real space of particle il of a one-cell system by one wave, its
 // lanes 64 partners at a time in original order.  The partners inside the
 // search radius go through the wave's LDS queue and are evaluated 64 at a
 // time, so the pair terms run on full waves whatever share of the partners is
@@ -631,16 +497,15 @@ __device__ __forceinline__ void fourier_lanes(const RealArgs<T> &a, const SysDev
 // mode per lane).  DIAM compiles the per-particle-diameter LJ (only launches
 // of contexts with diameters).
 template <typename T, bool ENERGY, bool DIAM, bool FOURIER>
-__device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, const Tile &t, const SysDev &S, double *ev,
+__device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, int il, const SysDev &S, double *ev,
                                               PairQueue<T, DIAM> &qu)
 {
     using Rec = typename RBT<T>::Rec;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (wave >= t.count) return;
     const Geo geo = make_geo<T>(S);
     const auto pc = pair_consts<T>(S);
     const Rec *pk = reinterpret_cast<const Rec *>(a.packed) + S.off;
-    const int il = t.start + wave, n = S.n;
+    const int n = S.n;
     const Rec pa = pk[il];
     const double da = DIAM && S.diam_on ? a.diam[S.off + il] : 0.0;
     double fx = 0, fy = 0, fz = 0;
@@ -708,158 +573,419 @@ __device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, const Tile &
     finish_particle<T, ENERGY>(a, S, S.off + il, fx, fy, fz, ev);
 }
 
-// Row-lane tile on the cell list.  With BUILD the rows are scanned with the
-// list radius and every hit is also written to the particle's list: the nine
-// row counts are prefixed in LDS so that the list keeps row order.
-template <bool ENERGY, bool BUILD>
-struct RowsLds {
-    double red[ENERGY ? 6 : 3][RL_BS];
-    int cnt[BUILD ? RL_BS : 1];
+// ---------------------------------------------------------------------------
+// Cell pass of one wave: every pair of its PPW (16 or 8) particles within the
+// search radius.  Lane l works for particle l mod PPW: the 4 (8) lanes of a
+// particle share its candidates.
+//  1. The particles are taken in segments: runs that lie in one row of cells
+//     and span few enough cells that the wrapped offsets from the segment's
+//     centre are minimum images for every pair within the radius.
+//  2. The candidates of a segment, the parts of the rows of cells around it
+//     that come within the radius, are numbered through and staged in LDS in
+//     chunks of kCellChunk: the records, and the offsets (-2u, |u|^2) from
+//     the segment's centre in box units.
+//  3. One 16x16x4 FP32 matrix product per sixteen candidates gives
+//     |u_i|^2 - R^2 + |u_j|^2 - 2 u_i.u_j, whose sign is the test: 256 pairs for
+//     one matrix instruction and four sign shifts, where a lane that tests
+//     its own particle's candidates takes about 15 instructions per pair of 64
+//     (and walks candidates of other particles' rows in step).  R^2 carries
+//     a margin above every rounding, so no pair is lost; what passes is
+//     evaluated from the exact records, whose terms test the cutoffs.
+//  4. Each lane appends its hits to its particle's list in LDS, and the lanes
+//     of a particle evaluate that list.
+// With eight particles per wave the matrix product has each of them in two
+// columns, each column taking every second group of sixteen candidates: twice
+// the waves and half the evaluations in each wave's chain, for launches that
+// would leave most wave slots of the chip empty.
+// ---------------------------------------------------------------------------
+constexpr int kCellChunk = 128;   // candidates per chunk: one 32-bit mask per lane
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <typename Rec>
+struct CellLds {
+    union {
+        float c[4][kCellChunk + 16];   // rows 16 banks apart: conflict-free operand reads
+        uint8_t hit[16][kCellChunk + 4];
+    };
+    Rec rec[kCellChunk];
+    int32_t slot[kCellChunk];
 };
 
-template <typename T, bool ENERGY, bool BUILD, bool DIAM>
-__device__ __forceinline__ void rows_body(const RealArgs<T> &a, const ListArgs *la, const Tile &t, const SysDev &S,
-                                          double *ev, RowsLds<ENERGY, BUILD> &lds, Four<T> s4 = nullptr)
+// Box fraction (x, y, z) of the segment's centre and a record's offset from it
+// in box units, wrapped.
+template <typename Rec>
+struct CellOrigin;
+template <>
+struct CellOrigin<PackF> {
+    uint32_t x, y, z;
+};
+template <>
+struct CellOrigin<PartD> {
+    double x, y, z;
+};
+
+// (any point near the centre will do: offsets of both sides are taken from it)
+__device__ __forceinline__ void cell_origin(float x, float y, float z, CellOrigin<PackF> &o)
+{
+    o.x = __builtin_amdgcn_readfirstlane((uint32_t)(x * 4294967040.0f));
+    o.y = __builtin_amdgcn_readfirstlane((uint32_t)(y * 4294967040.0f));
+    o.z = __builtin_amdgcn_readfirstlane((uint32_t)(z * 4294967040.0f));
+}
+__device__ __forceinline__ void cell_origin(float x, float y, float z, CellOrigin<PartD> &o)
+{
+    o.x = x;
+    o.y = y;
+    o.z = z;
+}
+__device__ __forceinline__ void cell_offset(const PackF &p, const CellOrigin<PackF> &o, float u[3])
+{
+    u[0] = (float)(int32_t)(p.x - o.x) * 0x1p-32f;
+    u[1] = (float)(int32_t)(p.y - o.y) * 0x1p-32f;
+    u[2] = (float)(int32_t)(p.z - o.z) * 0x1p-32f;
+}
+__device__ __forceinline__ void cell_offset(const PartD &p, const CellOrigin<PartD> &o, float u[3])
+{
+    const double x = p.x - o.x, y = p.y - o.y, z = p.z - o.z;
+    u[0] = (float)(x - rint(x));
+    u[1] = (float)(y - rint(y));
+    u[2] = (float)(z - rint(z));
+}
+
+// Calls pair(record, slot, k) for every partner of the lane's particle pa
+// (slot, active when act) that may lie within the search radius, split over
+// the particle's lanes; k numbers the particle's partners from 0.
+// Returns their number (the same on those lanes).  radius2: the search
+// radius squared in box units; st: the system's cell starts.
+template <typename T, int PPW, typename F>
+__device__ __forceinline__ int cell_pairs(const SysDev &S, const int32_t *st, const typename RBT<T>::Rec *gs,
+                                          const typename RBT<T>::Rec &pa, int slot, bool act, float radius2,
+                                          CellLds<typename RBT<T>::Rec> &w, F &&pair)
 {
     using Rec = typename RBT<T>::Rec;
-    auto &s_red = lds.red;
-    auto &s_cnt = lds.cnt;
-    const Geo geo = BUILD ? list_geo(S) : make_geo<T>(S);
+    const int lane = threadIdx.x & 63, i = lane & (PPW - 1), sub = lane >> 4;
+    constexpr uint32_t kParticles = (1u << PPW) - 1;
+    const int nc = __builtin_amdgcn_readfirstlane(S.nc), h = __builtin_amdgcn_readfirstlane(S.nh);
+    const int slo = S.off, shi = S.off + S.n;
+    int cx, cy, cz;
+    cell_coords<T>(pa, nc, cx, cy, cz);
+    const int row = cz * nc + cy;
+    const int span = max(nc - 2 * h - 1, 1);   // most cells along x of a segment
+    const int side = 2 * h + 1, nrows = side * side;
+    const float cell = 1.0f / (float)nc;
+    int listed = 0;
+    uint32_t todo = (uint32_t)__ballot(act) & kParticles;
+    while (todo) {
+        const int lead = __builtin_ctz(todo);
+        const int row0 = __builtin_amdgcn_readlane(row, lead), cx0 = __builtin_amdgcn_readlane(cx, lead);
+        const bool in = ((todo >> i) & 1) && row == row0 && (uint32_t)(cx - cx0) < (uint32_t)span;
+        const uint32_t seg = (uint32_t)__ballot(in) & kParticles;
+        const int cx1 = __builtin_amdgcn_readlane(cx, 31 - __builtin_clz(seg));
+        todo &= ~seg;
+        const int cy0 = __builtin_amdgcn_readlane(cy, lead), cz0 = __builtin_amdgcn_readlane(cz, lead);
+        // rows that wrap in x have two parts; part ids [0, nrows) are the
+        // first parts, [nrows, 2 nrows) the second ones
+        const int parts = (cx0 - h < 0 || cx1 + h >= nc) ? 2 * nrows : nrows;
+        // matrix operand of the sixteen: (u, 1) by component `sub`
+        CellOrigin<Rec> o;
+        cell_origin(0.5f * (float)(cx0 + cx1 + 1) * cell, ((float)cy0 + 0.5f) * cell, ((float)cz0 + 0.5f) * cell, o);
+        float ui[3];
+        cell_offset(pa, o, ui);
+        const float bop = sub == 0 ? ui[0] : (sub == 1 ? ui[1] : (sub == 2 ? ui[2] : 1.0f));
+        // offsets are at most ex in x and ey in y and z, so the product's
+        // terms stay below 4 (ex^2 + 2 ey^2); the margin covers their
+        // roundings several times over
+        const float ex = (0.5f * (float)(cx1 - cx0 + 1) + (float)h) * cell, ey = (0.5f + (float)h) * cell;
+        const float r2m = radius2 + 1e-5f * (ex * ex + 2.0f * ey * ey);
+        const float ci = in ? fmaf(ui[0], ui[0], fmaf(ui[1], ui[1], ui[2] * ui[2])) - r2m : 1e30f;
+        const f32x4 cop = {ci, ci, ci, ci};
+        for (int p0 = 0; p0 < parts; p0 += 64) {
+            // candidate ranges: lane l has part p0 + l
+            int rb = 0, rlen = 0;
+            const int v = p0 + lane;
+            const int q = v >= nrows ? v - nrows : v;
+            if (v < parts) {
+                const int qz = (q * (1024 / side + 1)) >> 10, qy = q - qz * side;   // q / side for q < 64, side <= 7
+                const int dz = qz - h, dy = qy - h;
+                int zz = cz0 + dz, yy = cy0 + dy;
+                zz += zz < 0 ? nc : (zz >= nc ? -nc : 0);
+                yy += yy < 0 ? nc : (yy >= nc ? -nc : 0);
+                // the row is at least gy, gz away from every particle of the
+                // segment: cells beyond the chord of the sphere are left out
+                const float gy = fmaxf(fabsf((float)dy) - 1.0f, 0.0f), gz = fmaxf(fabsf((float)dz) - 1.0f, 0.0f);
+                const float chord2 = radius2 * 1.00001f * (float)nc * (float)nc - (gy * gy + gz * gz);
+                const int hx = min(h, (int)ceilf(sqrtf(fmaxf(chord2, 0.0f)) * 1.00001f));
+                const int lo = cx0 - hx, hi = cx1 + hx;
+                int xa, xb;   // cells xa .. xb - 1 of the row
+                if (v < nrows) {
+                    xa = max(lo, 0);
+                    xb = min(hi, nc - 1) + 1;
+                } else {
+                    xa = lo < 0 ? lo + nc : 0;
+                    xb = lo < 0 ? nc : max(hi - nc + 1, 0);
+                }
+                if (chord2 < 0.0f) xb = xa;
+                const int base = (zz * nc + yy) * nc;
+                // cell starts come from the last complete scan; clamped to the
+                // system's slots every range stays in bounds whatever they hold
+                rb = min(max(st[base + xa], slo), shi);
+                rlen = min(max(st[base + xb], rb), shi) - rb;
+            }
+            const int incl = wave_incl_scan(rlen);
+            const int pre = incl - rlen, del = rb - pre;   // candidate k of range r is slot k + del
+            const int total = __builtin_amdgcn_readlane(incl, 63);
+            // this particle's own number among the candidates (it is in its
+            // own row, the middle one)
+            int self = -1;
+            for (int m = nrows / 2; m < parts; m += nrows) {
+                const int r = m - p0;
+                if (r < 0 || r >= 64) continue;
+                const int b0 = __builtin_amdgcn_readlane(rb, r), n = __builtin_amdgcn_readlane(rlen, r);
+                if ((uint32_t)(slot - b0) < (uint32_t)n) self = slot - __builtin_amdgcn_readlane(del, r);
+            }
+            int r0 = 0;   // first range of the chunk
+            for (int c0 = 0; c0 < total; c0 += kCellChunk) {
+                const int cnt = min(total - c0, kCellChunk);
+                // slots of the chunk's candidates
+                int d[2] = {0, 0}, r = r0;
+                for (; r < 64; ++r) {
+                    const int pr = __builtin_amdgcn_readlane(pre, r), dr = __builtin_amdgcn_readlane(del, r);
+                    if (pr >= c0 + cnt) break;
+                    d[0] = c0 + lane >= pr ? dr : d[0];
+                    d[1] = c0 + lane + 64 >= pr ? dr : d[1];
+                }
+                r0 = r - 1;   // the range that the chunk ends in may go on
+                Rec pb[2];
+                int sl[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int k = c0 + lane + 64 * u;
+                    sl[u] = k < total ? k + d[u] : -1;
+                    pb[u] = gs[max(sl[u], slo)];
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    float x[3];
+                    cell_offset(pb[u], o, x);
+                    const int k = lane + 64 * u;
+                    const bool ok = sl[u] >= 0;
+                    w.c[0][k] = ok ? -2.0f * x[0] : 0.0f;
+                    w.c[1][k] = ok ? -2.0f * x[1] : 0.0f;
+                    w.c[2][k] = ok ? -2.0f * x[2] : 0.0f;
+                    w.c[3][k] = ok ? fmaf(x[0], x[0], fmaf(x[1], x[1], x[2] * x[2])) : 1e30f;
+                    w.rec[k] = pb[u];
+                    w.slot[k] = sl[u];
+                }
+                wave_lds_order();
+                // lane (column, sub) gets candidates 16 g + 4 sub + t of group
+                // g in register t; their signs enter the mask from the right:
+                // candidate 16 g + 4 sub + t is bit 31 - (4 g + t)
+                uint32_t m = 0;
+#pragma unroll
+                for (int g = 0; g < 8; g += 4) {
+                    if (16 * g >= cnt) {
+                        m <<= 16;
+                        continue;
+                    }
+                    f32x4 y[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        y[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.c[sub][16 * (g + u) + (lane & 15)], bop, cop, 0, 0,
+                                                                    0);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int t = 0; t < 4; ++t) m = __builtin_amdgcn_alignbit(m, __float_as_uint(y[u][t]), 31);
+                }
+                const int sk = self - c0;
+                if ((uint32_t)sk < (uint32_t)kCellChunk && ((sk >> 2) & 3) == sub)
+                    m &= ~(0x80000000u >> (4 * (sk >> 4) + (sk & 3)));
+                // append to the particle's list, in the order of its lanes
+                // (the lists take the place of the operands)
+                wave_lds_order();
+                int at = 0, n, part = sub;
+                if constexpr (PPW == 8) {
+                    const bool odd = lane & 8;
+                    m &= odd ? 0x0F0F0F0Fu : 0xF0F0F0F0u;
+                    n = __builtin_popcount(m);
+                    const int both = lane_xor_sum<8>(n);
+                    at = odd ? both - n : 0;
+                    n = both;
+                    part = 2 * sub + (odd ? 1 : 0);
+                } else {
+                    n = __builtin_popcount(m);
+                }
+                uint32_t lower, upper;
+                lane_pair<16>((uint32_t)n, lower, upper);
+                at += (sub & 1) ? (int)lower : 0;
+                lane_pair<32>(lower + upper, lower, upper);
+                at += (sub & 2) ? (int)lower : 0;
+                n = (int)(lower + upper);
+                while (m) {
+                    const int b = __builtin_clz(m);
+                    m &= ~(0x80000000u >> b);
+                    w.hit[i][at++] = (uint8_t)(16 * (b >> 2) + 4 * sub + (b & 3));
+                }
+                wave_lds_order();
+                constexpr int kLanes = 64 / PPW;
+                for (int k = part; k < n; k += 2 * kLanes) {
+                    const bool two = k + kLanes < n;
+                    const int b0 = w.hit[i][k], b1 = w.hit[i][two ? k + kLanes : k];
+                    const Rec p0 = w.rec[b0], p1 = w.rec[b1];
+                    const int s0 = w.slot[b0], s1 = w.slot[b1];
+                    pair(p0, s0, listed + k);
+                    if (two) pair(p1, s1, listed + k + kLanes);
+                }
+                listed += n;
+                wave_lds_order();   // the next chunk reuses the LDS
+            }
+        }
+    }
+    return listed;
+}
+
+// Adds a value over the lanes that share a particle in the cell pass.
+template <int PPW>
+__device__ __forceinline__ double cell_sum(double v)
+{
+    if constexpr (PPW == 8) v = lane_xor_sum<8>(v);
+    return lane_xor_sum<32>(lane_xor_sum<16>(v));
+}
+
+// Cell pass of a wave over the cnt >= 1 slots from slot0 on of system `sys`.
+// With BUILD the search radius is the list radius and every partner is also
+// written to the particle's list.  The caller finishes the particles.
+struct CellSum {
+    double fx, fy, fz;
+    int32_t iorig;
+    bool first;   // the lane that finishes its particle
+};
+
+template <typename T, int PPW, bool ENERGY, bool BUILD, bool DIAM>
+__device__ __forceinline__ CellSum cells_body(const RealArgs<T> &a, const ListArgs *la, int sys, int slot0, int cnt,
+                                              const SysDev &S, double *ev, CellLds<typename RBT<T>::Rec> &lds, typename RBT<T>::Rec &pa)
+{
+    using Rec = typename RBT<T>::Rec;
+    const Geo geo = make_geo<T>(S);
     const auto pc = pair_consts<T>(S);
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
-    const int p = lane / 9, r = lane - 9 * (lane / 9);
-    const int k = wave * RL_PPW + p;
-    const bool act = lane < 9 * RL_PPW && k < t.count;
+    const int lane = threadIdx.x & 63;
+    CellSum c{0, 0, 0, 0, false};
+    const int k = lane & (PPW - 1);
+    const bool act = k < cnt;
+    const int slot = slot0 + min(k, cnt - 1);
+    const Rec *gs = reinterpret_cast<const Rec *>(a.sorted);
+    pa = gs[slot];
+    c.iorig = a.sorted_idx[slot];
+    const double da = DIAM && S.diam_on ? a.diam[c.iorig] : 0.0;
     double fx = 0, fy = 0, fz = 0, vir = 0;
     PairE e{0, 0};
-    int slot = -1;
-    const Rec *gs = reinterpret_cast<const Rec *>(a.sorted);
-    Rec pa{};
-    RowScan rs;
-    rs.nseg = 0;
-    rs.walk = false;
-    rs.b0[0] = rs.b0[1] = rs.b1[0] = rs.b1[1] = 0;
-    rs.m[0] = rs.m[1] = 0;
-    int64_t iorig = 0;   // original index, loaded with the record (see list_body)
-    if (act) {
-        slot = S.off + t.start + k;
-        pa = gs[slot];
-        iorig = a.sorted_idx[slot];
-        const int nc = S.nc;
-        int cx, cy, cz;
-        cell_coords<T>(pa, nc, cx, cy, cz);
-        const int zz = (cz + r / 3 - 1 + nc) % nc, yy = (cy + r % 3 - 1 + nc) % nc;
-        const int32_t *st = a.start + S.cell_off + t.sys;
-        row_scan(pa, slot, cx, yy, zz, nc, st, gs, geo, rs, S.off, S.off + S.n);
-    }
-    const double da = DIAM && act && S.diam_on ? a.diam[iorig] : 0.0;
-    int pos = 0, total = 0;
-    if constexpr (BUILD) {
-        const int cnt = __builtin_popcountll(rs.m[0]) + __builtin_popcountll(rs.m[1]);
-        s_cnt[tid] = cnt + (rs.walk ? (1 << 20) : 0);   // a walked row cannot be listed
-        __syncthreads();
-        if (act) {
-            const int first = tid - r;
-            for (int j = 0; j < 9; ++j) {
-                const int v = s_cnt[first + j];
-                if (j < r) pos += v;
-                total += v;
-            }
-        }
-    }
-    if (act) {
-        row_visit(pa, slot, rs, gs, geo, [&](const Rec &pb, int b) {
-            T dx, dy, dz, r2;
-            displacement(pa, pb, geo, dx, dy, dz, r2);
-            T phi = pair_phi<ENERGY>(pc, (T)pa.q, (T)pb.q, r2, e);
-            if (DIAM && S.diam_on)
-                phi += (T)lj_offset<ENERGY>(S, da, a.diam[a.sorted_idx[b]], r2_double(pa, pb, S.L), e);
-            const T ph = qphi(phi);
-            fx += qterm(ph * dx);
-            fy += qterm(ph * dy);
-            fz += qterm(ph * dz);
-            if constexpr (ENERGY) vir += 0.5 * (double)(phi * r2);
-            if constexpr (BUILD) {
-                if (pos < la->kmax) la->nbr[(int64_t)pos * a.ntot + slot] = b;
-                ++pos;
-            }
-        });
-    }
+    const float r2 = BUILD ? S.pair.rlist2_box : S.pair.rsearch2_box;
+    const int n = cell_pairs<T, PPW>(S, a.start + S.cell_off + sys, gs, pa, slot, act, r2, lds,
+                                [&](const Rec &pb, int b, int k) {
+        if constexpr (BUILD)
+            if (k < la->kmax) la->nbr[(int64_t)k * a.ntot + slot] = b;
+        if (b == slot) return;   // only where stale cell starts name a slot twice
+        T dx, dy, dz, d2;
+        displacement(pa, pb, geo, dx, dy, dz, d2);
+        T phi = pair_phi<ENERGY>(pc, (T)pa.q, (T)pb.q, d2, e);
+        if (DIAM && S.diam_on)
+            phi += (T)lj_offset<ENERGY>(S, da, a.diam[a.sorted_idx[b]], r2_double(pa, pb, S.L), e);
+        const T ph = qphi(phi);
+        fx += qterm(ph * dx);
+        fy += qterm(ph * dy);
+        fz += qterm(ph * dz);
+        if constexpr (ENERGY) vir += 0.5 * (double)(phi * d2);
+    });
     if constexpr (sizeof(T) == 4) range_check(fx, fy, fz, a.flag);
-    // add the nine row sums of each particle in row order
-    s_red[0][tid] = fx;
-    s_red[1][tid] = fy;
-    s_red[2][tid] = fz;
+    c.fx = cell_sum<PPW>(fx);
+    c.fy = cell_sum<PPW>(fy);
+    c.fz = cell_sum<PPW>(fz);
+    c.first = act && lane < PPW;
+    if constexpr (sizeof(T) == 4)
+        if (c.first) range_check(c.fx, c.fy, c.fz, a.flag);
     if constexpr (ENERGY) {
-        s_red[3][tid] = e.e_real;
-        s_red[4][tid] = e.e_lj;
-        s_red[5][tid] = vir;
+        ev[0] += e.e_real;
+        ev[1] += e.e_lj;
+        ev[2] += vir;
     }
-    __syncthreads();
-    if (act && r == 0) {
-        double sx = 0, sy = 0, sz = 0;
-        for (int j = 0; j < 9; ++j) {
-            sx += s_red[0][tid + j];
-            sy += s_red[1][tid + j];
-            sz += s_red[2][tid + j];
-        }
-        if constexpr (sizeof(T) == 4) range_check(sx, sy, sz, a.flag);
-        if constexpr (ENERGY)
-            for (int j = 0; j < 9; ++j) {
-                ev[0] += s_red[3][tid + j];
-                ev[1] += s_red[4][tid + j];
-                ev[2] += s_red[5][tid + j];
-            }
-        if constexpr (BUILD) {
+    if constexpr (BUILD)
+        if (c.first) {
             // an overflowing list is never read (the next step rebuilds)
-            const bool ok = total <= la->kmax;
-            la->nnb[slot] = ok ? total : 0;
+            const bool ok = n <= la->kmax;
+            la->nnb[slot] = ok ? n : 0;
             if (!ok) atomicOr(la->ls.overflow, 1);
         }
-        sx *= qscale<T>();
-        sy *= qscale<T>();
-        sz *= qscale<T>();
-        add_fourier<T>(s4, k, (T)pa.q, sx, sy, sz);
-        finish_particle<T, ENERGY>(a, S, iorig, sx, sy, sz, ev);
-    }
+    c.fx *= qscale<T>();
+    c.fy *= qscale<T>();
+    c.fz *= qscale<T>();
+    return c;
 }
 
-// Block partials of the energy sums.
-__device__ __forceinline__ void energy_block(double *ev, double *out)
+// The calling wave's tile (its own, so that a wave has one row of cells; see
+// write_row_tiles), in XCD order over the blocks.
+__device__ __forceinline__ int wave_tile(int nblocks)
 {
-    __shared__ double s_blk[8][RL_BS / 64];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int k = 0; k < 8; ++k) {
-        double v = ev[k];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-        if (lane == 0) s_blk[k][wave] = v;
-    }
-    __syncthreads();
-    if (tid < 8) {
-        double v = 0.0;
-        for (int w = 0; w < RL_BS / 64; ++w) v += s_blk[tid][w];
-        out[tid] = v;
-    }
+    return 4 * xcd_tile((int)blockIdx.x, nblocks) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
 
-template <typename T, bool ENERGY, bool DIAM>
-__global__ __launch_bounds__(RL_BS) void k_real_rows(RealArgs<T> a)
+// Real space of force and energy calls, a wave tile per wave.  Bound by the
+// VALU work of the pair terms and hit lists and, at small N, by the wave's chain of
+// dependent loads.  Against one row of cells per lane (nine lanes a particle,
+// tiles across rows, rows of more than 64 particles walked directly), force calls,
+// trace times: N = 1e5 at density 0.1 48.5 -> 28 us, N = 3e4 23 -> 15 us,
+// N = 3e4 with r_c = 13.6 (1060 partners) 778 -> 179 us; the step that builds the
+// lists at N = 1e5 68 -> 45 us.
+template <typename T, int PPW, bool ENERGY, bool DIAM>
+__global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? (ENERGY ? 6 : 7) : 1) void k_real_rows(RealArgs<T> a)
 {
-    const Tile t = a.tiles[blockIdx.x];
-    const SysDev S = a.sys[t.sys];
-    // a block runs one of the two bodies
+    // a wave runs one of the two bodies on its own part of either member
     __shared__ union {
         PairQueue<T, DIAM> pairs;
-        RowsLds<ENERGY, false> rows;
+        CellLds<typename RBT<T>::Rec> cells[RL_BS / 64];
     } lds;
+    const int wt = wave_tile((int)gridDim.x);
+    const Tile t = a.tiles[wt];
+    const SysDev S = a.sys[a.single ? 0 : t.sys];
     double ev[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (t.aux == 1)
-        allpairs_body<T, ENERGY, DIAM, false>(a, t, S, ev, lds.pairs);
-    else
-        rows_body<T, ENERGY, false, DIAM>(a, nullptr, t, S, ev, lds.rows);
-    if constexpr (ENERGY) energy_block(ev, a.epart + 8 * blockIdx.x);
+    if (t.aux == 1) {
+        allpairs_body<T, ENERGY, DIAM, false>(a, t.start, S, ev, lds.pairs);
+    } else if (t.count > 0) {
+        typename RBT<T>::Rec pa;
+        const CellSum c = cells_body<T, PPW, ENERGY, false, DIAM>(a, nullptr, t.sys, S.off + t.start, t.count, S, ev,
+                                                                  lds.cells[threadIdx.x >> 6], pa);
+        if (c.first) finish_particle<T, ENERGY>(a, S, c.iorig, c.fx, c.fy, c.fz, ev);
+    }
+    if constexpr (ENERGY) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) ev[k] = wave_sum(ev[k]);
+        if ((threadIdx.x & 63) == 0)
+            for (int k = 0; k < 8; ++k) a.epart[8 * (int64_t)wt + k] = ev[k];
+    }
+}
+
+// Sums of the wave tiles' energy partials per system, in a fixed order: a
+// block per system, eight lanes per tile and one sum each.
+__global__ __launch_bounds__(1024) void k_energy_sum(const SysDev *__restrict__ sys, int R, int n_tiles,
+                                                     const double *__restrict__ part, double *__restrict__ out)
+{
+    __shared__ double red[1024];
+    const int r = blockIdx.x, tid = threadIdx.x;
+    const int e1 = r + 1 < R ? sys[r + 1].ctile_off : n_tiles;
+    double v = 0.0;
+    int e = sys[r].ctile_off + (tid >> 3);
+    for (; e + 3 * 128 < e1; e += 4 * 128) {
+        double x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = part[8 * (int64_t)(e + 128 * u) + (tid & 7)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v += x[u];
+    }
+    for (; e < e1; e += 128) v += part[8 * (int64_t)e + (tid & 7)];
+    red[tid] = v;
+    for (int w = 512; w >= 8; w >>= 1) {
+        __syncthreads();
+        if (tid < w) red[tid] += red[tid + w];
+    }
+    if (tid < 8) out[8 * r + tid] = red[tid];
 }
 
 // List tile: LPP lanes per cell-sorted slot, U partners per lane and round.
@@ -876,7 +1002,7 @@ constexpr int kListU = 4;
 template <typename T>
 struct ListHead {
     typename RBT<T>::Rec pa;
-    int64_t iorig;
+    int32_t iorig;
     int n, slot;
     int b[kListU];
 };
@@ -1003,16 +1129,14 @@ __device__ __forceinline__ int wave_slot() { return __builtin_amdgcn_s_getreg((4
 // offsets (both 0) and its mode count from the launch, so that the record and
 // mode-constant loads do not wait for the tile and the system constants.
 template <typename T, int LPP, bool DIAM, bool SINGLE>
-__global__ __launch_bounds__(RL_BS) void k_real_step(RealArgs<T> a, ListArgs la)
+__global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 6 : 1) void k_real_step(RealArgs<T> a, ListArgs la)
 {
     __shared__ union {
-        struct {
-            T s4[4][FT_MAX][3];
-            RowsLds<false, true> rows;
-        } c;
+        T s4[4][FT_MAX][3];
+        CellLds<typename RBT<T>::Rec> cells[RL_BS / 64];
         PairQueue<T, DIAM> pairs;
     } lds;
-    auto &s4 = lds.c.s4;
+    auto &s4 = lds.s4;
     // both flags are read before anything is stored, so that neither read
     // waits for the other
     const int poison = *la.ls.poison;
@@ -1060,13 +1184,25 @@ __global__ __launch_bounds__(RL_BS) void k_real_step(RealArgs<T> a, ListArgs la)
         list_finish<T, LPP>(a, t, S, h, s4, fx, fy, fz);
         return;
     }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (allpairs) {
-        allpairs_body<T, false, DIAM, true>(a, t, S, nullptr, lds.pairs);
+        if (wave < t.count) allpairs_body<T, false, DIAM, true>(a, t.start + wave, S, nullptr, lds.pairs);
         return;
     }
+    // rebuild step: the pairs first, then the Fourier force, whose quarter sums
+    // take the LDS of the pairs
+    typename RBT<T>::Rec pa;
+    CellSum c{0, 0, 0, 0, false};
+    if (16 * wave < t.count)
+        c = cells_body<T, 16, false, true, DIAM>(a, &la, t.sys, S.off + t.start + 16 * wave, min(16, t.count - 16 * wave), S,
+                                                 nullptr, lds.cells[wave], pa);
+    __syncthreads();
     fourier_tile<T>(a, S, a.sorted, S.off + t.start, t.count, s4);
     __syncthreads();
-    rows_body<T, false, true, DIAM>(a, &la, t, S, nullptr, lds.c.rows, s4);
+    if (c.first) {
+        add_fourier<T>(s4, 16 * wave + (int)(threadIdx.x & 15), (T)pa.q, c.fx, c.fy, c.fz);
+        finish_particle<T, false>(a, S, c.iorig, c.fx, c.fy, c.fz, nullptr);
+    }
 }
 
 // Force pass of a time step of a context that has only one-cell systems:
@@ -1086,17 +1222,24 @@ __global__ __launch_bounds__(RL_BS) void k_pairs_step(RealArgs<T> a, int single_
         S.n = single_n;
         S.p = single_p;
     }
-    allpairs_body<T, false, DIAM, true>(a, t, S, nullptr, qu);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave < t.count) allpairs_body<T, false, DIAM, true>(a, t.start + wave, S, nullptr, qu);
 }
 
 // Stand-alone scatter into cell order (force and energy calls; a time step
-// on the neighbour list scatters inside the totals launch).
+// on the neighbour list scatters inside the totals launch), then blocks that
+// write the wave tiles.
 template <typename Rec>
 __global__ __launch_bounds__(256) void k_scatter(const SysDev *__restrict__ sys, const Tile *__restrict__ tiles,
                                                  const int32_t *__restrict__ start, const int32_t *__restrict__ cellid,
                                                  const int32_t *__restrict__ rank, const Rec *__restrict__ packed,
-                                                 int32_t *__restrict__ sorted_idx, Rec *__restrict__ sorted)
+                                                 int32_t *__restrict__ sorted_idx, Rec *__restrict__ sorted, int n_tiles,
+                                                 RowTileArgs rt)
 {
+    if ((int)blockIdx.x >= n_tiles) {
+        write_row_tiles(rt, blockIdx.x - n_tiles);
+        return;
+    }
     const Tile t = tiles[blockIdx.x];
     if ((int)threadIdx.x >= t.count) return;
     const int64_t i = sys[t.sys].off + t.start + threadIdx.x;
@@ -1112,7 +1255,7 @@ __global__ __launch_bounds__(256) void k_scatter(const SysDev *__restrict__ sys,
 //   dLoss/dr_i += sum_j [ -(phi'(r)/r)(dG.d) d - phi dG ]
 // G(r)/r = erfc(beta r)/r^3 + 2 beta exp(-alpha r^2)/(sqrt(pi) r^2), whose
 // derivative is -3 erfc/r^4 - 6 beta e/(sqrt(pi) r^3) - 4 beta^3 e/(sqrt(pi) r).
-// Same row-lane decomposition as the force.
+// Same decomposition as the force.
 // ---------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ void vjp_pair(const SysDev &S, T qi, T qj, T dx, T dy, T dz, T r2, T Gx, T Gy, T Gz,
@@ -1148,14 +1291,14 @@ __device__ __forceinline__ void vjp_pair(const SysDev &S, T qi, T qj, T dx, T dy
     rz -= (double)(dphi_r * GD * dz + phi * Gz);
 }
 
-template <typename T>
+template <typename T, int PPW>
 __global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__restrict__ gF, T *__restrict__ gpos,
                                                     T *__restrict__ gq, int accumulate)
 {
     using Rec = typename RBT<T>::Rec;
-    __shared__ double s_red[4][RL_BS];
-    const Tile t = a.tiles[blockIdx.x];
-    const SysDev S = a.sys[t.sys];
+    __shared__ CellLds<typename RBT<T>::Rec> lds[RL_BS / 64];
+    const Tile t = a.tiles[wave_tile((int)gridDim.x)];
+    const SysDev S = a.sys[a.single ? 0 : t.sys];
     const Geo geo = make_geo<T>(S);
     const int tid = threadIdx.x;
     const int64_t ntot = a.ntot;
@@ -1174,9 +1317,8 @@ __global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__re
     if (t.aux == 1) {
         // a particle per wave (as in allpairs_body), a partner per lane
         const Rec *pk = reinterpret_cast<const Rec *>(a.packed) + S.off;
-        const int w = tid >> 6;
-        if (w < t.count) {
-            const int il = t.start + w;
+        {
+            const int il = t.start;
             const int64_t i = S.off + il;
             const Rec pa = pk[il];
             const T Gix = gF[i], Giy = gF[ntot + i], Giz = gF[2 * ntot + i];
@@ -1199,48 +1341,28 @@ __global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__re
         }
         return;
     }
-    const int wave = tid >> 6, lane = tid & 63;
-    const int p = lane / 9, r = lane - 9 * (lane / 9);
-    const int k = wave * RL_PPW + p;
-    const bool act = lane < 9 * RL_PPW && k < t.count;
+    const int lane = tid & 63, k = lane & (PPW - 1);
+    const bool act = k < t.count;
+    if (t.count <= 0) return;
+    const int slot = S.off + t.start + min(k, t.count - 1);
+    const Rec *gs = reinterpret_cast<const Rec *>(a.sorted);
+    const Rec pa = gs[slot];
+    const int64_t i = a.sorted_idx[slot];
+    const T Gix = gF[i], Giy = gF[ntot + i], Giz = gF[2 * ntot + i];
     double dq = 0, rx = 0, ry = 0, rz = 0;
-    int slot = -1;
-    if (act) {
-        slot = S.off + t.start + k;
-        const Rec *gs = reinterpret_cast<const Rec *>(a.sorted);
-        const Rec pa = gs[slot];
-        const int64_t i = a.sorted_idx[slot];
-        const T Gix = gF[i], Giy = gF[ntot + i], Giz = gF[2 * ntot + i];
-        const int nc = S.nc;
-        int cx, cy, cz;
-        cell_coords<T>(pa, nc, cx, cy, cz);
-        const int zz = (cz + r / 3 - 1 + nc) % nc, yy = (cy + r % 3 - 1 + nc) % nc;
-        const int32_t *st = a.start + S.cell_off + t.sys;
-        RowScan rs;
-        row_scan(pa, slot, cx, yy, zz, nc, st, gs, geo, rs, S.off, S.off + S.n);
-        row_visit(pa, slot, rs, gs, geo, [&](const Rec &pb, int b) {
-            T dx, dy, dz, r2;
-            displacement(pa, pb, geo, dx, dy, dz, r2);
-            const int64_t jj = a.sorted_idx[b];
-            vjp_pair<T>(S, (T)pa.q, (T)pb.q, dx, dy, dz, r2, Gix - gF[jj], Giy - gF[ntot + jj],
-                        Giz - gF[2 * ntot + jj], dq, rx, ry, rz);
-        });
-    }
-    s_red[0][tid] = dq;
-    s_red[1][tid] = rx;
-    s_red[2][tid] = ry;
-    s_red[3][tid] = rz;
-    __syncthreads();
-    if (act && r == 0) {
-        double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-        for (int j = 0; j < 9; ++j) {
-            a0 += s_red[0][tid + j];
-            a1 += s_red[1][tid + j];
-            a2 += s_red[2][tid + j];
-            a3 += s_red[3][tid + j];
-        }
-        finish(a.sorted_idx[slot], a0, a1, a2, a3);
-    }
+    cell_pairs<T, PPW>(S, a.start + S.cell_off + t.sys, gs, pa, slot, act, S.pair.rsearch2_box, lds[tid >> 6],
+                       [&](const Rec &pb, int b, int) {
+        T dx, dy, dz, r2;
+        displacement(pa, pb, geo, dx, dy, dz, r2);
+        const int64_t jj = a.sorted_idx[b];
+        vjp_pair<T>(S, (T)pa.q, (T)pb.q, dx, dy, dz, r2, Gix - gF[jj], Giy - gF[ntot + jj], Giz - gF[2 * ntot + jj], dq,
+                    rx, ry, rz);
+    });
+    dq = cell_sum<PPW>(dq);
+    rx = cell_sum<PPW>(rx);
+    ry = cell_sum<PPW>(ry);
+    rz = cell_sum<PPW>(rz);
+    if (act && lane < PPW) finish(i, dq, rx, ry, rz);
 }
 
 __global__ void k_fill_zero(uint32_t *p, int64_t n)
@@ -1260,16 +1382,19 @@ hipError_t launch_fill_zero(hipStream_t s, void *ptr, int64_t nbytes)
     return hipGetLastError();
 }
 
+template <typename Rec>
+static void scatter_launch(const LaunchCfg &c, const Workspace &w)
+{
+    launch_k(k_scatter<Rec>, c.n_part_tiles + c.n_row_tiles, 256, 0, c.stream, w.sys, w.part_tiles, w.cell_start, w.cellid,
+             w.rank, (const Rec *)w.packed, w.sorted_idx, (Rec *)w.sorted, c.n_part_tiles, row_tile_args(c, w));
+}
+
 hipError_t launch_scatter(const LaunchCfg &c, const Workspace &w)
 {
     if (c.prec == RBE_FP64)
-        launch_k(k_scatter<PartD>, c.n_part_tiles, 256, 0, c.stream, w.sys, w.part_tiles, w.cell_start, w.cellid, w.rank,
-                                                               (const PartD *)w.packed, w.sorted_idx,
-                                                               (PartD *)w.sorted);
+        scatter_launch<PartD>(c, w);
     else
-        launch_k(k_scatter<PackF>, c.n_part_tiles, 256, 0, c.stream, w.sys, w.part_tiles, w.cell_start, w.cellid, w.rank,
-                                                               (const PackF *)w.packed, w.sorted_idx,
-                                                               (PackF *)w.sorted);
+        scatter_launch<PackF>(c, w);
     return hipGetLastError();
 }
 
@@ -1281,6 +1406,8 @@ static RealArgs<T> real_args(const LaunchCfg &c, const Workspace &w, void *force
     a.kick_step = kick_step;
     a.sys = w.sys;
     a.tiles = w.real_tiles;
+    a.wave_tiles = w.cell_tiles;
+    a.single = c.R == 1;
     a.start = w.cell_start;
     a.sorted_idx = w.sorted_idx;
     a.sorted = w.sorted;
@@ -1297,18 +1424,26 @@ static RealArgs<T> real_args(const LaunchCfg &c, const Workspace &w, void *force
     return a;
 }
 
-hipError_t launch_real(const LaunchCfg &c, const Workspace &w, void *force, int accumulate, void *vel_kick,
-                       uint64_t kick_step)
+template <typename T, bool ENERGY>
+static void real_rows_launch(const LaunchCfg &c, RealArgs<T> a)
 {
     // the per-particle-diameter LJ only in launches that need it: it costs
     // the others registers (and with them resident blocks)
-    const bool diam = w.diam != nullptr;
-    if (c.prec == RBE_FP64)
-        launch_k(diam ? k_real_rows<double, false, true> : k_real_rows<double, false, false>, c.n_real_tiles, RL_BS, 0,
-                 c.stream, real_args<double>(c, w, force, accumulate, vel_kick, nullptr, kick_step));
+    a.tiles = a.wave_tiles;
+    const int nb = c.n_cell_tiles / 4;
+    if (c.cell_ppw == 8)
+        launch_k(a.diam ? k_real_rows<T, 8, ENERGY, true> : k_real_rows<T, 8, ENERGY, false>, nb, RL_BS, 0, c.stream, a);
     else
-        launch_k(diam ? k_real_rows<float, false, true> : k_real_rows<float, false, false>, c.n_real_tiles, RL_BS, 0,
-                 c.stream, real_args<float>(c, w, force, accumulate, vel_kick, nullptr, kick_step));
+        launch_k(a.diam ? k_real_rows<T, 16, ENERGY, true> : k_real_rows<T, 16, ENERGY, false>, nb, RL_BS, 0, c.stream, a);
+}
+
+hipError_t launch_real(const LaunchCfg &c, const Workspace &w, void *force, int accumulate, void *vel_kick,
+                       uint64_t kick_step)
+{
+    if (c.prec == RBE_FP64)
+        real_rows_launch<double, false>(c, real_args<double>(c, w, force, accumulate, vel_kick, nullptr, kick_step));
+    else
+        real_rows_launch<float, false>(c, real_args<float>(c, w, force, accumulate, vel_kick, nullptr, kick_step));
     return hipGetLastError();
 }
 
@@ -1377,29 +1512,35 @@ hipError_t launch_real_step(const LaunchCfg &c, const Workspace &w, const ListSt
 
 hipError_t launch_energy(const LaunchCfg &c, const Workspace &w, const void *q, const void *vel)
 {
-    const bool diam = w.diam != nullptr;
     if (c.prec == RBE_FP64)
-        launch_k(diam ? k_real_rows<double, true, true> : k_real_rows<double, true, false>, c.n_real_tiles, RL_BS, 0,
-                 c.stream, real_args<double>(c, w, nullptr, 0, (void *)vel, q));
+        real_rows_launch<double, true>(c, real_args<double>(c, w, nullptr, 0, (void *)vel, q));
     else
-        launch_k(diam ? k_real_rows<float, true, true> : k_real_rows<float, true, false>, c.n_real_tiles, RL_BS, 0,
-                 c.stream, real_args<float>(c, w, nullptr, 0, (void *)vel, q));
+        real_rows_launch<float, true>(c, real_args<float>(c, w, nullptr, 0, (void *)vel, q));
     return hipGetLastError();
+}
+
+hipError_t launch_energy_sum(const LaunchCfg &c, const Workspace &w)
+{
+    launch_k(k_energy_sum, c.R, 1024, 0, c.stream, w.sys, c.R, c.n_cell_tiles, w.energy_part,
+             w.energy_part + 8 * (int64_t)c.n_cell_tiles);
+    return hipGetLastError();
+}
+
+template <typename T>
+static void vjp_real_launch(const LaunchCfg &c, RealArgs<T> a, const void *gF, void *gpos, void *gq, int accumulate)
+{
+    a.tiles = a.wave_tiles;
+    launch_k(c.cell_ppw == 8 ? k_vjp_real<T, 8> : k_vjp_real<T, 16>, c.n_cell_tiles / 4, RL_BS, 0, c.stream, a,
+             (const T *)gF, (T *)gpos, (T *)gq, accumulate);
 }
 
 hipError_t launch_vjp_real(const LaunchCfg &c, const Workspace &w, const void *gF, void *gpos, void *gq,
                            int accumulate)
 {
     if (c.prec == RBE_FP64)
-        launch_k(k_vjp_real<double>, c.n_real_tiles, RL_BS, 0, c.stream, real_args<double>(c, w, nullptr, 0, nullptr,
-                                                                                     nullptr),
-                                                                   (const double *)gF, (double *)gpos,
-                                                                   (double *)gq, accumulate);
+        vjp_real_launch<double>(c, real_args<double>(c, w, nullptr, 0, nullptr, nullptr), gF, gpos, gq, accumulate);
     else
-        launch_k(k_vjp_real<float>, c.n_real_tiles, RL_BS, 0, c.stream, real_args<float>(c, w, nullptr, 0, nullptr,
-                                                                                   nullptr),
-                                                                  (const float *)gF, (float *)gpos, (float *)gq,
-                                                                  accumulate);
+        vjp_real_launch<float>(c, real_args<float>(c, w, nullptr, 0, nullptr, nullptr), gF, gpos, gq, accumulate);
     return hipGetLastError();
 }
 

@@ -495,6 +495,41 @@ __device__ void rebuild_scatter(const RebuildArgs &a, int b, int nb)
 }
 
 
+// Wave tiles of the cell pass of a force, energy or adjoint call, written from
+// the cell starts by the launch that scatters the particles into cell order:
+// runs of at most ppw = 2^lg slots of one row of cells, so that a wave has one
+// set of candidates (a run across two rows has two, and with every wave of a
+// launch resident at once the launch lasted twice the average wave).  Row
+// `row` of a system takes the entries from base = floor(a0 / ppw) + row, a0
+// its first slot: one or two more than it needs at most, left empty, which
+// spares a prefix sum over the rows.
+struct RowTileArgs {
+    const SysDev *sys;
+    const Tile *rows;
+    const int32_t *start;
+    Tile *out;
+    int n;    // row tiles
+    int lg;   // log2 of the particles per wave tile
+};
+
+__device__ __forceinline__ void write_row_tiles(const RowTileArgs &a, int b)
+{
+    const Tile t = a.rows[b];
+    if ((int)threadIdx.x >= t.count) return;
+    const SysDev &S = a.sys[t.sys];
+    const int row = t.start + threadIdx.x;
+    const int32_t *st = a.start + S.cell_off + t.sys + row * S.nc;
+    const int a0 = min(max(st[0] - S.off, 0), S.n), a1 = min(max(st[S.nc] - S.off, a0), S.n);
+    const int base = S.ctile_off + (a0 >> a.lg) + row, end = S.ctile_off + (a1 >> a.lg) + row + 1;
+    for (int e = base, s = a0; e < end; ++e, s += 1 << a.lg)
+        a.out[e] = Tile{t.sys, min(s, a1), max(min(1 << a.lg, a1 - s), 0), 0};
+}
+
+inline RowTileArgs row_tile_args(const LaunchCfg &c, const Workspace &w)
+{
+    return RowTileArgs{w.sys, w.row_tiles, w.cell_start, w.cell_tiles, c.n_row_tiles, c.cell_ppw == 16 ? 4 : 3};
+}
+
 // Next step's modes of system b (exact sampler), drawn by one block; the
 // cumulative table is read from tab when given (the caller has room for it in
 // LDS), else from global memory.
