@@ -821,6 +821,8 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     g.ncell_tot = cell_off;
     g.max_cells = max_cells;
     g.max_p = c->max_p;
+    g.max_n = 0;
+    for (int r = 0; r < R; ++r) g.max_n = std::max(g.max_n, c->sysh[r].n);
     g.max_table = max_table;
     g.wait_limit = kWaitLimit;
 

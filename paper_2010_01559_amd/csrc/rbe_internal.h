@@ -218,6 +218,7 @@ struct LaunchCfg {
     int ncell_tot;
     int max_cells;   // largest cell count of one system
     int max_p;
+    int max_n;       // particles of the largest system
     int max_table;   // largest cumulative table (2M + 1)
     int list_on;     // some system uses the neighbour list
     int all_pairs;   // every system has one cell: steps run without any list or cell work
