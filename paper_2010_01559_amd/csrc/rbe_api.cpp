@@ -398,6 +398,8 @@ struct rbe_ctx {
     LaunchCfg cfg{};
     Workspace w{};
     size_t partial_cap = 0;        // doubles allocated for partial
+    void *col_mem = nullptr;       // buffers of a dense mode list (one of allocs)
+    size_t col_bytes = 0;
     std::vector<void *> allocs;
     std::string err = "no error";
     // profiling
@@ -631,6 +633,84 @@ void refresh_cfg_modes(rbe_ctx *c)
 }
 
 bool check_device_ptr(const void *p) { return p != nullptr; }
+
+// Columns of a mode list (see rbe_columns.hip): worth it when at least half of
+// the columns' slots are listed (a random batch fills few; its lists keep the
+// sums by mode).  The set has ncols = 0 for any other list.
+struct ColumnLists {
+    ColumnSet set{};
+    std::vector<ColumnDev> cols;
+    std::vector<int32_t> slot_col, slot_mode, tiles;
+    size_t coef = 0;   // doubles of the coefficient matrix
+};
+
+constexpr int kColumnMinModes = 512;
+constexpr int kColumnMaxM = 128;
+
+void build_columns(const int32_t *modes, int nm, int64_t n, ColumnLists &out)
+{
+    if (nm <= kColumnMinModes) return;
+    const int32_t *X = modes, *Y = modes + nm, *Z = modes + 2 * (size_t)nm;
+    int R = 0;
+    for (int l = 0; l < nm; ++l) {
+        const int m = std::max(std::abs(X[l]), std::abs(Y[l]));
+        if (m > kColumnMaxM || std::abs(Z[l]) > kColumnMaxM) return;
+        R = std::max(R, m);
+    }
+    // of the columns (m_x, m_y) and -(m_x, m_y) the first is the one with m_x > 0, or
+    // m_x = 0 and m_y >= 0
+    const int W = 2 * R + 1;
+    std::vector<int32_t> zmax((size_t)(R + 1) * W, -1), id((size_t)(R + 1) * W, -1);
+    auto flip = [&](int l) { return X[l] < 0 || (X[l] == 0 && Y[l] < 0); };
+    auto cell = [&](int l) { return (size_t)std::abs(X[l]) * W + (flip(l) ? -Y[l] : Y[l]) + R; };
+    for (int l = 0; l < nm; ++l) zmax[cell(l)] = std::max(zmax[cell(l)], std::abs(Z[l]));
+    int64_t D = 0;
+    std::vector<ColumnDev> &cols = out.cols;
+    for (int a = 0; a <= R; ++a)
+        for (int b = -R; b <= R; ++b) {
+            const int z = zmax[(size_t)a * W + b + R];
+            if (z < 0) continue;
+            cols.push_back(ColumnDev{a, b, z, 0, 0, 0});
+            D += 2 * z + 1;
+        }
+    if (D > nm) return;   // a full set of columns and their negatives lists about 2 D modes
+    std::stable_sort(cols.begin(), cols.end(), [](const ColumnDev &p, const ColumnDev &q) { return p.Z > q.Z; });
+    ColumnSet s{};
+    s.ncols = (int)cols.size();
+    s.Rx = s.Ry = R;
+    s.Zm = cols[0].Z;
+    s.D = (int)D;
+    int base = 0, slot = 0;
+    for (int c = 0; c < s.ncols; ++c) {
+        ColumnDev &k = cols[c];
+        if (c % 4 == 0) {
+            // a tile of four columns has the rows of its longest, in fours
+            const int rows = (2 * k.Z + 1 + 3) & ~3;
+            out.tiles.push_back(rows);
+            out.tiles.push_back((int32_t)out.coef);
+            out.coef += 16 * (size_t)rows;
+        }
+        k.base = base;
+        k.slot = slot;
+        k.coef = out.tiles[2 * (c / 4) + 1] + 4 * (c % 4);
+        id[(size_t)k.mx * W + k.my + R] = c;
+        for (int z = 0; z <= k.Z; ++z) out.slot_col.push_back(c);
+        base += 2 * k.Z + 1;
+        slot += k.Z + 1;
+    }
+    s.nslots = slot;
+    if (out.coef > (size_t)1 << 30) return;
+    out.slot_mode.assign(4 * (size_t)slot, -1);
+    for (int l = 0; l < nm; ++l) {
+        const bool f = flip(l);
+        const int z = f ? -Z[l] : Z[l];
+        int32_t &e = out.slot_mode[4 * (size_t)(cols[id[cell(l)]].slot + std::abs(z)) + (f ? 2 : 0) + (z < 0 ? 1 : 0)];
+        if (e >= 0) return;   // a mode listed twice
+        e = l;
+    }
+    if (!column_shapes(s, n)) return;
+    out.set = s;
+}
 
 }  // namespace
 
@@ -1048,6 +1128,7 @@ rbe_status rbe_reserve_modes(rbe_ctx *c, int32_t cap)
     };
     drop_graphs(c);
     c->sample_pending = false;
+    c->cfg.cols = ColumnSet{};
     c->cur_drawn = c->next_ready = false;
     const int old_cap = c->mcap;
     c->mcap = cap;
@@ -1094,6 +1175,7 @@ rbe_status rbe_sample_k(rbe_ctx *c, uint64_t step, int32_t *modes_out)
         if ((s = upload_rho_tiles(c)) != RBE_OK) return s;
     }
     c->modes_valid = true;
+    c->cfg.cols = ColumnSet{};
     c->cur_drawn = !c->any_mh;
     c->cur_step = step;
     if (!c->any_mh && c->next_ready && c->next_step == step) {
@@ -1115,6 +1197,50 @@ rbe_status rbe_sample_k(rbe_ctx *c, uint64_t step, int32_t *modes_out)
             HIPCHK(c, hipMemcpyAsync(modes_out + (size_t)d * c->mtot, c->w.modes + (size_t)d * c->mcap,
                                      sizeof(int32_t) * c->mtot, hipMemcpyDeviceToDevice, c->stream));
     }
+    return RBE_OK;
+}
+
+// Lays the list out as columns when it is dense.  Their buffers grow with the
+// longest such list; where they do not fit in memory the sums by mode stay.
+static rbe_status use_columns(rbe_ctx *c, const int32_t *modes, int nm)
+{
+    ColumnLists cl;
+    build_columns(modes, nm, c->ntot, cl);
+    // the partial sums share the buffer of the sums by mode
+    if (cl.set.ncols == 0 || 2 * (size_t)cl.set.D * (size_t)cl.set.groups > c->partial_cap) return RBE_OK;
+    auto pad = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const size_t b0 = pad(cl.cols.size() * sizeof(ColumnDev)), b1 = pad(cl.slot_col.size() * 4),
+                 b2 = pad(cl.slot_mode.size() * 4), b3 = pad(cl.tiles.size() * 4), b4 = pad(cl.coef * 8);
+    const size_t need = b0 + b1 + b2 + b3 + b4;
+    if (need > c->col_bytes) {
+        void *nw = nullptr;
+        const hipError_t e = hipMalloc(&nw, need);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return RBE_OK;
+        }
+        auto it = std::find(c->allocs.begin(), c->allocs.end(), c->col_mem);
+        if (it != c->allocs.end()) c->allocs.erase(it);
+        if (c->col_mem) (void)hipFree(c->col_mem);
+        c->col_mem = nw;
+        c->col_bytes = need;
+        c->allocs.push_back(nw);
+    }
+    char *base = (char *)c->col_mem;
+    std::vector<char> h(b0 + b1 + b2 + b3, 0);
+    std::memcpy(h.data(), cl.cols.data(), cl.cols.size() * sizeof(ColumnDev));
+    std::memcpy(h.data() + b0, cl.slot_col.data(), cl.slot_col.size() * 4);
+    std::memcpy(h.data() + b0 + b1, cl.slot_mode.data(), cl.slot_mode.size() * 4);
+    std::memcpy(h.data() + b0 + b1 + b2, cl.tiles.data(), cl.tiles.size() * 4);
+    c->w.cols = (ColumnDev *)base;
+    c->w.col_slot = (int32_t *)(base + b0);
+    c->w.col_mode = (int32_t *)(base + b0 + b1);
+    c->w.col_tile = (int32_t *)(base + b0 + b1 + b2);
+    c->w.col_coef = (double *)(base + b0 + b1 + b2 + b3);
+    HIPCHK(c, hipMemcpy(base, h.data(), h.size(), hipMemcpyHostToDevice));
+    HIPCHK(c, hipMemset(c->w.col_coef, 0, cl.coef * 8));   // rows past a column's end stay zero
+    HIPCHK(c, hipStreamSynchronize(nullptr));
+    c->cfg.cols = cl.set;
     return RBE_OK;
 }
 
@@ -1142,6 +1268,7 @@ rbe_status rbe_set_k(rbe_ctx *c, const int32_t *modes, int32_t nm, const double 
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipMemcpy(c->w.modes, m.data(), sizeof(int32_t) * m.size(), hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(c->w.mode_w, wv.data(), sizeof(double) * nm, hipMemcpyHostToDevice));
+    c->cfg.cols = ColumnSet{};
     if (c->sysh[0].p != nm) {
         c->sysh[0].p = nm;
         rbe_status s = upload_sys(c);
@@ -1150,7 +1277,7 @@ rbe_status rbe_set_k(rbe_ctx *c, const int32_t *modes, int32_t nm, const double 
         if ((s = upload_rho_tiles(c)) != RBE_OK) return s;
     }
     c->modes_valid = true;
-    return RBE_OK;
+    return use_columns(c, modes, nm);
 }
 
 // ---- classical Ewald mode lists (eq. 2.9, second term, truncated) ----
@@ -1258,6 +1385,12 @@ static rbe_status materialize_sample(rbe_ctx *c)
 
 static rbe_status kspace_impl(rbe_ctx *c, const void *pos, const void *q, void *force, int accumulate)
 {
+    if (c->cfg.cols.ncols) {
+        RUN(c, K_STAGE, launch_col_rho(c->cfg, c->w, pos, q));
+        RUN(c, K_MID, launch_col_final(c->cfg, c->w));
+        if (force) RUN(c, K_KFORCE, launch_col_force(c->cfg, c->w, pos, q, force, accumulate));
+        return RBE_OK;
+    }
     StageRequest rq{const_cast<void *>(pos), nullptr, nullptr, q, 0, 0, 0, 0, 0, 1};
     rq.mode_split = mode_split(c->cfg.n_rho_tiles, c->max_p, 256);
     if (c->sample_pending) {
@@ -1448,6 +1581,7 @@ rbe_status rbe_step(rbe_ctx *c, void *pos, void *vel, const void *q, void *force
         if (st != RBE_OK) return st;
     } else if (nsteps > 0) {
         c->sample_pending = false;   // the first step draws its own modes
+        c->cfg.cols = ColumnSet{};
         c->cur_drawn = false;
     }
     // time steps draw the next step's modes into the alternate arrays

@@ -139,6 +139,22 @@ struct KVjpD {
     double C, S, A, B;
 };
 
+// One column of a dense mode list: modes (mx, my, -Z .. Z) and their negatives.
+struct ColumnDev {
+    int32_t mx, my, Z;
+    int32_t base;    // first of its 2 Z + 1 trigonometric slots
+    int32_t slot;    // first of its Z + 1 slots (column, n)
+    int32_t coef;    // its place in the coefficient matrix of the force pass
+};
+
+// Shape of the dense mode list in use (ncols = 0: none).
+struct ColumnSet {
+    int ncols, nslots, Rx, Ry, Zm;
+    int D;                 // trigonometric slots of all columns
+    int rho_nb, force_nb;  // particles per block of the two passes
+    int groups, per;       // particle groups of the structure factor
+};
+
 // Kernel ids for per-launch event timing.
 enum KernelId {
     K_SAMPLE = 0,   // stand-alone mode sampling
@@ -201,6 +217,11 @@ struct Workspace {
     uint64_t *step_base;   // [1]: step number of a graph replay (see ListStep)
     void *fpart;           // [kMaxModeSplit][3][Ntot] partial forces of mode-split force passes (long
                            // mode lists only; NULL until rbe_reserve_modes raises the capacity)
+    ColumnDev *cols;       // dense mode list: columns by falling Z ...
+    int32_t *col_slot;     // ... the column of each slot ...
+    int32_t *col_mode;     // ... [slots][4] list entries of (m_x, m_y, +-n) and of their negatives, or -1 ...
+    int32_t *col_tile;     // ... [tiles of four columns][2] rows and offset in ...
+    double *col_coef;      // ... the coefficient matrix of the force pass
     double *diam;          // [Ntot] per-particle diameters (original order), or NULL
 };
 
@@ -225,6 +246,7 @@ struct LaunchCfg {
     int kmax;        // list capacity per particle
     int n_list_tiles;
     int wait_limit;  // spin bound of the device-side waits of a list rebuild
+    ColumnSet cols;  // the active mode list as columns (rbe_set_k of a dense list)
 };
 
 // Device view of the neighbour-list state for one step.
@@ -259,7 +281,12 @@ struct StageRequest {
     int mode_split = 1;    // no integration/binning/sampling: split the modes over this many blocks per chunk
 };
 
-// ---- launchers (rbe_kspace.hip, rbe_real.hip) ----
+// ---- launchers (rbe_kspace.hip, rbe_real.hip, rbe_columns.hip) ----
+bool column_shapes(ColumnSet &s, int64_t n);
+hipError_t launch_col_rho(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q);
+hipError_t launch_col_final(const LaunchCfg &c, const Workspace &w);
+hipError_t launch_col_force(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, void *force,
+                            int accumulate);
 hipError_t launch_sample(const LaunchCfg &c, const Workspace &w, uint64_t step, int use_mh);
 hipError_t launch_stage(const LaunchCfg &c, const Workspace &w, const StageRequest &rq);
 size_t stage_lds_bytes(const LaunchCfg &c, int sample_in_kernel, int *table_lds, int *tab_max);
