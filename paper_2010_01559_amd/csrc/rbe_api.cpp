@@ -950,11 +950,12 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     const size_t pack_sz = c->prec == RBE_FP64 ? 32 : 16;
     const size_t km_sz = c->prec == RBE_FP64 ? sizeof(KModeD) : sizeof(KModeF);
     const size_t kv_sz = c->prec == RBE_FP64 ? sizeof(KVjpD) : sizeof(KVjpF);
-    (void)esz;
     // the largest rho tile list is the one for the smallest chunk (64)
     int64_t max_rho_tiles = 0;
     for (int r = 0; r < R; ++r) max_rho_tiles += (c->sysh[r].n + 63) / 64;
-    c->partial_cap = partial_need(c, 64);
+    // the adjoint needs twice the partials of the structure factor: the chunks
+    // of a large system are at least twice that small
+    c->partial_cap = partial_need(c, 64) * (R > 1 || ntot < 65536 ? 2 : 1);
     Workspace &w = c->w;
     rbe_status st = RBE_OK;
 #define ALLOC(ptr, bytes)                                   \
@@ -1002,6 +1003,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     // one padding record after the last slot: the cell pass's row scan reads
     // candidates two at a time and may read one past a segment's end
     ALLOC(w.sorted, pack_sz * (ntot + 1));
+    ALLOC(w.gsorted, 4 * esz * ntot);
     ALLOC(w.modes_alt, sizeof(int32_t) * 3 * c->mcap);
     ALLOC(w.mode_w_alt, sizeof(double) * c->mcap);
     ALLOC(w.energy_part, sizeof(double) * 8 * ((size_t)g.n_cell_tiles + R));
@@ -1428,13 +1430,13 @@ static rbe_status kspace_impl(rbe_ctx *c, const void *pos, const void *q, void *
 
 // Cell list of pos: bin (staging launch without the structure factor),
 // scan, scatter into cell order.
-static rbe_status cells_impl(rbe_ctx *c, const void *pos, const void *q)
+static rbe_status cells_impl(rbe_ctx *c, const void *pos, const void *q, const void *gF = nullptr)
 {
     c->list_valid = false;   // the cell order changes under the list
     StageRequest rq{const_cast<void *>(pos), nullptr, nullptr, q, 0, 0, 0, 1, 0, 0};
     RUN(c, K_STAGE, launch_stage(c->cfg, c->w, rq));
     RUN(c, K_MID, launch_mid(c->cfg, c->w, 0, 1));
-    RUN(c, K_SCATTER, launch_scatter(c->cfg, c->w));
+    RUN(c, K_SCATTER, launch_scatter(c->cfg, c->w, gF));
     return RBE_OK;
 }
 
@@ -1829,19 +1831,32 @@ rbe_status rbe_forces_vjp(rbe_ctx *c, const void *pos, const void *q, const void
         for (int r = 0; r < c->R; ++r)
             if (c->sysh[r].diam_on)
                 return set_err(c, RBE_ERR_STATE, "the real-space adjoint does not cover per-particle diameters");
-    if (parts & RBE_PART_KSPACE) {
-        rbe_status s = kspace_impl(c, pos, q, nullptr, 0);
+    const bool kspace = parts & RBE_PART_KSPACE, real = parts & RBE_PART_REAL;
+    if (kspace) {
+        rbe_status s = materialize_sample(c);
         if (s != RBE_OK) return s;
-        RUN(c, K_VJP_REDUCE, launch_vjp_reduce(c->cfg, c->w, pos, q, grad_force));
-        RUN(c, K_VJP_REDUCE, launch_vjp_final(c->cfg, c->w));
-        RUN(c, K_VJP_GATHER, launch_vjp_gather(c->cfg, c->w, pos, q, grad_force, grad_pos, grad_q));
-    }
-    if (parts & RBE_PART_REAL) {
-        rbe_status s = cells_impl(c, pos, q);
+        if (real) c->list_valid = false;   // the cell order changes under the list
+        // a pass over the modes needs four sums per tile and mode: all modes
+        // at once where the partials have room (as allocated at creation), else a
+        // single system's long list in slices
+        const int64_t tiles = c->cfg.n_rho_tiles;
+        int slices = 1;
+        if (c->R == 1)
+            while (slices < c->max_p && 4 * tiles * ((c->max_p + slices - 1) / slices) > (int64_t)c->partial_cap) ++slices;
+        for (int k = 0; k < slices; ++k) {
+            const int l0 = slices == 1 ? 0 : (int)((int64_t)c->max_p * k / slices);
+            const int l1 = slices == 1 ? 0 : (int)((int64_t)c->max_p * (k + 1) / slices);
+            const int first = real && k == 0 ? 1 : 0;
+            RUN(c, K_VJP_REDUCE, launch_vjp_stage(c->cfg, c->w, pos, q, grad_force, l0, l1, first,
+                                                  mode_split(c->cfg.n_rho_tiles, (l1 ? l1 - l0 : c->max_p), 256)));
+            RUN(c, K_VJP_REDUCE, launch_vjp_final(c->cfg, c->w, l0, l1, first));
+        }
+        RUN(c, K_VJP_GATHER, launch_vjp_gather(c->cfg, c->w, pos, q, grad_force, grad_pos, grad_q, real ? 1 : 0));
+    } else {
+        rbe_status s = cells_impl(c, pos, q, grad_force);
         if (s != RBE_OK) return s;
-        RUN(c, K_VJP_REAL, launch_vjp_real(c->cfg, c->w, grad_force, grad_pos, grad_q,
-                                           (parts & RBE_PART_KSPACE) ? 1 : 0));
     }
+    if (real) RUN(c, K_VJP_REAL, launch_vjp_real(c->cfg, c->w, grad_force, grad_pos, grad_q, kspace ? 1 : 0));
     return RBE_OK;
 }
 

@@ -418,24 +418,12 @@ bool column_shapes(ColumnSet &s, int64_t n)
     return true;
 }
 
-// Kernels whose dynamic LDS may exceed 64 KB.
-template <typename F, typename... Args>
-static hipError_t launch_lds(F kernel, dim3 g, size_t lds, hipStream_t st, Args... args)
-{
-    if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-    }
-    launch_k(kernel, g, dim3(256), (uint32_t)lds, st, args...);
-    return hipGetLastError();
-}
-
 template <typename T>
 static hipError_t col_rho(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q)
 {
     const ColumnSet &s = c.cols;
     const dim3 g(s.groups, (s.ncols + kColsPerBlock - 1) / kColsPerBlock, (2 * s.Zm + 1 + kTrigPerBlock - 1) / kTrigPerBlock);
-    return launch_lds(s.rho_nb == 64 ? k_col_rho<T, 64> : k_col_rho<T, 32>, g, rho_lds(s, s.rho_nb), c.stream,
+    return launch_lds(s.rho_nb == 64 ? k_col_rho<T, 64> : k_col_rho<T, 32>, g, dim3(256), rho_lds(s, s.rho_nb), c.stream,
                       col_args(c, w), (const T *)pos, (const T *)q, c.ntot);
 }
 
@@ -464,7 +452,7 @@ static hipError_t col_force(const LaunchCfg &c, const Workspace &w, const void *
 {
     const ColumnSet &s = c.cols;
     const dim3 g((unsigned)((c.ntot + s.force_nb - 1) / s.force_nb));
-    return launch_lds(s.force_nb == 64 ? k_col_force<T, 64> : k_col_force<T, 32>, g, force_lds(s, s.force_nb), c.stream,
+    return launch_lds(s.force_nb == 64 ? k_col_force<T, 64> : k_col_force<T, 32>, g, dim3(256), force_lds(s, s.force_nb), c.stream,
                       col_args(c, w), (const int32_t *)w.col_tile, (const double *)w.col_coef, (const T *)pos,
                       (const T *)q, c.ntot, (T *)F, acc, w.flag);
 }

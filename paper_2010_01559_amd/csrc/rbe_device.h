@@ -517,6 +517,43 @@ __device__ __forceinline__ bool record_update(const SysDev &S, int64_t i, double
     return moved;
 }
 
+// Moves particle i's record into slot `slot` of the cell order.
+template <typename T>
+__device__ __forceinline__ void scatter_record(int64_t i, int slot, const void *packed, int32_t *sorted_idx,
+                                               void *sorted)
+{
+    sorted_idx[slot] = (int32_t)i;
+    if constexpr (sizeof(T) == 4)
+        reinterpret_cast<PackF *>(sorted)[slot] = reinterpret_cast<const PackF *>(packed)[i];
+    else
+        reinterpret_cast<PartD *>(sorted)[slot] = reinterpret_cast<const PartD *>(packed)[i];
+}
+
+// Row `slot` of a [n][4] array as one or two 16-byte accesses.
+__device__ __forceinline__ void store4(float *p, int64_t slot, float x, float y, float z)
+{
+    reinterpret_cast<float4 *>(p)[slot] = make_float4(x, y, z, 0.0f);
+}
+__device__ __forceinline__ void store4(double *p, int64_t slot, double x, double y, double z)
+{
+    reinterpret_cast<double2 *>(p)[2 * slot] = make_double2(x, y);
+    reinterpret_cast<double2 *>(p)[2 * slot + 1] = make_double2(z, 0.0);
+}
+__device__ __forceinline__ void load4(const float *p, int64_t slot, float &x, float &y, float &z)
+{
+    const float4 v = reinterpret_cast<const float4 *>(p)[slot];
+    x = v.x;
+    y = v.y;
+    z = v.z;
+}
+__device__ __forceinline__ void load4(const double *p, int64_t slot, double &x, double &y, double &z)
+{
+    const double2 a = reinterpret_cast<const double2 *>(p)[2 * slot], b = reinterpret_cast<const double2 *>(p)[2 * slot + 1];
+    x = a.x;
+    y = a.y;
+    z = b.x;
+}
+
 // Inclusive prefix sum across the 64 lanes of a wave, with data-parallel
 // primitives (within rows of 16, then row ends broadcast to later rows): no
 // LDS round trips.

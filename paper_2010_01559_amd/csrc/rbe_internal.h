@@ -31,6 +31,18 @@ inline void launch_k(F kernel, dim3 grid, dim3 block, uint32_t shmem, hipStream_
     hipExtLaunchKernelGGL(kernel, grid, block, shmem, stream, a, e.stop, 0u, args...);
 }
 
+// The same for kernels whose dynamic LDS may exceed 64 KB (of 160 KB).
+template <typename F, typename... Args>
+inline hipError_t launch_lds(F kernel, dim3 grid, dim3 block, size_t lds, hipStream_t stream, Args... args)
+{
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    launch_k(kernel, grid, block, (uint32_t)lds, stream, args...);
+    return hipGetLastError();
+}
+
 constexpr double kPi = 3.14159265358979323846264338327950288;
 
 // Tags in the top byte of Philox counter word 1; they separate the random
@@ -125,7 +137,7 @@ struct KModeD {
 
 // Per-mode constants of the adjoint gather pass.
 struct KVjpF {
-    double m[3];
+    float m[3];
     float a[3];
     float k[3];     // 2 pi m / L
     float C, S, A, B;
@@ -201,6 +213,7 @@ struct Workspace {
     int32_t *sorted_idx;   // [Ntot] particle at each sorted slot
     void *packed;          // [Ntot] wrapped position + charge, original order
     void *sorted;          // [Ntot] same, sorted by cell
+    void *gsorted;         // [Ntot][4] gradient of the forces by cell-sorted slot (adjoint of the real space)
     int32_t *modes_alt;    // the next step's modes and weights when the totals launch draws them
     double *mode_w_alt;
     double *energy_part;   // [wave tiles][8], then [R][8] sums
@@ -296,7 +309,7 @@ hipError_t launch_mid(const LaunchCfg &c, const Workspace &w, int do_final, int 
                       const ListStep *ls = nullptr);
 hipError_t launch_kforce(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, void *force,
                          int accumulate, int scatter, int mode_split = 1);
-hipError_t launch_scatter(const LaunchCfg &c, const Workspace &w);
+hipError_t launch_scatter(const LaunchCfg &c, const Workspace &w, const void *gF = nullptr);
 hipError_t launch_set_step(const LaunchCfg &c, const Workspace &w, uint64_t step);
 hipError_t launch_pair_hist(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, double r_max,
                             int nbins, int64_t *counts);
@@ -306,11 +319,13 @@ hipError_t launch_real(const LaunchCfg &c, const Workspace &w, void *force, int 
                        uint64_t kick_step = 0);
 hipError_t launch_energy(const LaunchCfg &c, const Workspace &w, const void *q, const void *vel);
 hipError_t launch_energy_sum(const LaunchCfg &c, const Workspace &w);
-hipError_t launch_vjp_reduce(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q,
-                             const void *gF);
-hipError_t launch_vjp_final(const LaunchCfg &c, const Workspace &w);
+// Adjoint of the Fourier part: sums over the modes [l0, l1) of a single system (l1 = 0: all modes of
+// every system), their totals, and the gather; with bin, scan and scatter also the cell list.
+hipError_t launch_vjp_stage(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, const void *gF,
+                            int l0, int l1, int bin, int mode_split);
+hipError_t launch_vjp_final(const LaunchCfg &c, const Workspace &w, int l0, int l1, int scan);
 hipError_t launch_vjp_gather(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q,
-                             const void *gF, void *gpos, void *gq);
+                             const void *gF, void *gpos, void *gq, int scatter);
 hipError_t launch_vjp_real(const LaunchCfg &c, const Workspace &w, const void *gF, void *gpos, void *gq,
                            int accumulate);
 hipError_t launch_fill_zero(hipStream_t s, void *ptr, int64_t nbytes);

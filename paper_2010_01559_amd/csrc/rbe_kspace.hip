@@ -24,7 +24,8 @@
 //                   counts, and the gated list rebuild (one launch)
 //   k_kforce        force pass + [scatter into cell order]; long mode lists
 //                   split over blocks (grid y) and summed by k_fsum
-//   k_vjp_*         adjoint of the force at a fixed mode sample
+//   k_vjp_*         adjoint of the force at a fixed mode sample [+ bin, scan,
+//                   scatter for its real-space part]
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -609,11 +610,7 @@ __global__ __launch_bounds__(256) void k_kforce(ForceArgs<T, KM> a)
             atomicOr(a.flag, kFlagBounds);
             return;
         }
-        a.sorted_idx[slot] = (int32_t)i;
-        if constexpr (sizeof(T) == 4)
-            reinterpret_cast<PackF *>(a.sorted)[slot] = reinterpret_cast<const PackF *>(a.packed)[i];
-        else
-            reinterpret_cast<PartD *>(a.sorted)[slot] = reinterpret_cast<const PartD *>(a.packed)[i];
+        scatter_record<T>(i, slot, a.packed, a.sorted_idx, a.sorted);
     }
 }
 
@@ -639,29 +636,34 @@ __global__ __launch_bounds__(256) void k_fsum(const T *__restrict__ fpart, int y
 //   w_il = G_i . a_l,  A_l = sum_i q_i w_il cos th_il,  B_l = sum_i q_i w_il sin th_il,
 //   dLoss/dq_i = -sum_l [w_il (cos th S_l - sin th C_l) + A_l sin th - B_l cos th],
 //   dLoss/dr_i = q_i sum_l k_l [w_il (sin th S_l + cos th C_l) - A_l cos th - B_l sin th],
-// k_l = 2 pi m_l / L.  The (A, B) reduction has the shape of the structure
-// factor and reuses its tiling; the gather has the shape of the force pass.
+// k_l = 2 pi m_l / L.  Neither sum of (C, S) and (A, B) needs the other, so one
+// launch forms both from one sine and cosine per pair (k_vjp_stage, which
+// also bins for the real-space part), one adds their tile partials (and scans
+// the cells), and the gather has the shape of the force pass (and scatters into
+// cell order).  The structure factor, its totals, the (A, B) sums, their
+// totals, the gather, binning, scan and scatter were eight launches, 61 us at
+// N = 30000, P = 200 (trace); the three take 34 us.
 // ---------------------------------------------------------------------------
-// LDS record of the adjoint reduction: the particle's phase inputs and
-// q_i G_i.  Single precision takes the phase from the exact split of the box
-// fraction (the same phases as the forward passes), double the fraction.
+// LDS record of the reduction: the particle's phase inputs, q_i G_i and q_i.
+// Single precision takes the phase from the exact split of the box fraction (the
+// same phases as the forward passes), double the fraction.
 template <typename T>
 struct VjpRec;
 template <>
 struct VjpRec<float> {
     struct alignas(16) type {
-        float hx, hy, hz, lx, ly, lz, gx, gy, gz, pad[3];
+        float hx, hy, hz, lx, ly, lz, gx, gy, gz, q, pad[2];
     };
 };
 template <>
 struct VjpRec<double> {
-    struct alignas(16) type {
-        double x, y, z, gx, gy, gz;
+    struct type {
+        double x, y, z, gx, gy, gz, q;
     };
 };
 
 __device__ __forceinline__ void vjp_record(const SysDev &S, double sx, double sy, double sz, float gx, float gy,
-                                           float gz, VjpRec<float>::type &v)
+                                           float gz, float q, VjpRec<float>::type &v)
 {
     split_frac(sx, S, v.hx, v.lx);
     split_frac(sy, S, v.hy, v.ly);
@@ -669,11 +671,12 @@ __device__ __forceinline__ void vjp_record(const SysDev &S, double sx, double sy
     v.gx = gx;
     v.gy = gy;
     v.gz = gz;
-    v.pad[0] = v.pad[1] = v.pad[2] = 0.0f;
+    v.q = q;
+    v.pad[0] = v.pad[1] = 0.0f;
 }
 
 __device__ __forceinline__ void vjp_record(const SysDev &, double sx, double sy, double sz, double gx, double gy,
-                                           double gz, VjpRec<double>::type &v)
+                                           double gz, double q, VjpRec<double>::type &v)
 {
     v.x = sx;
     v.y = sy;
@@ -681,6 +684,7 @@ __device__ __forceinline__ void vjp_record(const SysDev &, double sx, double sy,
     v.gx = gx;
     v.gy = gy;
     v.gz = gz;
+    v.q = q;
 }
 
 // sin and cos of a record's phase for mode m.
@@ -698,168 +702,263 @@ __device__ __forceinline__ void vjp_sincos(const VjpRec<double>::type &v, double
     sincospi(2.0 * wrap_rev(fma(mx, v.x, fma(my, v.y, mz * v.z))), &sn, &cs);
 }
 
-template <typename T, typename KM, int BS>
-__global__ __launch_bounds__(BS) void k_vjp_reduce(const SysDev *__restrict__ sys, const Tile *__restrict__ tiles,
-                                                   const T *__restrict__ pos, const T *__restrict__ q,
-                                                   const T *__restrict__ gF, int64_t ntot,
-                                                   const KM *__restrict__ km, double *__restrict__ partial,
-                                                   const int32_t *__restrict__ part_off)
+template <typename T>
+struct VjpStageArgs {
+    const SysDev *sys;
+    const Tile *tiles;
+    const T *pos, *q, *gF;
+    int64_t ntot;
+    const int32_t *modes;
+    const double *mode_w;
+    int mcap;
+    double *partial;            // [tile][modes of the slice][4]: C, S, A, B
+    const int32_t *part_off;
+    int l0, l1;                 // single system: the slice of modes (l1 = 0: all modes of every system)
+    int chunk;
+    int do_bin;
+    int32_t *count, *cellid, *rank;
+    void *packed;
+};
+
+template <typename T, int BS>
+__global__ __launch_bounds__(BS) void k_vjp_stage(VjpStageArgs<T> a)
 {
     using VR = typename VjpRec<T>::type;
     extern __shared__ __align__(16) unsigned char smem[];
-    const Tile t = tiles[blockIdx.x];
-    const SysDev S = sys[t.sys];
+    const Tile t = a.tiles[blockIdx.x];
+    const SysDev S = a.sys[t.sys];
     VR *sp = reinterpret_cast<VR *>(smem);
-    double2 *red = reinterpret_cast<double2 *>(smem + sizeof(VR) * t.count);
+    double2 *red = reinterpret_cast<double2 *>(smem + ((sizeof(VR) * a.chunk + 15) & ~(size_t)15));
     const int tid = threadIdx.x;
     const int count = t.count;
     for (int j = tid; j < count; j += BS) {
         const int64_t i = S.off + t.start + j;
-        const T qi = q[i];
+        const T qi = a.q[i];
+        const double sx = frac01((double)a.pos[i] * S.invL), sy = frac01((double)a.pos[a.ntot + i] * S.invL),
+                     sz = frac01((double)a.pos[2 * a.ntot + i] * S.invL);
         VR v;
-        vjp_record(S, frac01((double)pos[i] * S.invL), frac01((double)pos[ntot + i] * S.invL),
-                   frac01((double)pos[2 * ntot + i] * S.invL), qi * gF[i], qi * gF[ntot + i],
-                   qi * gF[2 * ntot + i], v);
+        vjp_record(S, sx, sy, sz, qi * a.gF[i], qi * a.gF[a.ntot + i], qi * a.gF[2 * a.ntot + i], qi, v);
         sp[j] = v;
+        // (the mode slices and mode parts of a launch stage the same particles)
+        if (a.do_bin && blockIdx.y == 0) bin_one<T>(S, i, sx, sy, sz, qi, a.count, a.cellid, a.rank, a.packed);
     }
     __syncthreads();
-    const int P = S.p;
-    const int Pt = P < BS ? P : BS;
+    const int L0 = a.l1 ? a.l0 : 0, L1 = a.l1 ? a.l1 : S.p, P = L1 - L0;
+    // modes [mb, me) of this block (long lists are split over grid y)
+    const int ys = (int)gridDim.y;
+    const int mb = L0 + (int)(((int64_t)P * blockIdx.y) / ys), me = L0 + (int)(((int64_t)P * (blockIdx.y + 1)) / ys);
+    const int Pm = me - mb;
+    if (Pm <= 0) return;
+    const int Pt = Pm < BS ? Pm : BS;
     const int G = BS / Pt;
-    double *prow = partial + 2 * ((int64_t)part_off[t.sys] + (int64_t)t.aux * P);
-    for (int m0 = 0; m0 < P; m0 += Pt) {
+    double *prow = a.partial + 4 * ((a.l1 ? 0 : (int64_t)a.part_off[t.sys]) + (int64_t)t.aux * P);
+    for (int m0 = mb; m0 < me; m0 += Pt) {
         const int lt = tid % Pt, g = tid / Pt;
         const int l = m0 + lt;
-        const bool act = g < G && l < P;
-        double A = 0.0, B = 0.0;
+        const bool act = g < G && l < me;
+        double C = 0.0, Sn = 0.0, A = 0.0, B = 0.0;
         if (act) {
-            const KM k = km[S.moff + l];
-            const T mx = (T)k.m[0], my = (T)k.m[1], mz = (T)k.m[2];
-            const T ax = (T)k.a[0], ay = (T)k.a[1], az = (T)k.a[2];
+            const KModeIn in = kmode_in(S, S.moff, l, a.modes, a.mode_w, a.mcap);
+            const double f = in.coulomb * in.w * 2.0 / (in.L * in.L * (in.mx * in.mx + in.my * in.my + in.mz * in.mz));
+            const T mx = (T)in.mx, my = (T)in.my, mz = (T)in.mz;
+            const T ax = (T)(f * in.mx), ay = (T)(f * in.my), az = (T)(f * in.mz);
             for (int j0 = g; j0 < count; j0 += 8 * G) {
-                T a8 = 0, b8 = 0;
+                T c8 = 0, s8 = 0, a8 = 0, b8 = 0;
+                auto term = [&](const VR &v) {
+                    T sn, cs;
+                    vjp_sincos(v, mx, my, mz, sn, cs);
+                    c8 = fma(v.q, cs, c8);
+                    s8 = fma(v.q, sn, s8);
+                    const T w = fma(v.gx, ax, fma(v.gy, ay, v.gz * az));
+                    a8 = fma(w, cs, a8);
+                    b8 = fma(w, sn, b8);
+                };
+                if (j0 + 7 * G < count) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int j = j0 + u * G;
-                    if (j < count) {
-                        const VR v = sp[j];
-                        T sn, cs;
-                        vjp_sincos(v, mx, my, mz, sn, cs);
-                        const T w = fma(v.gx, ax, fma(v.gy, ay, v.gz * az));
-                        a8 = fma(w, cs, a8);
-                        b8 = fma(w, sn, b8);
-                    }
+                    for (int u = 0; u < 8; ++u) term(sp[j0 + u * G]);
+                } else {
+                    for (int j = j0; j < count; j += G) term(sp[j]);
                 }
+                C += (double)c8;
+                Sn += (double)s8;
                 A += (double)a8;
                 B += (double)b8;
             }
         }
-        red[tid] = make_double2(A, B);
-        __syncthreads();
-        if (tid < Pt && l < P) {
-            double av = 0.0, bv = 0.0;
-            for (int gg = 0; gg < G; ++gg) {
-                const double2 v = red[gg * Pt + lt];
-                av += v.x;
-                bv += v.y;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            red[tid] = h == 0 ? make_double2(C, Sn) : make_double2(A, B);
+            __syncthreads();
+            if (tid < Pt && l < me) {
+                double u = 0.0, v = 0.0;
+                for (int gg = 0; gg < G; ++gg) {
+                    const double2 r = red[gg * Pt + lt];
+                    u += r.x;
+                    v += r.y;
+                }
+                reinterpret_cast<double2 *>(prow)[2 * (int64_t)(l - L0) + h] = make_double2(u, v);
             }
-            prow[2 * l] = av;
-            prow[2 * l + 1] = bv;
+            if (h == 0 || m0 + Pt < me) __syncthreads();   // red is reused
         }
-        if (m0 + Pt < P) __syncthreads();   // red is reused by the next mode tile
     }
 }
 
+// Totals of the adjoint: a wave per mode adds the tile partials of its four
+// sums; then one cell-scan block per system when the real-space part follows.
 template <typename KM, typename KV>
-__global__ __launch_bounds__(64) void k_vjp_final(const SysDev *__restrict__ sys, const double *__restrict__ partial,
-                                                  const int32_t *__restrict__ part_off, int R,
-                                                  const KM *__restrict__ km, double *__restrict__ ab,
-                                                  KV *__restrict__ kv)
+struct VjpFinalArgs {
+    const SysDev *sys;
+    int R, max_p, n_final_blocks;
+    const double *partial;
+    const int32_t *part_off;
+    int l0, l1;
+    const int32_t *modes;
+    const double *mode_w;
+    int mcap;
+    double *rho, *ab;
+    KM *km;
+    KV *kv;
+    int32_t *count, *start;
+};
+
+template <typename KM, typename KV>
+__global__ __launch_bounds__(1024) void k_vjp_final(VjpFinalArgs<KM, KV> a)
 {
-    const int r = blockIdx.y;
-    const SysDev S = sys[r];
-    const int l = blockIdx.x;
+    if ((int)blockIdx.x >= a.n_final_blocks) {
+        const int r = blockIdx.x - a.n_final_blocks;
+        mid_scan<16>(a.sys[r], r, a.count, a.start);
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    const int gm = blockIdx.x * 16 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int span = a.l1 ? a.l1 - a.l0 : a.max_p;
+    const int r = gm / span, l = a.l0 + gm % span;
+    if (r >= a.R) return;
+    const SysDev &S = a.sys[r];
     if (l >= S.p) return;
-    const int nt = part_off[R + r];
-    const double *base = partial + 2 * (int64_t)part_off[r];
-    double av = 0.0, bv = 0.0;
-    for (int t = threadIdx.x; t < nt; t += 64) {
-        av += base[2 * ((int64_t)t * S.p + l)];
-        bv += base[2 * ((int64_t)t * S.p + l) + 1];
+    const int P = a.l1 ? span : S.p, nt = a.part_off[a.R + r];
+    const double2 *base = reinterpret_cast<const double2 *>(a.partial) + 2 * ((a.l1 ? 0 : (int64_t)a.part_off[r]) + l - a.l0);
+    KModeIn in{};
+    if (lane == 0) in = kmode_in(S, S.moff, l, a.modes, a.mode_w, a.mcap);
+    double c = 0.0, s = 0.0, av = 0.0, bv = 0.0;
+    for (int t0 = lane; t0 < nt; t0 += 4 * 64) {
+        double2 x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (t0 + 64 * u < nt) {
+                x[u] = base[2 * (int64_t)(t0 + 64 * u) * P];
+                y[u] = base[2 * (int64_t)(t0 + 64 * u) * P + 1];
+            }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (t0 + 64 * u < nt) {
+                c += x[u].x;
+                s += x[u].y;
+                av += y[u].x;
+                bv += y[u].y;
+            }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
+        c += __shfl_down(c, off, 64);
+        s += __shfl_down(s, off, 64);
         av += __shfl_down(av, off, 64);
         bv += __shfl_down(bv, off, 64);
     }
-    if (threadIdx.x == 0) {
-        const int o = S.moff + l;
-        ab[2 * o] = av;
-        ab[2 * o + 1] = bv;
-        const KM k = km[o];
-        KV v;
-        const double tp = 2.0 * kPi * S.invL;
-        for (int d = 0; d < 3; ++d) {
-            v.m[d] = k.m[d];
-            v.a[d] = k.a[d];
-            v.k[d] = tp * k.m[d];
-        }
-        v.C = k.C;
-        v.S = k.S;
-        v.A = av;
-        v.B = bv;
-        if constexpr (sizeof(KV) == sizeof(KVjpF)) v.pad[0] = v.pad[1] = v.pad[2] = 0.0f;
-        kv[o] = v;
+    if (lane != 0) return;
+    make_kmode<KM>(in, c, s, a.rho, a.km);
+    const int o = in.o;
+    a.ab[2 * o] = av;
+    a.ab[2 * o + 1] = bv;
+    const KM k = a.km[o];
+    KV v;
+    const double tp = 2.0 * kPi * S.invL, m[3] = {in.mx, in.my, in.mz};
+    for (int d = 0; d < 3; ++d) {
+        v.m[d] = k.m[d];
+        v.a[d] = k.a[d];
+        v.k[d] = tp * m[d];
     }
+    v.C = c;
+    v.S = s;
+    v.A = av;
+    v.B = bv;
+    if constexpr (sizeof(KV) == sizeof(KVjpF)) v.pad[0] = v.pad[1] = v.pad[2] = 0.0f;
+    a.kv[o] = v;
 }
 
+// A particle's adjoint from all modes (the wave's share of them).  The mode
+// constants are wave-uniform and read by scalar loads, as in fourier_range: by
+// vector loads of the same 80 bytes for every lane the launch took 20 us at
+// N = 30000, P = 200.
+template <typename T, typename KV>
+struct VjpGatherArgs {
+    const SysDev *sys;
+    const Tile *tiles;
+    int ntiles, n_blocks;
+    const T *pos, *q, *gF;
+    int64_t ntot;
+    const KV *kv;
+    T *gpos, *gq;
+    // scatter into cell order, with the gradient of the forces
+    int do_scatter;
+    const int32_t *start, *cellid, *rank;
+    const void *packed;
+    int32_t *sorted_idx;
+    void *sorted;
+    T *gsorted;    // [ntot][4]
+    int32_t *flag;
+    RowTileArgs rt;
+};
+
 template <typename T, typename KV, int SPLIT>
-__global__ __launch_bounds__(256) void k_vjp_gather(const SysDev *__restrict__ sys, const Tile *__restrict__ tiles,
-                                                    int ntiles, const T *__restrict__ pos, const T *__restrict__ q,
-                                                    const T *__restrict__ gF, int64_t ntot,
-                                                    const KV *__restrict__ kv, T *__restrict__ gpos,
-                                                    T *__restrict__ gq)
+__global__ __launch_bounds__(256) void k_vjp_gather(VjpGatherArgs<T, KV> a)
 {
     __shared__ T red[4][4][64];
+    if (a.do_scatter && (int)blockIdx.x >= a.n_blocks) {
+        write_row_tiles(a.rt, blockIdx.x - a.n_blocks);
+        return;
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int group = wave / SPLIT, part = wave % SPLIT;
     const int ti = blockIdx.x * (4 / SPLIT) + group;
+    const int64_t ntot = a.ntot;
     T dq = 0, rx = 0, ry = 0, rz = 0;
     int64_t i = -1;
-    T qi = 0;
-    if (ti < ntiles) {
-        const Tile t = tiles[ti];
-        const SysDev S = sys[t.sys];
+    T qi = 0, gx = 0, gy = 0, gz = 0;
+    int sysi = 0;
+    if (ti < a.ntiles) {
+        const Tile t = a.tiles[ti];
+        sysi = t.sys;
+        const SysDev S = a.sys[t.sys];
         double sx = 0.0, sy = 0.0, sz = 0.0;
-        T gx = 0, gy = 0, gz = 0;
         if (lane < t.count) {
             i = S.off + t.start + lane;
-            sx = frac01((double)pos[i] * S.invL);
-            sy = frac01((double)pos[ntot + i] * S.invL);
-            sz = frac01((double)pos[2 * ntot + i] * S.invL);
-            qi = q[i];
-            gx = gF[i];
-            gy = gF[ntot + i];
-            gz = gF[2 * ntot + i];
+            sx = frac01((double)a.pos[i] * S.invL);
+            sy = frac01((double)a.pos[ntot + i] * S.invL);
+            sz = frac01((double)a.pos[2 * ntot + i] * S.invL);
+            qi = a.q[i];
+            gx = a.gF[i];
+            gy = a.gF[ntot + i];
+            gz = a.gF[2 * ntot + i];
         }
-        const int64_t nparts = (int64_t)SPLIT * gridDim.y, gp = (int64_t)blockIdx.y * SPLIT + part;
-        const int l0 = (int)((S.p * gp) / nparts), l1 = (int)((S.p * (gp + 1)) / nparts);
-        const KV *kk = kv + S.moff;
+        const int l0 = __builtin_amdgcn_readfirstlane((S.p * part) / SPLIT),
+                  l1 = __builtin_amdgcn_readfirstlane((S.p * (part + 1)) / SPLIT);
+        const auto kk = uniform_modes(a.kv + S.moff);
         typename VjpRec<T>::type rec;
-        vjp_record(S, sx, sy, sz, (T)0, (T)0, (T)0, rec);
+        vjp_record(S, sx, sy, sz, (T)0, (T)0, (T)0, (T)0, rec);
 #pragma unroll 2
         for (int l = l0; l < l1; ++l) {
-            const KV k = kk[l];
+            const T ka[3] = {(T)kk[l].a[0], (T)kk[l].a[1], (T)kk[l].a[2]};
             T sn, cs;
-            vjp_sincos(rec, (T)k.m[0], (T)k.m[1], (T)k.m[2], sn, cs);
-            const T w = fma(gx, (T)k.a[0], fma(gy, (T)k.a[1], gz * (T)k.a[2]));
-            const T Ck = (T)k.C, Sk = (T)k.S, Ak = (T)k.A, Bk = (T)k.B;
+            vjp_sincos(rec, (T)kk[l].m[0], (T)kk[l].m[1], (T)kk[l].m[2], sn, cs);
+            const T w = fma(gx, ka[0], fma(gy, ka[1], gz * ka[2]));
+            const T Ck = (T)kk[l].C, Sk = (T)kk[l].S, Ak = (T)kk[l].A, Bk = (T)kk[l].B;
             dq -= fma(w, cs * Sk - sn * Ck, Ak * sn - Bk * cs);
             const T tt = fma(w, sn * Sk + cs * Ck, -(Ak * cs + Bk * sn));
-            rx = fma(tt, (T)k.k[0], rx);
-            ry = fma(tt, (T)k.k[1], ry);
-            rz = fma(tt, (T)k.k[2], rz);
+            rx = fma(tt, (T)kk[l].k[0], rx);
+            ry = fma(tt, (T)kk[l].k[1], ry);
+            rz = fma(tt, (T)kk[l].k[2], rz);
         }
     }
     if constexpr (SPLIT > 1) {
@@ -877,10 +976,20 @@ __global__ __launch_bounds__(256) void k_vjp_gather(const SysDev *__restrict__ s
         }
     }
     if (i < 0) return;
-    gq[i] = dq;
-    gpos[i] = qi * rx;
-    gpos[ntot + i] = qi * ry;
-    gpos[2 * ntot + i] = qi * rz;
+    a.gq[i] = dq;
+    a.gpos[i] = qi * rx;
+    a.gpos[ntot + i] = qi * ry;
+    a.gpos[2 * ntot + i] = qi * rz;
+    if (a.do_scatter) {
+        const int slot = a.start[a.cellid[i] + sysi] + a.rank[i];
+        const SysDev &S = a.sys[sysi];
+        if (slot < S.off || slot >= S.off + S.n) {
+            atomicOr(a.flag, kFlagBounds);
+            return;
+        }
+        scatter_record<T>(i, slot, a.packed, a.sorted_idx, a.sorted);
+        store4(a.gsorted, slot, gx, gy, gz);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1150,79 +1259,127 @@ hipError_t launch_kforce(const LaunchCfg &c, const Workspace &w, const void *pos
                               : kforce_dispatch<float, KModeF>(c, w, pos, q, force, accumulate, scatter, mode_split);
 }
 
-template <typename T, typename KM>
-static hipError_t vjp_reduce_dispatch(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q,
-                                      const void *gF)
+template <typename T>
+static hipError_t vjp_stage_dispatch(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q,
+                                     const void *gF, int l0, int l1, int bin, int mode_split)
 {
-    const size_t sm = sizeof(typename VjpRec<T>::type) * c.rho_chunk + sizeof(double2) * c.rho_block;
-    const T *p = (const T *)pos, *qq = (const T *)q, *g = (const T *)gF;
-    const KM *km = (const KM *)w.kmode;
-    dim3 gr(c.n_rho_tiles);
+    VjpStageArgs<T> a;
+    a.sys = w.sys;
+    a.tiles = w.rho_tiles;
+    a.pos = (const T *)pos;
+    a.q = (const T *)q;
+    a.gF = (const T *)gF;
+    a.ntot = c.ntot;
+    a.modes = w.modes;
+    a.mode_w = w.mode_w;
+    a.mcap = c.mcap;
+    a.partial = w.partial;
+    a.part_off = w.partial_off;
+    a.l0 = l0;
+    a.l1 = l1;
+    a.chunk = c.rho_chunk;
+    a.do_bin = bin;
+    a.count = w.cell_count;
+    a.cellid = w.cellid;
+    a.rank = w.rank;
+    a.packed = w.packed;
+    const size_t sm = ((sizeof(typename VjpRec<T>::type) * c.rho_chunk + 15) & ~(size_t)15) + sizeof(double2) * c.rho_block;
+    const dim3 g(c.n_rho_tiles, mode_split);
     switch (c.rho_block) {
     case 256:
-        launch_k(k_vjp_reduce<T, KM, 256>, gr, 256, sm, c.stream, w.sys, w.rho_tiles, p, qq, g, c.ntot, km, w.partial,
-                                                            w.partial_off);
-        break;
+        return launch_lds(k_vjp_stage<T, 256>, g, dim3(256), sm, c.stream, a);
     case 512:
-        launch_k(k_vjp_reduce<T, KM, 512>, gr, 512, sm, c.stream, w.sys, w.rho_tiles, p, qq, g, c.ntot, km, w.partial,
-                                                            w.partial_off);
-        break;
+        return launch_lds(k_vjp_stage<T, 512>, g, dim3(512), sm, c.stream, a);
     default:
-        launch_k(k_vjp_reduce<T, KM, 1024>, gr, 1024, sm, c.stream, w.sys, w.rho_tiles, p, qq, g, c.ntot, km, w.partial,
-                                                              w.partial_off);
-        break;
+        return launch_lds(k_vjp_stage<T, 1024>, g, dim3(1024), sm, c.stream, a);
     }
+}
+
+hipError_t launch_vjp_stage(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, const void *gF,
+                            int l0, int l1, int bin, int mode_split)
+{
+    return c.prec == RBE_FP64 ? vjp_stage_dispatch<double>(c, w, pos, q, gF, l0, l1, bin, mode_split)
+                              : vjp_stage_dispatch<float>(c, w, pos, q, gF, l0, l1, bin, mode_split);
+}
+
+template <typename KM, typename KV>
+static hipError_t vjp_final_dispatch(const LaunchCfg &c, const Workspace &w, int l0, int l1, int scan)
+{
+    VjpFinalArgs<KM, KV> a;
+    a.sys = w.sys;
+    a.R = c.R;
+    a.max_p = c.max_p;
+    a.n_final_blocks = (c.R * (l1 ? l1 - l0 : c.max_p) + 15) / 16;
+    a.partial = w.partial;
+    a.part_off = w.partial_off;
+    a.l0 = l0;
+    a.l1 = l1;
+    a.modes = w.modes;
+    a.mode_w = w.mode_w;
+    a.mcap = c.mcap;
+    a.rho = w.rho;
+    a.ab = w.ab;
+    a.km = (KM *)w.kmode;
+    a.kv = (KV *)w.kvjp;
+    a.count = w.cell_count;
+    a.start = w.cell_start;
+    launch_k(k_vjp_final<KM, KV>, a.n_final_blocks + (scan ? c.R : 0), 1024, 0, c.stream, a);
     return hipGetLastError();
 }
 
-hipError_t launch_vjp_reduce(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q,
-                             const void *gF)
+hipError_t launch_vjp_final(const LaunchCfg &c, const Workspace &w, int l0, int l1, int scan)
 {
-    return c.prec == RBE_FP64 ? vjp_reduce_dispatch<double, KModeD>(c, w, pos, q, gF)
-                              : vjp_reduce_dispatch<float, KModeF>(c, w, pos, q, gF);
-}
-
-hipError_t launch_vjp_final(const LaunchCfg &c, const Workspace &w)
-{
-    dim3 g(c.max_p, c.R);
-    if (c.prec == RBE_FP64)
-        launch_k(k_vjp_final<KModeD, KVjpD>, g, 64, 0, c.stream, w.sys, w.partial, w.partial_off, c.R,
-                                                           (const KModeD *)w.kmode, w.ab, (KVjpD *)w.kvjp);
-    else
-        launch_k(k_vjp_final<KModeF, KVjpF>, g, 64, 0, c.stream, w.sys, w.partial, w.partial_off, c.R,
-                                                           (const KModeF *)w.kmode, w.ab, (KVjpF *)w.kvjp);
-    return hipGetLastError();
+    return c.prec == RBE_FP64 ? vjp_final_dispatch<KModeD, KVjpD>(c, w, l0, l1, scan)
+                              : vjp_final_dispatch<KModeF, KVjpF>(c, w, l0, l1, scan);
 }
 
 template <typename T, typename KV>
 static hipError_t vjp_gather_dispatch(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q,
-                                      const void *gF, void *gpos, void *gq)
+                                      const void *gF, void *gpos, void *gq, int scatter)
 {
-    const T *p = (const T *)pos, *qq = (const T *)q, *g = (const T *)gF;
-    const KV *kv = (const KV *)w.kvjp;
-    const int n = c.n_force_tiles;
+    VjpGatherArgs<T, KV> a;
+    a.sys = w.sys;
+    a.tiles = w.force_tiles;
+    a.ntiles = c.n_force_tiles;
+    a.pos = (const T *)pos;
+    a.q = (const T *)q;
+    a.gF = (const T *)gF;
+    a.ntot = c.ntot;
+    a.kv = (const KV *)w.kvjp;
+    a.gpos = (T *)gpos;
+    a.gq = (T *)gq;
+    a.do_scatter = scatter;
+    a.start = w.cell_start;
+    a.cellid = w.cellid;
+    a.rank = w.rank;
+    a.packed = w.packed;
+    a.sorted_idx = w.sorted_idx;
+    a.sorted = w.sorted;
+    a.gsorted = (T *)w.gsorted;
+    a.flag = w.flag;
+    a.rt = row_tile_args(c, w);
+    const int n = c.n_force_tiles, rows = scatter ? c.n_row_tiles : 0;
+    a.n_blocks = c.force_split == 1 ? (n + 3) / 4 : (c.force_split == 2 ? (n + 1) / 2 : n);
+    const dim3 g(a.n_blocks + rows);
     switch (c.force_split) {
     case 1:
-        launch_k(k_vjp_gather<T, KV, 1>, (n + 3) / 4, 256, 0, c.stream, w.sys, w.force_tiles, n, p, qq, g, c.ntot, kv,
-                                                                  (T *)gpos, (T *)gq);
+        launch_k(k_vjp_gather<T, KV, 1>, g, 256, 0, c.stream, a);
         break;
     case 2:
-        launch_k(k_vjp_gather<T, KV, 2>, (n + 1) / 2, 256, 0, c.stream, w.sys, w.force_tiles, n, p, qq, g, c.ntot, kv,
-                                                                  (T *)gpos, (T *)gq);
+        launch_k(k_vjp_gather<T, KV, 2>, g, 256, 0, c.stream, a);
         break;
     default:
-        launch_k(k_vjp_gather<T, KV, 4>, n, 256, 0, c.stream, w.sys, w.force_tiles, n, p, qq, g, c.ntot, kv, (T *)gpos,
-                                                        (T *)gq);
+        launch_k(k_vjp_gather<T, KV, 4>, g, 256, 0, c.stream, a);
         break;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_vjp_gather(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q,
-                             const void *gF, void *gpos, void *gq)
+                             const void *gF, void *gpos, void *gq, int scatter)
 {
-    return c.prec == RBE_FP64 ? vjp_gather_dispatch<double, KVjpD>(c, w, pos, q, gF, gpos, gq)
-                              : vjp_gather_dispatch<float, KVjpF>(c, w, pos, q, gF, gpos, gq);
+    return c.prec == RBE_FP64 ? vjp_gather_dispatch<double, KVjpD>(c, w, pos, q, gF, gpos, gq, scatter)
+                              : vjp_gather_dispatch<float, KVjpF>(c, w, pos, q, gF, gpos, gq, scatter);
 }
 
 }  // namespace rbe

@@ -1229,12 +1229,14 @@ __global__ __launch_bounds__(RL_BS) void k_pairs_step(RealArgs<T> a, int single_
 // Stand-alone scatter into cell order (force and energy calls; a time step
 // on the neighbour list scatters inside the totals launch), then blocks that
 // write the wave tiles.
-template <typename Rec>
+// With gF the gradient of the forces moves along (adjoint of the real space).
+template <typename T>
 __global__ __launch_bounds__(256) void k_scatter(const SysDev *__restrict__ sys, const Tile *__restrict__ tiles,
                                                  const int32_t *__restrict__ start, const int32_t *__restrict__ cellid,
-                                                 const int32_t *__restrict__ rank, const Rec *__restrict__ packed,
-                                                 int32_t *__restrict__ sorted_idx, Rec *__restrict__ sorted, int n_tiles,
-                                                 RowTileArgs rt)
+                                                 const int32_t *__restrict__ rank, const void *__restrict__ packed,
+                                                 int32_t *__restrict__ sorted_idx, void *__restrict__ sorted, int n_tiles,
+                                                 RowTileArgs rt, const T *__restrict__ gF, T *__restrict__ gsorted,
+                                                 int64_t ntot)
 {
     if ((int)blockIdx.x >= n_tiles) {
         write_row_tiles(rt, blockIdx.x - n_tiles);
@@ -1244,9 +1246,8 @@ __global__ __launch_bounds__(256) void k_scatter(const SysDev *__restrict__ sys,
     if ((int)threadIdx.x >= t.count) return;
     const int64_t i = sys[t.sys].off + t.start + threadIdx.x;
     const int slot = start[cellid[i] + t.sys] + rank[i];
-    const Rec v = packed[i];
-    sorted_idx[slot] = (int32_t)i;
-    sorted[slot] = v;
+    scatter_record<T>(i, slot, packed, sorted_idx, sorted);
+    if (gF) store4(gsorted, slot, gF[i], gF[ntot + i], gF[2 * ntot + i]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1292,7 +1293,8 @@ __device__ __forceinline__ void vjp_pair(const SysDev &S, T qi, T qj, T dx, T dy
 }
 
 template <typename T, int PPW>
-__global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__restrict__ gF, T *__restrict__ gpos,
+__global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__restrict__ gF,
+                                                    const T *__restrict__ gsorted, T *__restrict__ gpos,
                                                     T *__restrict__ gq, int accumulate)
 {
     using Rec = typename RBT<T>::Rec;
@@ -1348,15 +1350,16 @@ __global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__re
     const Rec *gs = reinterpret_cast<const Rec *>(a.sorted);
     const Rec pa = gs[slot];
     const int64_t i = a.sorted_idx[slot];
-    const T Gix = gF[i], Giy = gF[ntot + i], Giz = gF[2 * ntot + i];
+    T Gix, Giy, Giz;
+    load4(gsorted, slot, Gix, Giy, Giz);
     double dq = 0, rx = 0, ry = 0, rz = 0;
     cell_pairs<T, PPW>(S, a.start + S.cell_off + t.sys, gs, pa, slot, act, S.pair.rsearch2_box, lds[tid >> 6],
                        [&](const Rec &pb, int b, int) {
         T dx, dy, dz, r2;
         displacement(pa, pb, geo, dx, dy, dz, r2);
-        const int64_t jj = a.sorted_idx[b];
-        vjp_pair<T>(S, (T)pa.q, (T)pb.q, dx, dy, dz, r2, Gix - gF[jj], Giy - gF[ntot + jj], Giz - gF[2 * ntot + jj], dq,
-                    rx, ry, rz);
+        T Gjx, Gjy, Gjz;
+        load4(gsorted, b, Gjx, Gjy, Gjz);
+        vjp_pair<T>(S, (T)pa.q, (T)pb.q, dx, dy, dz, r2, Gix - Gjx, Giy - Gjy, Giz - Gjz, dq, rx, ry, rz);
     });
     dq = cell_sum<PPW>(dq);
     rx = cell_sum<PPW>(rx);
@@ -1382,19 +1385,20 @@ hipError_t launch_fill_zero(hipStream_t s, void *ptr, int64_t nbytes)
     return hipGetLastError();
 }
 
-template <typename Rec>
-static void scatter_launch(const LaunchCfg &c, const Workspace &w)
+template <typename T>
+static void scatter_launch(const LaunchCfg &c, const Workspace &w, const void *gF)
 {
-    launch_k(k_scatter<Rec>, c.n_part_tiles + c.n_row_tiles, 256, 0, c.stream, w.sys, w.part_tiles, w.cell_start, w.cellid,
-             w.rank, (const Rec *)w.packed, w.sorted_idx, (Rec *)w.sorted, c.n_part_tiles, row_tile_args(c, w));
+    launch_k(k_scatter<T>, c.n_part_tiles + c.n_row_tiles, 256, 0, c.stream, w.sys, w.part_tiles, w.cell_start, w.cellid,
+             w.rank, w.packed, w.sorted_idx, w.sorted, c.n_part_tiles, row_tile_args(c, w), (const T *)gF,
+             (T *)w.gsorted, c.ntot);
 }
 
-hipError_t launch_scatter(const LaunchCfg &c, const Workspace &w)
+hipError_t launch_scatter(const LaunchCfg &c, const Workspace &w, const void *gF)
 {
     if (c.prec == RBE_FP64)
-        scatter_launch<PartD>(c, w);
+        scatter_launch<double>(c, w, gF);
     else
-        scatter_launch<PackF>(c, w);
+        scatter_launch<float>(c, w, gF);
     return hipGetLastError();
 }
 
@@ -1527,20 +1531,21 @@ hipError_t launch_energy_sum(const LaunchCfg &c, const Workspace &w)
 }
 
 template <typename T>
-static void vjp_real_launch(const LaunchCfg &c, RealArgs<T> a, const void *gF, void *gpos, void *gq, int accumulate)
+static void vjp_real_launch(const LaunchCfg &c, RealArgs<T> a, const void *gF, const void *gsorted, void *gpos, void *gq,
+                            int accumulate)
 {
     a.tiles = a.wave_tiles;
     launch_k(c.cell_ppw == 8 ? k_vjp_real<T, 8> : k_vjp_real<T, 16>, c.n_cell_tiles / 4, RL_BS, 0, c.stream, a,
-             (const T *)gF, (T *)gpos, (T *)gq, accumulate);
+             (const T *)gF, (const T *)gsorted, (T *)gpos, (T *)gq, accumulate);
 }
 
 hipError_t launch_vjp_real(const LaunchCfg &c, const Workspace &w, const void *gF, void *gpos, void *gq,
                            int accumulate)
 {
     if (c.prec == RBE_FP64)
-        vjp_real_launch<double>(c, real_args<double>(c, w, nullptr, 0, nullptr, nullptr), gF, gpos, gq, accumulate);
+        vjp_real_launch<double>(c, real_args<double>(c, w, nullptr, 0, nullptr, nullptr), gF, w.gsorted, gpos, gq, accumulate);
     else
-        vjp_real_launch<float>(c, real_args<float>(c, w, nullptr, 0, nullptr, nullptr), gF, gpos, gq, accumulate);
+        vjp_real_launch<float>(c, real_args<float>(c, w, nullptr, 0, nullptr, nullptr), gF, w.gsorted, gpos, gq, accumulate);
     return hipGetLastError();
 }
 
