@@ -475,10 +475,10 @@ __global__ __launch_bounds__(1024) void k_mid(MidArgs<KM> a)
     if (a.reb) {
         if (*a.bin_gate == 0) return;
         using Rec = typename std::conditional<sizeof(KM) == sizeof(KModeF), PackF, PartD>::type;
-        if (b3 == 0)
-            rebuild_scan<16>(a.rb);
+        if (b3 < a.rb.n_scan)
+            rebuild_scan<16>(a.rb, b3);
         else
-            rebuild_scatter<Rec>(a.rb, b3 - 1, a.n_reb_scatter);
+            rebuild_scatter<Rec>(a.rb, b3 - a.rb.n_scan, a.n_reb_scatter);
         return;
     }
     if (!a.do_scan) return;
@@ -1104,6 +1104,7 @@ hipError_t launch_stage(const LaunchCfg &c, const Workspace &w, const StageReque
 // the rebuild itself scales with them (measured at N = 1e5 and 1e6: 16 -> 128
 // blocks, step 41.3 -> 40.5 and 260 -> 255 us).
 constexpr int kRebBlocks = 128;
+constexpr int kScanBlocks = 32;   // a batch's systems are shared by up to so many scan blocks
 
 template <typename KM>
 static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_final, int do_scan,
@@ -1170,12 +1171,13 @@ static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_fi
         r.flag = w.flag;
         r.bins_done = ls->bins_done;
         r.n_bin = a.n_bin_blocks;
+        r.n_scan = std::min(c.R, kScanBlocks);
         r.poison = ls->poison;
         r.wait_limit = c.wait_limit;
     }
     const size_t sm = a.table_lds ? sizeof(double) * c.max_table : 0;
     const int nb = a.n_final_blocks + a.n_bin_blocks + a.n_sample_blocks + (do_scan ? c.R : 0) +
-                   (a.reb ? 1 + a.n_reb_scatter : 0);
+                   (a.reb ? a.rb.n_scan + a.n_reb_scatter : 0);
     if (nb == 0) return hipSuccess;
     const bool lean = !do_scan && !a.n_bin_blocks && !a.n_sample_blocks && !a.reb && !clear_flag;
     if (lean)
