@@ -398,6 +398,7 @@ struct rbe_ctx {
     LaunchCfg cfg{};
     Workspace w{};
     size_t partial_cap = 0;        // doubles allocated for partial
+    int mean_list = 0;             // expected neighbours of a list particle (largest system)
     void *col_mem = nullptr;       // buffers of a dense mode list (one of allocs)
     size_t col_bytes = 0;
     std::vector<void *> allocs;
@@ -590,11 +591,26 @@ void build_list_tiles(rbe_ctx *c, int lpp, std::vector<Tile> &out)
     }
 }
 
+// Lanes per particle of the list pass.  real_split as the caller set it; its
+// default of 4 becomes 8, 16 or 32 while that would leave compute units without a
+// block and the lists are longer than the lanes: the launch then lasts as long as
+// one lane's chain of list rounds (N = 3101, lists of 217: 36 us with 4 lanes,
+// FIGURE us with 32).  The sums over a particle's list are exact in single
+// precision, so the lanes do not change them.
+int list_lanes(const rbe_ctx *c)
+{
+    int lanes = c->cfg.real_split;
+    if (lanes != 4) return lanes;
+    while (lanes < 32 && c->ntot * lanes / 256 < 256 && 2 * lanes <= c->mean_list) lanes *= 2;
+    return lanes;
+}
+
 rbe_status upload_list_tiles(rbe_ctx *c)
 {
     if (!c->cfg.list_on) return RBE_OK;
     std::vector<Tile> lt;
-    build_list_tiles(c, c->cfg.real_split, lt);
+    c->cfg.list_lanes = list_lanes(c);
+    build_list_tiles(c, c->cfg.list_lanes, lt);
     c->cfg.n_list_tiles = (int)lt.size();
     HIPCHK(c, hipMemcpy(c->w.list_tiles, lt.data(), lt.size() * sizeof(Tile), hipMemcpyHostToDevice));
     return RBE_OK;
@@ -862,6 +878,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
             const double dens = (double)p.n / (p.box * p.box * p.box);
             const double mean = dens * 4.0 / 3.0 * kPi * rlist * rlist * rlist;
             kmax = std::max(kmax, (int)std::ceil(1.5 * mean + 32.0));
+            c->mean_list = std::max(c->mean_list, (int)mean);
         }
         c->sysh.push_back(s);
         if (p.sampler == RBE_SAMPLER_MH) c->any_mh = true;
@@ -1012,9 +1029,10 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     ALLOC(w.step_base, sizeof(uint64_t));
     if (any_diam) ALLOC(w.diam, sizeof(double) * ntot);
     {
-        // list-pass tiles: at most one per 32 slots (the 8-lane shape), or the
-        // all-pairs tiles of a one-cell system
-        int64_t nl = 0;
+        // list-pass tiles: at most one per 32 slots (the 8-lane shape; more lanes
+        // are taken only with fewer than 512 tiles), or the all-pairs tiles of
+        // a one-cell system
+        int64_t nl = R + 512;
         for (int r = 0; r < R; ++r) {
             const int step = c->sysh[r].nc == 1 ? real_allpairs_per_tile() : 32;
             nl += (c->sysh[r].n + step - 1) / step;

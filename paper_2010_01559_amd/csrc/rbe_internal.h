@@ -257,6 +257,7 @@ struct LaunchCfg {
     int list_on;     // some system uses the neighbour list
     int all_pairs;   // every system has one cell: steps run without any list or cell work
     int kmax;        // list capacity per particle
+    int list_lanes;  // lanes per particle of the list pass (real_split, or more for small systems)
     int n_list_tiles;
     int wait_limit;  // spin bound of the device-side waits of a list rebuild
     ColumnSet cols;  // the active mode list as columns (rbe_set_k of a dense list)

@@ -996,8 +996,8 @@ constexpr int kListU = 4;
 // raw partner slots of its first round.  None depends on the Fourier part,
 // so the force launch issues these loads before it and their latency
 // overlaps the Fourier arithmetic.  The first round's slots are read whatever
-// the length (its columns, below 4 LPP <= 32, lie inside the list's kmax
-// columns; a clamp keeps them there) and replaced by the particle's own slot
+// the length (its columns are below 4 LPP; a clamp keeps them inside the list's
+// kmax columns) and replaced by the particle's own slot
 // past the length before any is used.
 template <typename T>
 struct ListHead {
@@ -1476,7 +1476,7 @@ static void real_step_dispatch(const LaunchCfg &c, const RealArgs<T> &a, const L
                  la.single_n, la.single_p);
         return;
     }
-    switch (c.real_split) {
+    switch (c.list_lanes) {
     case 1:
         real_step_launch<T, 1>(c, a, la);
         break;
@@ -1485,6 +1485,12 @@ static void real_step_dispatch(const LaunchCfg &c, const RealArgs<T> &a, const L
         break;
     case 8:
         real_step_launch<T, 8>(c, a, la);
+        break;
+    case 16:
+        real_step_launch<T, 16>(c, a, la);
+        break;
+    case 32:
+        real_step_launch<T, 32>(c, a, la);
         break;
     default:
         real_step_launch<T, 4>(c, a, la);
