@@ -595,7 +595,7 @@ void build_list_tiles(rbe_ctx *c, int lpp, std::vector<Tile> &out)
 // default of 4 becomes 8, 16 or 32 while that would leave compute units without a
 // block and the lists are longer than the lanes: the launch then lasts as long as
 // one lane's chain of list rounds (N = 3101, lists of 217: 36 us with 4 lanes,
-// FIGURE us with 32).  The sums over a particle's list are exact in single
+// 12 us with 32).  The sums over a particle's list are exact in single
 // precision, so the lanes do not change them.
 int list_lanes(const rbe_ctx *c)
 {
