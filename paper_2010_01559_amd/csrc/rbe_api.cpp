@@ -155,16 +155,42 @@ void pair_constants(SysDev &s)
     c.rlist2_box = (float)(s.rlist2 / (s.L * s.L) * (1.0 + 1e-6));
 }
 
-// Default tile shapes for ntot particles: one structure-factor block per
-// compute unit when the particles allow (the block's registers leave room
-// for one 1024-thread block per CU); four waves share a 64-particle tile in
-// the force pass while the tiles alone would not fill the chip several
-// times over, two beyond.
+// Structure-factor shape of the calls without a context: one 1024-thread block
+// per compute unit when the particles allow.
 int default_rho_chunk(int64_t ntot)
 {
     return (int)std::min<int64_t>(512, std::max<int64_t>(64, ((ntot + 255) / 256 + 7) / 8 * 8));
 }
 
+// Default structure-factor shape of a context.  The step's block integrates its
+// chunk from memory and then works on the chunk's sums; 512 threads leave room for
+// a second block (256 threads for four more) whose loads run under them.
+// - Up to a block of 512 particles per compute unit, one block each: its 512
+//   threads cost less to synchronise than 1024 and cover a 64-particle chunk's
+//   terms (N = 1e4 in double precision 32.2 -> 30.8 us a step), 256 do where the
+//   chunk has fewer than 4096 of them (N = 300, P = 10: 21.4 -> 20.4 us).
+// - Beyond, lists of at least 160 modes, whose sums outweigh the loads, and double
+//   precision take two blocks of 512 threads per compute unit and round (N = 1e6,
+//   P = 200: 331 us a step with 512 particles on 1024 threads, 276 with 984 on
+//   512, 285 with 512 on 256), shorter lists three of 256 (N = 1e6, P = 50: 249 and 214 us
+//   with 1024 / 512, 201 with 512 / 256; 64 x 20000, P = 100: 177, 152, 146 us).
+void default_rho_shape(int64_t ntot, int max_p, int prec, int *chunk, int *block)
+{
+    const auto per = [&](int64_t blocks) { return (int)(((ntot + blocks - 1) / blocks + 7) / 8 * 8); };
+    if (ntot <= 256 * 512) {
+        *chunk = std::max(64, per(256));
+        *block = (int64_t)*chunk * max_p < 4096 ? 256 : 512;
+    } else if (max_p >= 160 || prec == RBE_FP64) {
+        *chunk = per(512 * ((ntot + 512 * 1024 - 1) / (512 * 1024)));
+        *block = 512;
+    } else {
+        *chunk = std::min(512, per(768));
+        *block = 256;
+    }
+}
+
+// Four waves share a 64-particle tile in the force pass while the tiles alone
+// would not fill the chip several times over, two beyond.
 int default_force_split(int64_t ntot) { return ntot >= 500000 ? 2 : 4; }
 
 // ---------------------------------------------------------------------------
@@ -904,8 +930,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     g.prec = c->prec;
     g.ntot = ntot;
     g.mcap = c->mcap;
-    g.rho_chunk = default_rho_chunk(ntot);
-    g.rho_block = 1024;
+    default_rho_shape(ntot, c->max_p, c->prec, &g.rho_chunk, &g.rho_block);
     g.force_split = default_force_split(ntot);
     g.real_split = 4;
     g.kmax = std::min((kmax + 7) & ~7, 1024);

@@ -248,6 +248,15 @@ __device__ __forceinline__ void rho_term(const PartD &v, double mx, double my, d
 constexpr int kRhoGroupsMax = 32;
 constexpr int kRhoUnroll = 8;
 
+// A lane takes two modes of lists of at least kRhoTwoModes in chunks of at least
+// kRhoTwoChunk particles: every record it reads serves two terms, and the 32-byte
+// reads of 64 lanes bound the one-mode loop (64 x 20000, P = 100: 151 -> 144 us
+// a step; N = 3e5, P = 200: 101 -> 95 us).  The second mode's sum over the groups costs
+// a round more, which short chunks do not win back (N = 3000: 21.1 instead of
+// 20.6 us).  Double precision is bound by its sines and takes one.
+constexpr int kRhoTwoModes = 64;
+constexpr int kRhoTwoChunk = 256;
+
 // VAR = 0 compiles a lean variant for launches that only stage the
 // particles and compute structure factors (force calls, energies, long
 // Ewald lists): without the integrator, binning, sampling and list code it
@@ -352,11 +361,13 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
     const int mb = (int)(((int64_t)P * blockIdx.y) / ys), me = (int)(((int64_t)P * (blockIdx.y + 1)) / ys);
     const int Pm = me - mb;
     if (Pm <= 0) return;
-    const int Pt = Pm < BS ? Pm : BS;
-    const int G = BS / Pt < kRhoGroupsMax ? BS / Pt : kRhoGroupsMax;
+    const bool two = sizeof(T) == 4 && Pm >= kRhoTwoModes && a.chunk >= kRhoTwoChunk;
+    const int Pt = min(Pm, BS), Pl = two ? (Pt + 1) / 2 : Pt;
+    const int G = min(BS / Pl, kRhoGroupsMax);
+    const int U = two ? kRhoUnroll / 2 : kRhoUnroll;
     // zero-charge records up to a multiple of 8 G, so the unrolled loop
     // below needs no bounds tests
-    const int cpad = (count + kRhoUnroll * G - 1) / (kRhoUnroll * G) * (kRhoUnroll * G);
+    const int cpad = (count + U * G - 1) / (U * G) * (U * G);
     for (int j = count + tid; j < cpad; j += BS) {
         RR z{};
         sp[j] = z;
@@ -388,31 +399,54 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
             smode[2 * BS + tid] = mz;
         }
         __syncthreads();
-        const int lt = tid % Pt, g = tid / Pt;
+        const int lt = tid % Pl, g = tid / Pl;
         const int l = m0 + lt;
         const bool act = g < G && l < me;
-        double C = 0.0, Sn = 0.0;
+        double C = 0.0, Sn = 0.0, C2 = 0.0, Sn2 = 0.0;
         if (act) {
             const T mx = (T)smode[lt], my = (T)smode[BS + lt], mz = (T)smode[2 * BS + lt];
-            for (int j0 = g; j0 < cpad; j0 += kRhoUnroll * G) {
-                T c8 = 0, s8 = 0;
+            if (two) {
+                // the last lane of an odd count repeats a mode that is not stored
+                const int l2 = min(lt + Pl, Pt - 1);
+                const T nx = (T)smode[l2], ny = (T)smode[BS + l2], nz = (T)smode[2 * BS + l2];
+                for (int j0 = g; j0 < cpad; j0 += kRhoUnroll / 2 * G) {
+                    T c8 = 0, s8 = 0, c9 = 0, s9 = 0;
 #pragma unroll
-                for (int u = 0; u < kRhoUnroll; ++u) rho_term(sp[j0 + u * G], mx, my, mz, c8, s8);
-                C += (double)c8;
-                Sn += (double)s8;
+                    for (int u = 0; u < kRhoUnroll / 2; ++u) {
+                        const RR v = sp[j0 + u * G];
+                        rho_term(v, mx, my, mz, c8, s8);
+                        rho_term(v, nx, ny, nz, c9, s9);
+                    }
+                    C += (double)c8;
+                    Sn += (double)s8;
+                    C2 += (double)c9;
+                    Sn2 += (double)s9;
+                }
+            } else {
+                for (int j0 = g; j0 < cpad; j0 += kRhoUnroll * G) {
+                    T c8 = 0, s8 = 0;
+#pragma unroll
+                    for (int u = 0; u < kRhoUnroll; ++u) rho_term(sp[j0 + u * G], mx, my, mz, c8, s8);
+                    C += (double)c8;
+                    Sn += (double)s8;
+                }
             }
         }
-        red[tid] = make_double2(C, Sn);
-        __syncthreads();
-        if (tid < Pt && l < me) {
-            double c = 0.0, s = 0.0;
-            for (int gg = 0; gg < G; ++gg) {
-                const double2 v = red[gg * Pt + lt];
-                c += v.x;
-                s += v.y;
+        for (int h = 0; h <= (two ? 1 : 0); ++h) {
+            if (h) __syncthreads();
+            red[tid] = h ? make_double2(C2, Sn2) : make_double2(C, Sn);
+            __syncthreads();
+            const int lh = l + h * Pl;
+            if (tid < Pl && lh < m0 + Pt && lh < me) {
+                double c = 0.0, s = 0.0;
+                for (int gg = 0; gg < G; ++gg) {
+                    const double2 v = red[gg * Pl + lt];
+                    c += v.x;
+                    s += v.y;
+                }
+                prow[2 * lh] = c;
+                prow[2 * lh + 1] = s;
             }
-            prow[2 * l] = c;
-            prow[2 * l + 1] = s;
         }
         // the next mode tile reuses smode and red; after the last one the
         // block ends without waiting for its stores
