@@ -235,7 +235,8 @@ __global__ __launch_bounds__(256) void k_col_final(ColArgs a, int groups, const 
         in.w = w[e];
         in.coulomb = S.coulomb;
         in.L = S.L;
-        make_kmode<KM>(in, r.x, sg * r.y, rho, km);
+        in.polar = S.polar;
+        make_kmode<KM>(in, force_coefficient(in), r.x, sg * r.y, rho, km);
     }
     // g+- = f w rho / |m|^2, a pair's weights added; P = g+ + g-, Q = g+ - g-
     const double m2 = (double)col.mx * col.mx + (double)col.my * col.my + (double)n * n;

@@ -277,6 +277,16 @@ __device__ __forceinline__ const __attribute__((address_space(4))) KM *uniform_m
     return (const __attribute__((address_space(4))) KM *)(((uint64_t)hi << 32) | lo);
 }
 
+__device__ __forceinline__ void load_factor(const __attribute__((address_space(4))) KModeF &s, KModeF &k) {
+    k.u = s.u;
+    k.v = s.v;
+}
+__device__ __forceinline__ void load_factor(const __attribute__((address_space(4))) KModeD &s, KModeD &k)
+{
+    k.C = s.C;
+    k.S = s.S;
+}
+
 template <typename KM>
 __device__ __forceinline__ KM load_mode(const __attribute__((address_space(4))) KM *kk, int l)
 {
@@ -285,17 +295,27 @@ __device__ __forceinline__ KM load_mode(const __attribute__((address_space(4))) 
         k.m[d] = kk[l].m[d];
         k.a[d] = kk[l].a[d];
     }
-    k.C = kk[l].C;
-    k.S = kk[l].S;
+    load_factor(kk[l], k);
     return k;
 }
 
-// The term of one mode.
+// The term of one mode.  POLAR: one sine of the particle's phase less the
+// structure factor's.  frac(m.hi) and u are multiples of 2^-24 in [0, 1), so
+// their difference is exact, and only the sum with the small rest rounds, as a
+// phase alone does.
+template <bool POLAR>
 __device__ __forceinline__ void fourier_term(const KModeF &k, const float h[3], const float lo[3], float f[3])
 {
-    const float rf = phase_split(k.m[0], k.m[1], k.m[2], h[0], h[1], h[2], lo[0], lo[1], lo[2]);
-    const float sn = __builtin_amdgcn_sinf(rf), cs = __builtin_amdgcn_cosf(rf);
-    const float im = cs * k.S - sn * k.C;
+    float im;
+    if constexpr (POLAR) {
+        const float hi = fmaf(k.m[0], h[0], fmaf(k.m[1], h[1], k.m[2] * h[2]));
+        const float l = fmaf(k.m[0], lo[0], fmaf(k.m[1], lo[1], k.m[2] * lo[2]));
+        im = __builtin_amdgcn_sinf((__builtin_amdgcn_fractf(hi) - k.u) + (l + k.v));
+    } else {
+        const float rf = phase_split(k.m[0], k.m[1], k.m[2], h[0], h[1], h[2], lo[0], lo[1], lo[2]);
+        const float sn = __builtin_amdgcn_sinf(rf), cs = __builtin_amdgcn_cosf(rf);
+        im = cs * k.v - sn * k.u;
+    }
     f[0] = fmaf(im, k.a[0], f[0]);
     f[1] = fmaf(im, k.a[1], f[1]);
     f[2] = fmaf(im, k.a[2], f[2]);
@@ -312,14 +332,19 @@ __device__ __forceinline__ void fourier_term(const KModeD &k, const double s[3],
     f[2] = fma(im, k.a[2], f[2]);
 }
 
-__device__ __forceinline__ void fourier_range(const KModeF *kk0, int l0, int l1, const float h[3], const float lo[3],
-                                              float f[3])
+__device__ __forceinline__ void fourier_range(const KModeF *kk0, int l0, int l1, int polar, const float h[3],
+                                              const float lo[3], float f[3])
 {
     const auto kk = uniform_modes(kk0);
     l0 = __builtin_amdgcn_readfirstlane(l0);
     l1 = __builtin_amdgcn_readfirstlane(l1);
+    if (polar) {
 #pragma unroll 4
-    for (int l = l0; l < l1; ++l) fourier_term(load_mode(kk, l), h, lo, f);
+        for (int l = l0; l < l1; ++l) fourier_term<true>(load_mode(kk, l), h, lo, f);
+    } else {
+#pragma unroll 4
+        for (int l = l0; l < l1; ++l) fourier_term<false>(load_mode(kk, l), h, lo, f);
+    }
 }
 
 __device__ __forceinline__ void fourier_range(const KModeD *kk0, int l0, int l1, const double s[3], double f[3])

@@ -90,7 +90,7 @@ struct SysDev {
     int32_t hi_bits;       // FP32 phases: box fractions split as hi (multiple of 2^-hi_bits) + lo
     float hi_scale, hi_inv;  // 2^hi_bits, 2^-hi_bits
     int32_t ctile_off;     // first wave tile of this system (Workspace::cell_tiles)
-    int32_t pad0;
+    int32_t polar;         // FP32: the mode constants hold the structure factor in polar form
     int32_t n_fixed;       // particles 0 .. n_fixed-1 never move
     int32_t diam_on;       // per-particle diameters: LJ with r_off = (d_i + d_j)/2 - sigma
     double L, invL;
@@ -122,11 +122,15 @@ struct Tile {
 
 // Per-mode constants for the force pass (single precision path): the mode
 // (small integers, exact in float), the force coefficients
-// a = w 2 m/(L^2 |m|^2) and the structure factor (C, S).
+// a = w 2 m/(L^2 |m|^2) and the structure factor (u = C, v = S).
+// With SysDev::polar the structure factor is in polar form, C + i S = A
+// exp(2 pi i t): a is multiplied by -A, u is a multiple of 2^-24 in [0, 1), v
+// at most 2^-25, and u - v = t, so that a particle's term is one sine,
+//   S cos(2 pi m.s) - C sin(2 pi m.s) = -A sin(2 pi (m.s - t)).
 struct KModeF {
     float m[3];
     float a[3];
-    float C, S;
+    float u, v;
 };
 
 struct KModeD {

@@ -597,7 +597,7 @@ __global__ __launch_bounds__(256) void k_kforce(ForceArgs<T, KM> a)
         if constexpr (sizeof(T) == 4) {
             float h[3], lo[3];
             for (int d = 0; d < 3; ++d) split_frac(s3[d], S, h[d], lo[d]);
-            fourier_range(kk, l0, l1, h, lo, f);
+            fourier_range(kk, l0, l1, S.polar, h, lo, f);
         } else {
             fourier_range(kk, l0, l1, s3, f);
         }
@@ -900,16 +900,16 @@ __global__ __launch_bounds__(1024) void k_vjp_final(VjpFinalArgs<KM, KV> a)
         bv += __shfl_down(bv, off, 64);
     }
     if (lane != 0) return;
-    make_kmode<KM>(in, c, s, a.rho, a.km);
+    const double f = force_coefficient(in);
+    make_kmode<KM>(in, f, c, s, a.rho, a.km);
     const int o = in.o;
     a.ab[2 * o] = av;
     a.ab[2 * o + 1] = bv;
-    const KM k = a.km[o];
     KV v;
     const double tp = 2.0 * kPi * S.invL, m[3] = {in.mx, in.my, in.mz};
     for (int d = 0; d < 3; ++d) {
-        v.m[d] = k.m[d];
-        v.a[d] = k.a[d];
+        v.m[d] = m[d];
+        v.a[d] = f * m[d];
         v.k[d] = tp * m[d];
     }
     v.C = c;

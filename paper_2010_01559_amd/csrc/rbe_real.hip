@@ -410,7 +410,7 @@ __device__ __forceinline__ void fourier_tile(const RealArgs<T> &a, const SysDev 
                 split_fix(r.x, S, h[0], lo[0]);
                 split_fix(r.y, S, h[1], lo[1]);
                 split_fix(r.z, S, h[2], lo[2]);
-                fourier_range(kk, l0, l1, h, lo, f);
+                fourier_range(kk, l0, l1, S.polar, h, lo, f);
             } else {
                 const double s3[3] = {r.x, r.y, r.z};
                 fourier_range(kk, l0, l1, s3, f);
@@ -476,7 +476,12 @@ __device__ __forceinline__ void fourier_lanes(const RealArgs<T> &a, const SysDev
         split_fix(pa.x, S, h[0], lo[0]);
         split_fix(pa.y, S, h[1], lo[1]);
         split_fix(pa.z, S, h[2], lo[2]);
-        for (int l = threadIdx.x & 63; l < S.p; l += 64) fourier_term(kk[l], h, lo, g);
+        for (int l = threadIdx.x & 63; l < S.p; l += 64) {
+            if (S.polar)
+                fourier_term<true>(kk[l], h, lo, g);
+            else
+                fourier_term<false>(kk[l], h, lo, g);
+        }
     } else {
         const double s3[3] = {pa.x, pa.y, pa.z};
         for (int l = threadIdx.x & 63; l < S.p; l += 64) fourier_term(kk[l], s3, g);

@@ -22,7 +22,7 @@ namespace rbe {
 // latency overlaps the sums.
 struct KModeIn {
     double mx, my, mz, w, coulomb, L;
-    int o;
+    int o, polar;
 };
 
 __device__ __forceinline__ KModeIn kmode_in(const SysDev &S, int moff, int l, const int32_t *modes,
@@ -36,29 +36,90 @@ __device__ __forceinline__ KModeIn kmode_in(const SysDev &S, int moff, int l, co
     in.w = mode_w[in.o];
     in.coulomb = S.coulomb;
     in.L = S.L;
+    in.polar = S.polar;
     return in;
 }
 
-// Structure factor totals and force constants of mode in.o:
+// Polar form of the structure factor c + i s: modulus A and phase
+// t = u - v in revolutions (see KModeF), the phase within 1e-8.  It is straight-line code
+// on the totals launch's critical path, where fetching instructions is what costs,
+// so it is short: the phase is an eighth of a turn's multiple and an odd
+// polynomial of degree 11 (Chebyshev fit of atan(z) / (2 pi z) in z^2,
+// |z| <= tan(pi/8)).  The library's hypot and atan2 took 0.9 us more (launch
+// of 100 modes at N = 3000).
+__device__ __forceinline__ void polar(double c, double s, double &A, float &u, float &v)
+{
+    const double x = fabs(c), y = fabs(s), hi = fmax(x, y), lo = fmin(x, y);
+    const double d2 = fma(hi, hi, lo * lo);
+    const double r = __builtin_amdgcn_rsq(d2), a = d2 * r;
+    const bool red = lo > 0.41421356237309503 * hi;
+    float z = (float)((red ? lo - hi : lo) * __builtin_amdgcn_rcp(red ? lo + hi : hi));
+    A = fma(fma(-a, a, d2), 0.5 * r, a);
+    if (d2 == 0.0) {
+        A = 0.0;
+        z = 0.0f;
+    }
+    const float w = z * z;
+    float p = fmaf(w, -0.00960183144f, 0.0168270133f);
+    p = fmaf(w, p, -0.0226636175f);
+    p = fmaf(w, p, 0.031828139f);
+    p = fmaf(w, p, -0.0530516058f);
+    p = fmaf(w, p, 0.159154937f);
+    // t = e + k
+    float e = p * z, k = red ? 0.125f : 0.0f;
+    if (y > x) {
+        e = -e;
+        k = 0.25f - k;
+    }
+    if (c < 0.0) {
+        e = -e;
+        k = 0.5f - k;
+    }
+    if (s < 0.0) {
+        e = -e;
+        k = -k;
+    }
+    const float eh = rintf(e * 16777216.0f) * (1.0f / 16777216.0f);
+    u = __builtin_amdgcn_fractf(k + eh);
+    v = eh - e;
+}
+
+// Force coefficient of mode m without its factor m:
 //   a_l = coulomb w_l 2 m_l / (L^2 |m_l|^2)   (eq. 3.6 with k = 2 pi m / L).
+__device__ __forceinline__ double force_coefficient(const KModeIn &in)
+{
+    const double m2 = in.mx * in.mx + in.my * in.my + in.mz * in.mz;
+    return in.coulomb * in.w * 2.0 / (in.L * in.L * m2);
+}
+
+// Structure factor totals and force constants of mode in.o, f its
+// force_coefficient().
 template <typename KM>
-__device__ __forceinline__ void make_kmode(const KModeIn &in, double c, double s, double *rho, KM *km)
+__device__ __forceinline__ void make_kmode(const KModeIn &in, double f, double c, double s, double *rho, KM *km)
 {
     const int o = in.o;
     rho[2 * o] = c;
     rho[2 * o + 1] = s;
     const double mx = in.mx, my = in.my, mz = in.mz;
-    const double m2 = mx * mx + my * my + mz * mz;
-    const double f = in.coulomb * in.w * 2.0 / (in.L * in.L * m2);
     KM k;
+    if constexpr (sizeof(KM) == sizeof(KModeF)) {
+        k.u = c;
+        k.v = s;
+        if (in.polar) {
+            double A;
+            polar(c, s, A, k.u, k.v);
+            f *= -A;
+        }
+    } else {
+        k.C = c;
+        k.S = s;
+    }
     k.m[0] = mx;
     k.m[1] = my;
     k.m[2] = mz;
     k.a[0] = f * mx;
     k.a[1] = f * my;
     k.a[2] = f * mz;
-    k.C = c;
-    k.S = s;
     km[o] = k;
 }
 
@@ -249,6 +310,8 @@ __device__ void mid_final(const MidArgs<KM> &a, int blk)
             s += __shfl_down(s, off, 64);
         }
     }
+    // in every lane, without a branch: its divisions run under the shuffles
+    const double f = force_coefficient(in);
     if (lane == 0) q_sum[wave] = make_double2(c, s);
     __syncthreads();
     if (ok && q == 0 && lane == 0) {
@@ -257,7 +320,7 @@ __device__ void mid_final(const MidArgs<KM> &a, int blk)
             cc += q_sum[wave + k].x;
             ss += q_sum[wave + k].y;
         }
-        make_kmode<KM>(in, cc, ss, a.rho, a.km);
+        make_kmode<KM>(in, f, cc, ss, a.rho, a.km);
     }
 }
 

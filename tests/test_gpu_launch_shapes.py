@@ -87,3 +87,24 @@ def test_list_lanes(n, r_cut):
         out.append((host(P), host(V), host(F)))
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("charge", [0.0, 1e-25, 1e15])
+def test_polar_form_range(charge):
+    """2^23 particle-mode terms and more take the structure factor in polar form:
+    with no charges the force is zero, and it scales over the range of charges."""
+    s = _random_system(65536, 128)
+    modes, _ = O.sample_modes(s.alpha, s.L, s.p, s.seed, 1)
+    pos, q = rounded(s, R.RBE_FP32)
+    f1 = O.rbe_kspace_force(pos, q, s.L, s.alpha, modes)
+    ctx = make_ctx(s, R.RBE_FP32)
+    P, Q, V, F = device_state(ctx, s)
+    R.rbe_set_k(ctx, modes)
+    R.rbe_kspace_forces(ctx, P, (Q.double() * charge).float(), F)
+    f = host(F)
+    if charge == 0.0:
+        assert (f == 0.0).all()
+    elif charge < 1.0:
+        assert np.isfinite(f).all()          # below the range of single precision
+    else:
+        assert rel_l2(f, f1 * charge * charge) <= 1e-5
