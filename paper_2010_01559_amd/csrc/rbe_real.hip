@@ -1133,8 +1133,12 @@ __device__ __forceinline__ int wave_slot() { return __builtin_amdgcn_s_getreg((4
 // index as the host builds it, and takes the system's particle and mode
 // offsets (both 0) and its mode count from the launch, so that the record and
 // mode-constant loads do not wait for the tile and the system constants.
+// Seven waves per SIMD (72 registers, a few of the rebuild's in scratch): the list
+// pass waits on its gathers, and 1792 blocks at once take N = 1e5 (1563) without a
+// second round (N = 1e6 step 267 -> 263 us against six; eight spill into the list
+// pass, 271 us).
 template <typename T, int LPP, bool DIAM, bool SINGLE>
-__global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 6 : 1) void k_real_step(RealArgs<T> a, ListArgs la)
+__global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 7 : 1) void k_real_step(RealArgs<T> a, ListArgs la)
 {
     __shared__ union {
         T s4[4][FT_MAX][3];
