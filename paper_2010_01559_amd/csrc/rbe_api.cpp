@@ -900,6 +900,8 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         s.c1 = std::exp(-p.gamma * p.dt / p.mass);
         s.c2 = std::sqrt((1.0 - s.c1 * s.c1) * p.kT / p.mass);
         s.nu_dt = p.nu * p.dt;
+        s.h_m = 0.5 * p.dt / p.mass;
+        s.sv = std::sqrt(p.kT / p.mass);
         s.nu = p.nu;
         s.anneal = 0.0;
         s.seed = p.seed;
@@ -1729,6 +1731,7 @@ rbe_status rbe_set_dt(rbe_ctx *c, double dt, double anneal)
         s.c1 = std::exp(-p.gamma * dt / p.mass);
         s.c2 = std::sqrt((1.0 - s.c1 * s.c1) * p.kT / p.mass);
         s.nu_dt = p.nu * dt;
+        s.h_m = 0.5 * dt / s.mass;
         s.anneal = anneal;
     }
     return upload_sys(c);

@@ -299,6 +299,14 @@ __device__ __forceinline__ KM load_mode(const __attribute__((address_space(4))) 
     return k;
 }
 
+// t / d for 0 <= t < 2^16 and d >= 1, exact (the quotient of t + 1/2 is at least 1/(2 d)
+// from an integer): a sixth of the instructions of an integer division, which
+// count where a block's one wave works alone.
+__device__ __forceinline__ int small_div(int t, int d)
+{
+    return (int)(((float)t + 0.5f) * __builtin_amdgcn_rcpf((float)d));
+}
+
 // The term of one mode.  POLAR: one sine of the particle's phase less the
 // structure factor's.  frac(m.hi) and u are multiples of 2^-24 in [0, 1), so
 // their difference is exact, and only the sum with the small rest rounds, as a
@@ -382,21 +390,52 @@ __device__ __forceinline__ int xcd_tile(int b, int n)
 __device__ __forceinline__ double step_dt(const SysDev &S, uint64_t n)
 {
     if (S.anneal <= 0.0) return S.dt;
-    return S.anneal / log1p(n < 1 ? 1.0 : (double)n);
+    double x = n < 1 ? 1.0 : (double)n;
+    // keeps the logarithm (and what follows from it) in this branch: without it the
+    // compiler ran them before the loop over the particles on every step,
+    // 600 double-precision instructions and 1 us for nothing
+    asm volatile("" : "+v"(x));
+    return S.anneal / log1p(x);
+}
+
+// Constants of one integrator step of a system.
+struct StepConst {
+    double dt;
+    double hm;       // force to velocity: dt/(2 mass) (Langevin) or dt/mass (Andersen)
+    double hk;       // the previous step's closing half kick, dt/(2 mass)
+    double c1, c2;   // Langevin velocity update
+    double nu_dt;    // Andersen collision probability
+};
+
+__device__ __forceinline__ StepConst step_const(const SysDev &S, uint64_t step, bool kick)
+{
+    const bool langevin = S.integrator == RBE_LANGEVIN_BAOAB;
+    StepConst k{S.dt, langevin ? S.h_m : 2.0 * S.h_m, S.h_m, S.c1, S.c2, S.nu_dt};
+    if (S.anneal > 0.0) {
+        k.dt = step_dt(S, step);
+        k.hm = (langevin ? 0.5 * k.dt : k.dt) / S.mass;
+        if (kick) k.hk = 0.5 * step_dt(S, step - 1) / S.mass;
+        k.nu_dt = S.nu * k.dt;
+        if (langevin) {
+            k.c1 = exp(-S.gamma * k.dt / S.mass);
+            k.c2 = sqrt((1.0 - k.c1 * k.c1) * S.kT / S.mass);
+        }
+    }
+    return k;
 }
 
 template <typename T>
-__device__ __forceinline__ void integrate_comp(const SysDev &S, T p0, T v0, T f, double xi, bool hit, bool kick,
-                                               double dt, double dt_prev, double c1, double c2, T &p1, T &v1)
+__device__ __forceinline__ void integrate_comp(const SysDev &S, const StepConst &c, T p0, T v0, T f, double xi,
+                                               bool hit, bool kick, T &p1, T &v1)
 {
     if (S.integrator == RBE_LANGEVIN_BAOAB) {
-        const double h = 0.5 * dt;
+        const double h = 0.5 * c.dt;
         // the previous step's closing half kick, rounded to T as if it had
         // been stored by the force pass
-        if (kick) v0 = (T)fma(0.5 * dt_prev / S.mass, (double)f, (double)v0);
-        double v = (double)v0 + h * (double)f / S.mass;         // B
+        if (kick) v0 = (T)fma(c.hk, (double)f, (double)v0);
+        double v = fma(c.hm, (double)f, (double)v0);            // B
         double r = (double)p0 + h * v;                          // A
-        v = c1 * v + c2 * xi;                                   // O
+        v = c.c1 * v + c.c2 * xi;                                   // O
         r += h * v;                                             // A
         r -= S.L * floor(r * S.invL);
         T rs = (T)r;
@@ -405,26 +444,26 @@ __device__ __forceinline__ void integrate_comp(const SysDev &S, T p0, T v0, T f,
         v1 = (T)v;
         return;
     }
-    const double sv = sqrt(S.kT / S.mass);
-    const double v = (double)v0 + dt * (double)f / S.mass;
-    double r = (double)p0 + dt * v;
+    const double v = fma(c.hm, (double)f, (double)v0);
+    double r = (double)p0 + c.dt * v;
     r -= S.L * floor(r * S.invL);
     T rs = (T)r;
     if (rs >= (T)S.L || rs < (T)0) rs = (T)0;
     p1 = rs;
-    v1 = (T)(hit ? sv * xi : v);
+    v1 = (T)(hit ? S.sv * xi : v);
 }
 
 // Andersen collision of particle il at step.
-__device__ __forceinline__ bool andersen_hit(const SysDev &S, int il, uint64_t step)
+__device__ __forceinline__ bool andersen_hit(const SysDev &S, int il, uint64_t step, double nu_dt)
 {
     const U4 w = draw((uint32_t)il, kTagAndersen, S.seed, step);
-    return (double)w.x * (1.0 / 4294967296.0) < (S.anneal > 0.0 ? S.nu * step_dt(S, step) : S.nu_dt);
+    return (double)w.x * (1.0 / 4294967296.0) < nu_dt;
 }
 
 template <typename T>
 __device__ __forceinline__ void integrate_one(const SysDev &S, int il, int64_t i, int64_t ntot, T *pos, T *vel,
-                                              const T *F, uint64_t step, bool kick, double x[3])
+                                              const T *F, uint64_t step, bool kick, const StepConst &c,
+                                              double x[3])
 {
     // all nine loads first, before the branches on the system constants (so
     // they do not wait for them), and since the stores of one component
@@ -443,14 +482,8 @@ __device__ __forceinline__ void integrate_one(const SysDev &S, int il, int64_t i
         for (int d = 0; d < 3; ++d) x[d] = (double)p0[d];
         return;
     }
-    const bool hit = S.integrator == RBE_LANGEVIN_BAOAB ? false : andersen_hit(S, il, step);
+    const bool hit = S.integrator == RBE_LANGEVIN_BAOAB ? false : andersen_hit(S, il, step, c.nu_dt);
     const bool noise = S.integrator == RBE_LANGEVIN_BAOAB || hit;
-    const double dt = step_dt(S, step), dt_prev = kick ? step_dt(S, step - 1) : 0.0;
-    double c1 = S.c1, c2 = S.c2;
-    if (S.anneal > 0.0 && S.integrator == RBE_LANGEVIN_BAOAB) {
-        c1 = exp(-S.gamma * dt / S.mass);
-        c2 = sqrt((1.0 - c1 * c1) * S.kT / S.mass);
-    }
     // the three normals come from one draw outside the component loop, so
     // that the loop unrolls and its arrays stay in registers
     double xi[3] = {0.0, 0.0, 0.0};
@@ -458,7 +491,7 @@ __device__ __forceinline__ void integrate_one(const SysDev &S, int il, int64_t i
     T p1[3], v1[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        integrate_comp<T>(S, p0[d], v0[d], f[d], xi[d], hit, kick, dt, dt_prev, c1, c2, p1[d], v1[d]);
+        integrate_comp<T>(S, c, p0[d], v0[d], f[d], xi[d], hit, kick, p1[d], v1[d]);
         x[d] = (double)p1[d];
     }
 #pragma unroll

@@ -104,6 +104,8 @@ struct SysDev {
     double kT, gamma, dt, mass;
     double c1, c2;          // Ornstein-Uhlenbeck factors exp(-gamma dt/m), sqrt((1-c1^2) kT/m)
     double nu_dt;           // Andersen collision probability per step
+    double h_m;             // dt / (2 mass)
+    double sv;              // sqrt(kT / mass)
     double nu;              // Andersen collision frequency
     double anneal;          // > 0: the step of index n uses dt = anneal / ln(1 + n) instead of dt
     double rlist2;          // (largest cutoff + skin)^2

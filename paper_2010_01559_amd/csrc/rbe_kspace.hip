@@ -293,7 +293,33 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
     const int K = 2 * S.M + 1;
     if (SAMPLE && a.do_sample && a.table_lds)
         for (int k = tid; k < K; k += BS) tab[k] = a.cdf[S.cdf_off + k];
+    // modes [mb, me) of this block: a launch with gridDim.y > 1 splits long
+    // mode lists (classical Ewald) over blocks; it never integrates, bins or
+    // samples, so every y-block may stage the chunk on its own
+    const int P = a.do_rho ? S.p : 0;
+    const int ys = (int)gridDim.y;
+    int mb = 0, me = P;
+    if (ys > 1) {
+        mb = (int)(((int64_t)P * blockIdx.y) / ys);
+        me = (int)(((int64_t)P * (blockIdx.y + 1)) / ys);
+    }
+    const int Pm = me - mb;
+    // modes that were drawn before: the first tile's are loaded here, so that
+    // their latency runs under the particles' (loaded after them it cost every
+    // step 0.5 us)
+    // By the last waves: in a short chunk the first one has all the particles.
+    const bool drawn = !(SAMPLE && a.do_sample);
+    const int rid = BS - 1 - tid;
+    int m3[3] = {0, 0, 0};
+    if (drawn && rid < Pm) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) m3[d] = a.modes[d * a.mcap + S.moff + mb + rid];
+    }
+    int redo = 0;
     if (FULL && a.list_mode && blockIdx.x == 0 && tid == 0) {
+        // the host's and the overflow's requests; a rebuild that gave up in the
+        // step before is redone
+        redo = a.ls.force_rebuild | *a.ls.overflow | *a.ls.poison;
         // the rebuild of this step (in the totals launch) starts from zero
         *a.ls.ready = 0;
         *a.ls.bins_done = 0;
@@ -301,6 +327,8 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
     bool moved = false;
     const uint64_t base = FULL && a.list_mode && a.ls.step_base ? *a.ls.step_base : 0;
     const uint64_t step = a.step + base, sample_step = a.sample_step + base;
+    StepConst sc{};
+    if (FULL && a.do_integrate) sc = step_const(S, step, a.kick != 0);
     for (int j = tid; j < count; j += BS) {
         const int il = t.start + j;
         const int64_t i = S.off + il;
@@ -311,7 +339,7 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
         ListRef lr;
         if (FULL && EARLY && a.list_mode) load_list_ref<T>(S, i, a.slot_of, a.ref, lr);
         if (FULL && a.do_integrate) {
-            integrate_one<T>(S, il, i, a.ntot, a.pos, a.vel, a.F, step, a.kick != 0, x);
+            integrate_one<T>(S, il, i, a.ntot, a.pos, a.vel, a.F, step, a.kick != 0, sc, x);
         } else {
             x[0] = (double)a.pos[i];
             x[1] = (double)a.pos[a.ntot + i];
@@ -340,66 +368,61 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
         if (FULL && !EARLY && a.list_mode) load_list_ref<T>(S, i, a.slot_of, a.ref, lr);
         if (FULL && a.list_mode) moved |= list_update<T>(S, i, sx, sy, sz, qi, a, lr);
     }
+    const bool two = sizeof(T) == 4 && Pm >= kRhoTwoModes && a.chunk >= kRhoTwoChunk;
+    const int Pt = min(Pm, BS), Pl = two ? (Pt + 1) / 2 : Pt;
+    const int G = min(small_div(BS, max(Pl, 1)), kRhoGroupsMax);
+    const int U = two ? kRhoUnroll / 2 : kRhoUnroll;
+    // zero-charge records up to a multiple of U G, so the unrolled loop
+    // below needs no bounds tests
+    const int cpad = Pm > 0 ? small_div(count + U * G - 1, U * G) * (U * G) : 0;
+    for (int j = count + rid; j < cpad; j += BS) {
+        RR z{};
+        sp[j] = z;
+    }
+    if (drawn && rid < Pm)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) smode[d * BS + rid] = m3[d];
     if (FULL && a.list_mode) {
-        // one request per block; block 0 adds the host's and the overflow's
+        // one request per block
         const int any = __syncthreads_or(moved ? 1 : 0);
-        if (tid == 0) {
-            // a rebuild that gave up in the step before is redone
-            const bool req =
-                any || (blockIdx.x == 0 && (a.ls.force_rebuild || *a.ls.overflow != 0 || *a.ls.poison != 0));
-            if (req) atomicOr(a.ls.rebuild, 1);
-        }
+        if (tid == 0 && (any || redo)) atomicOr(a.ls.rebuild, 1);
     } else {
         __syncthreads();
     }
     if (!a.do_rho) return;
-    const int P = S.p;
-    // modes [mb, me) of this block: a launch with gridDim.y > 1 splits long
-    // mode lists (classical Ewald) over blocks; it never integrates, bins or
-    // samples, so every y-block may stage the chunk on its own
-    const int ys = (int)gridDim.y;
-    const int mb = (int)(((int64_t)P * blockIdx.y) / ys), me = (int)(((int64_t)P * (blockIdx.y + 1)) / ys);
-    const int Pm = me - mb;
     if (Pm <= 0) return;
-    const bool two = sizeof(T) == 4 && Pm >= kRhoTwoModes && a.chunk >= kRhoTwoChunk;
-    const int Pt = min(Pm, BS), Pl = two ? (Pt + 1) / 2 : Pt;
-    const int G = min(BS / Pl, kRhoGroupsMax);
-    const int U = two ? kRhoUnroll / 2 : kRhoUnroll;
-    // zero-charge records up to a multiple of 8 G, so the unrolled loop
-    // below needs no bounds tests
-    const int cpad = (count + U * G - 1) / (U * G) * (U * G);
-    for (int j = count + tid; j < cpad; j += BS) {
-        RR z{};
-        sp[j] = z;
-    }
     const double *tabp = a.table_lds ? tab : a.cdf + S.cdf_off;
     double *prow = a.partial + 2 * ((SINGLE ? 0 : (int64_t)a.part_off[t.sys]) + (int64_t)t.aux * P);
     for (int m0 = mb; m0 < me; m0 += Pt) {
         // modes of this tile into LDS: drawn here or read from the mode arrays
-        if (tid < Pt && m0 + tid < me) {
-            const int l = m0 + tid;
-            int mx, my, mz;
-            if (SAMPLE && a.do_sample) {
-                sample_mode(tabp, S.M, (uint32_t)l, S.seed, sample_step, mx, my, mz);
-                if (t.aux == 0) {
+        if (!(drawn && m0 == mb)) {
+            if (tid < Pt && m0 + tid < me) {
+                const int l = m0 + tid;
+                int mx, my, mz;
+                if (SAMPLE && a.do_sample) {
+                    sample_mode(tabp, S.M, (uint32_t)l, S.seed, sample_step, mx, my, mz);
+                    if (t.aux == 0) {
+                        const int o = S.moff + l;
+                        a.modes[o] = mx;
+                        a.modes[a.mcap + o] = my;
+                        a.modes[2 * a.mcap + o] = mz;
+                        double w = S.S;
+                        asm volatile("" : "+v"(w));   // keeps the division here
+                        a.mode_w[o] = w / (double)P;
+                    }
+                } else {
                     const int o = S.moff + l;
-                    a.modes[o] = mx;
-                    a.modes[a.mcap + o] = my;
-                    a.modes[2 * a.mcap + o] = mz;
-                    a.mode_w[o] = S.S / (double)P;
+                    mx = a.modes[o];
+                    my = a.modes[a.mcap + o];
+                    mz = a.modes[2 * a.mcap + o];
                 }
-            } else {
-                const int o = S.moff + l;
-                mx = a.modes[o];
-                my = a.modes[a.mcap + o];
-                mz = a.modes[2 * a.mcap + o];
+                smode[tid] = mx;
+                smode[BS + tid] = my;
+                smode[2 * BS + tid] = mz;
             }
-            smode[tid] = mx;
-            smode[BS + tid] = my;
-            smode[2 * BS + tid] = mz;
+            __syncthreads();
         }
-        __syncthreads();
-        const int lt = tid % Pl, g = tid / Pl;
+        const int g = small_div(tid, Pl), lt = tid - g * Pl;
         const int l = m0 + lt;
         const bool act = g < G && l < me;
         double C = 0.0, Sn = 0.0, C2 = 0.0, Sn2 = 0.0;
@@ -432,17 +455,29 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
                 }
             }
         }
-        for (int h = 0; h <= (two ? 1 : 0); ++h) {
-            if (h) __syncthreads();
-            red[tid] = h ? make_double2(C2, Sn2) : make_double2(C, Sn);
+        // sums over the groups; the second modes' follow the first ones', over
+        // the records as well (32 (chunk + 256) bytes, chunk >= 256) once no mode
+        // tile needs them any more, else in a round of their own
+        const bool over = two && m0 + Pt >= me;
+        double2 *rd = red;
+        if (over) {
             __syncthreads();
-            const int lh = l + h * Pl;
-            if (tid < Pl && lh < m0 + Pt && lh < me) {
+            rd = reinterpret_cast<double2 *>(smem);
+            rd[BS + tid] = make_double2(C2, Sn2);
+        }
+        for (int h = 0; h <= (two && !over ? 1 : 0); ++h) {
+            if (h) __syncthreads();
+            rd[tid] = h ? make_double2(C2, Sn2) : make_double2(C, Sn);
+            __syncthreads();
+            const int h1 = over && tid >= Pl ? 1 : h, k = tid - (over && tid >= Pl ? Pl : 0);
+            const int lh = m0 + k + h1 * Pl;
+            if (k < Pl && lh < m0 + Pt && lh < me) {
+                const double2 *v = rd + (over && h1 ? BS : 0) + k;
                 double c = 0.0, s = 0.0;
+#pragma unroll 8
                 for (int gg = 0; gg < G; ++gg) {
-                    const double2 v = red[gg * Pl + lt];
-                    c += v.x;
-                    s += v.y;
+                    c += v[gg * Pl].x;
+                    s += v[gg * Pl].y;
                 }
                 prow[2 * lh] = c;
                 prow[2 * lh + 1] = s;

@@ -336,7 +336,7 @@ __device__ __forceinline__ void finish_particle(const RealArgs<T> &a, const SysD
     a.F[2 * a.ntot + i] = fz;
     if (a.vel && i - S.off >= S.n_fixed) {
         // the same rounding as the deferred kick of the integrator
-        const double h = 0.5 * step_dt(S, a.kick_step) / S.mass;
+        const double h = S.anneal > 0.0 ? 0.5 * step_dt(S, a.kick_step) / S.mass : S.h_m;
         a.vel[i] = (T)fma(h, (double)fx, (double)a.vel[i]);
         a.vel[a.ntot + i] = (T)fma(h, (double)fy, (double)a.vel[a.ntot + i]);
         a.vel[2 * a.ntot + i] = (T)fma(h, (double)fz, (double)a.vel[2 * a.ntot + i]);

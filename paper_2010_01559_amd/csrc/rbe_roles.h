@@ -268,7 +268,7 @@ __device__ void mid_final(const MidArgs<KM> &a, int blk)
     const int lw = a.final_lw, W = 1 << lw;
     const int gm = (blk << (4 - lw)) + (wave >> lw);
     const int q = wave & (W - 1);
-    const int r = gm / a.max_p, l = gm % a.max_p;
+    const int r = a.single_p ? (gm >= a.max_p ? a.R : 0) : gm / a.max_p, l = gm - r * a.max_p;
     // a single system's mode and tile counts come with the launch, so that
     // the partial loads do not wait for the system constants and offsets
     bool ok = r < a.R;
