@@ -671,4 +671,56 @@ __device__ __forceinline__ double lane_xor_sum(double v)
     }
 }
 
+// v of another lane of its row of 16 (CTRL: a data-parallel permutation).
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v)
+{
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false));
+}
+
+template <int XOR>
+__device__ __forceinline__ float lane_xor_sum(float v)
+{
+    uint32_t a, b;
+    lane_pair<XOR>(__float_as_uint(v), a, b);
+    return __uint_as_float(a) + __uint_as_float(b);
+}
+
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E;                       // quad_perm 1,0,3,2 and 2,3,0,1
+constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128, kDppHalfMirror = 0x141;
+
+// Sum over the wave, the same on every lane: lanes l and l ^ 32, then ^ 16, 8, 4,
+// 2, 1, without LDS round trips (six of them took 0.3 us where a wave has
+// nothing else to do).  Once the sums over ^ 8 repeat every eight lanes, a rotation
+// by four within the row is ^ 4.
+template <typename V>
+__device__ __forceinline__ V wave_sum(V v)
+{
+    v = lane_xor_sum<16>(lane_xor_sum<32>(v));
+    v += dpp_move<kDppRor8>(v);
+    v += dpp_move<kDppRor4>(v);
+    v += dpp_move<kDppXor2>(v);
+    return v + dpp_move<kDppXor1>(v);
+}
+
+// Sum over aligned groups of W lanes: ^ 1, ^ 2, ^ 4, ... (a half row mirrored is ^ 4
+// once the lanes of a quad agree).
+template <int W>
+__device__ __forceinline__ double group_sum(double v)
+{
+    if constexpr (W >= 2) v += dpp_move<kDppXor1>(v);
+    if constexpr (W >= 4) v += dpp_move<kDppXor2>(v);
+    if constexpr (W >= 8) v += dpp_move<kDppHalfMirror>(v);
+    if constexpr (W >= 16) v += dpp_move<kDppRor8>(v);
+    if constexpr (W >= 32) v = lane_xor_sum<16>(v);
+    return v;
+}
+
 }  // namespace rbe

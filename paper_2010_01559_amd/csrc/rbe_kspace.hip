@@ -927,13 +927,10 @@ __global__ __launch_bounds__(1024) void k_vjp_final(VjpFinalArgs<KM, KV> a)
                 bv += y[u].y;
             }
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        c += __shfl_down(c, off, 64);
-        s += __shfl_down(s, off, 64);
-        av += __shfl_down(av, off, 64);
-        bv += __shfl_down(bv, off, 64);
-    }
+    c = wave_sum(c);
+    s = wave_sum(s);
+    av = wave_sum(av);
+    bv = wave_sum(bv);
     if (lane != 0) return;
     const double f = force_coefficient(in);
     make_kmode<KM>(in, f, c, s, a.rho, a.km);

@@ -454,14 +454,6 @@ __device__ __forceinline__ void wave_lds_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <typename V>
-__device__ __forceinline__ V wave_sum(V v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // Fourier force of one particle (record pa) with a mode per lane, summed over
 // the wave.
 template <typename T>
@@ -1090,12 +1082,9 @@ __device__ __forceinline__ void list_pairs(const RealArgs<T> &a, const ListArgs 
         }
     }
     if constexpr (sizeof(T) == 4) range_check(fx, fy, fz, a.flag);
-#pragma unroll
-    for (int o = 1; o < LPP; o <<= 1) {
-        fx += __shfl_xor(fx, o, 64);
-        fy += __shfl_xor(fy, o, 64);
-        fz += __shfl_xor(fz, o, 64);
-    }
+    fx = group_sum<LPP>(fx);
+    fy = group_sum<LPP>(fy);
+    fz = group_sum<LPP>(fz);
 }
 
 // Last step of a list particle (its first lane): scale of the real-space sum,

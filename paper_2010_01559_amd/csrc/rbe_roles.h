@@ -304,24 +304,21 @@ __device__ void mid_final(const MidArgs<KM> &a, int blk)
                     s += v[u].y;
                 }
         }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-            c += __shfl_down(c, off, 64);
-            s += __shfl_down(s, off, 64);
-        }
+        c = wave_sum(c);
+        s = wave_sum(s);
     }
-    // in every lane, without a branch: its divisions run under the shuffles
+    // in every lane, without a branch: its divisions run under the sums
     const double f = force_coefficient(in);
-    if (lane == 0) q_sum[wave] = make_double2(c, s);
-    __syncthreads();
-    if (ok && q == 0 && lane == 0) {
-        double cc = 0.0, ss = 0.0;
+    if (W > 1) {
+        if (lane == 0) q_sum[wave] = make_double2(c, s);
+        __syncthreads();
+        c = s = 0.0;
         for (int k = 0; k < W; ++k) {
-            cc += q_sum[wave + k].x;
-            ss += q_sum[wave + k].y;
+            c += q_sum[min(wave + k, 15)].x;
+            s += q_sum[min(wave + k, 15)].y;
         }
-        make_kmode<KM>(in, f, cc, ss, a.rho, a.km);
     }
+    if (ok && q == 0 && lane == 0) make_kmode<KM>(in, f, c, s, a.rho, a.km);
 }
 
 // Exclusive scan of one system's cell counts with NW waves (64 NW threads).
