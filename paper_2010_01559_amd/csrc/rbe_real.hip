@@ -367,9 +367,8 @@ __device__ __forceinline__ SysDev pair_consts<double>(const SysDev &S)
 
 // ---------------------------------------------------------------------------
 // Fourier force fused into the real-space pass of a step (eq. 3.6).  Wave w of
-// the block sums the modes of quarter w, [w P/4, (w+1) P/4), in mode order for
-// every particle of the tile (64 per pass, one per lane; the mode constants are
-// wave-uniform), and leaves the partial sum in LDS; the particle's lane adds
+// the block sums the modes of quarter w, [w P/4, (w+1) P/4), for every particle of
+// the tile and leaves the partial sum in LDS; the particle's lane adds
 // the quarters in a fixed order when it finishes the particle.  The decomposition
 // is the same on every tile shape, so the Fourier force of a particle does not
 // depend on the real-space path.
@@ -390,7 +389,49 @@ struct KMT<double> {
 template <typename T>
 using Four = T (*)[FT_MAX][3];
 
-template <typename T>
+// Terms of the modes [l0, l1) of one lane's particle, as four sums f_j over the modes
+// l0 + j, l0 + j + 4, ..., added as (f_0 + f_1) + (f_2 + f_3).  SUBS lanes of the
+// wave share a particle (64 / SUBS apart), each with 4 / SUBS of the sums, so that
+// small tiles, whose particles would leave lanes idle, walk a half or a quarter of the
+// modes each (step at N = 3000 with 16 particles per tile 18.6 -> 17.5 us, N = 10001 in
+// double precision with 32 30.3 -> 29.6).  With one lane per particle the mode constants
+// are wave-uniform (scalar loads).
+template <int SUBS, typename KM, typename Term>
+__device__ __forceinline__ void fourier_subs(const KM *kk0, int l0, int l1, decltype(KM::m[0] + 0) f[3], Term &&term)
+{
+    using T = decltype(KM::m[0] + 0);
+    constexpr int NS = 4 / SUBS;
+    T s[NS][3];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) s[j][0] = s[j][1] = s[j][2] = 0;
+    if constexpr (SUBS == 1) {
+        const auto kk = uniform_modes(kk0);
+        l0 = __builtin_amdgcn_readfirstlane(l0);
+        l1 = __builtin_amdgcn_readfirstlane(l1);
+        int l = l0;
+        for (; l + 4 <= l1; l += 4)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) term(load_mode(kk, l + j), s[j]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            if (l + j < l1) term(load_mode(kk, l + j), s[j]);
+    } else {
+        const int g = ((int)threadIdx.x & 63) / (64 / SUBS);
+#pragma unroll 4
+        for (int l = l0 + NS * g; l < l1; l += 4)
+#pragma unroll
+            for (int j = 0; j < NS; ++j)
+                if (l + j < l1) term(kk0[l + j], s[j]);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        if constexpr (SUBS == 1) f[d] = (s[0][d] + s[1][d]) + (s[2][d] + s[3][d]);
+        if constexpr (SUBS == 2) f[d] = lane_xor_sum<32>(s[0][d] + s[1][d]);
+        if constexpr (SUBS == 4) f[d] = lane_xor_sum<32>(lane_xor_sum<16>(s[0][d]));
+    }
+}
+
+template <typename T, int SUBS>
 __device__ __forceinline__ void fourier_tile(const RealArgs<T> &a, const SysDev &S, const void *recs, int first,
                                              int count, Four<T> s4)
 {
@@ -400,21 +441,25 @@ __device__ __forceinline__ void fourier_tile(const RealArgs<T> &a, const SysDev 
     const int l0 = (S.p * wave) / 4, l1 = (S.p * (wave + 1)) / 4;
     const KM *kk = reinterpret_cast<const KM *>(a.km) + S.moff;
     const Rec *rp = reinterpret_cast<const Rec *>(recs) + first;
-    for (int p0 = 0; p0 < count; p0 += 64) {
-        const int p = p0 + lane;
+    constexpr int PART = 64 / SUBS;
+    for (int p0 = 0; p0 < count; p0 += PART) {
+        const int p = p0 + (lane & (PART - 1));
         T f[3] = {0, 0, 0};
-        if (p < count) {
-            const Rec r = rp[p];
-            if constexpr (sizeof(T) == 4) {
-                float h[3], lo[3];
-                split_fix(r.x, S, h[0], lo[0]);
-                split_fix(r.y, S, h[1], lo[1]);
-                split_fix(r.z, S, h[2], lo[2]);
-                fourier_range(kk, l0, l1, S.polar, h, lo, f);
-            } else {
-                const double s3[3] = {r.x, r.y, r.z};
-                fourier_range(kk, l0, l1, s3, f);
-            }
+        const Rec r = rp[min(p, count - 1)];
+        if constexpr (sizeof(T) == 4) {
+            float h[3], lo[3];
+            split_fix(r.x, S, h[0], lo[0]);
+            split_fix(r.y, S, h[1], lo[1]);
+            split_fix(r.z, S, h[2], lo[2]);
+            if (S.polar)
+                fourier_subs<SUBS>(kk, l0, l1, f, [&](const KM &k, T g[3]) { fourier_term<true>(k, h, lo, g); });
+            else
+                fourier_subs<SUBS>(kk, l0, l1, f, [&](const KM &k, T g[3]) { fourier_term<false>(k, h, lo, g); });
+        } else {
+            const double s3[3] = {r.x, r.y, r.z};
+            fourier_subs<SUBS>(kk, l0, l1, f, [&](const KM &k, T g[3]) { fourier_term(k, s3, g); });
+        }
+        if (p < count && lane < PART) {
             s4[wave][p][0] = f[0];
             s4[wave][p][1] = f[1];
             s4[wave][p][2] = f[2];
@@ -1135,6 +1180,7 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 7 : 1) void k_real
         PairQueue<T, DIAM> pairs;
     } lds;
     auto &s4 = lds.s4;
+    constexpr int SUBS = LPP <= 4 ? 1 : (LPP == 8 ? 2 : 4);   // list tiles of 256 / LPP particles
     // both flags are read before anything is stored, so that neither read
     // waits for the other
     const int poison = *la.ls.poison;
@@ -1173,9 +1219,9 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 7 : 1) void k_real
         // loads at the same time
         if (wave_slot() & 1) {
             list_pairs<T, LPP, DIAM>(a, la, t, S, h, fx, fy, fz);
-            fourier_tile<T>(a, S, a.sorted, S.off + t.start, t.count, s4);
+            fourier_tile<T, SUBS>(a, S, a.sorted, S.off + t.start, t.count, s4);
         } else {
-            fourier_tile<T>(a, S, a.sorted, S.off + t.start, t.count, s4);
+            fourier_tile<T, SUBS>(a, S, a.sorted, S.off + t.start, t.count, s4);
             list_pairs<T, LPP, DIAM>(a, la, t, S, h, fx, fy, fz);
         }
         __syncthreads();
@@ -1195,7 +1241,7 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 7 : 1) void k_real
         c = cells_body<T, 16, false, true, DIAM>(a, &la, t.sys, S.off + t.start + 16 * wave, min(16, t.count - 16 * wave), S,
                                                  nullptr, lds.cells[wave], pa);
     __syncthreads();
-    fourier_tile<T>(a, S, a.sorted, S.off + t.start, t.count, s4);
+    fourier_tile<T, 1>(a, S, a.sorted, S.off + t.start, t.count, s4);
     __syncthreads();
     if (c.first) {
         add_fourier<T>(s4, 16 * wave + (int)(threadIdx.x & 15), (T)pa.q, c.fx, c.fy, c.fz);
