@@ -628,13 +628,18 @@ void build_list_tiles(rbe_ctx *c, int lpp, std::vector<Tile> &out)
 // default of 4 becomes 8, 16 or 32 while that would leave compute units without a
 // block and the lists are longer than the lanes: the launch then lasts as long as
 // one lane's chain of list rounds (N = 3101, lists of 217: 36 us with 4 lanes,
-// 12 us with 32).  The sums over a particle's list are exact in single
+// 12 us with 32).  The chains of double precision are ten times as long and
+// worth more lanes a little beyond, up to 640 blocks (N = 10001 with 16 instead of 8
+// 29.6 -> 28.6 us a step, N = 20000 with 8 instead of 4 36.0 -> 34.5; N = 14000 with 16, 875
+// blocks, 30.2 -> 32.0; single precision at N = 18000 with 8, 562 blocks, 20.8 -> 22.0).
+// The sums over a particle's list are exact in single
 // precision, so the lanes do not change them.
 int list_lanes(const rbe_ctx *c)
 {
     int lanes = c->cfg.real_split;
     if (lanes != 4) return lanes;
-    while (lanes < 32 && c->ntot * lanes / 256 < 256 && 2 * lanes <= c->mean_list) lanes *= 2;
+    const int64_t room = c->prec == RBE_FP64 ? 321 : 256;
+    while (lanes < 32 && c->ntot * lanes / 256 < room && 2 * lanes <= c->mean_list) lanes *= 2;
     return lanes;
 }
 
