@@ -1542,10 +1542,12 @@ static rbe_status list_step(rbe_ctx *c, void *pos, void *vel, const void *q, voi
     rq.kick = !first && !andersen;
     RUN(c, K_STAGE, launch_stage(c->cfg, c->w, rq));
     const bool draw_next = !c->any_mh && !c->fixed && !last;
-    // (an all-pairs context has nothing to rebuild)
-    RUN(c, K_MID, launch_mid(c->cfg, c->w, 1, 0, nullptr, c->cfg.list_on ? ls.rebuild : nullptr, ls.rebuild_next,
+    // an all-pairs context has nothing to rebuild, and a small one no totals launch
+    const PairsStep ps{totals_in_force(c->cfg), draw_next ? 1 : 0, ks + 1};
+    if (!ps.totals)
+        RUN(c, K_MID, launch_mid(c->cfg, c->w, 1, 0, nullptr, c->cfg.list_on ? ls.rebuild : nullptr, ls.rebuild_next,
                              draw_next ? 1 : 0, ks + 1, &ls));
-    RUN(c, K_REAL, launch_real_step(c->cfg, c->w, ls, force, (andersen || !last) ? nullptr : vel, s));
+    RUN(c, K_REAL, launch_real_step(c->cfg, c->w, ls, ps, force, (andersen || !last) ? nullptr : vel, s));
     c->list_valid = true;
     ++c->list_gen;
     if (draw_next) {

@@ -320,8 +320,15 @@ hipError_t launch_scatter(const LaunchCfg &c, const Workspace &w, const void *gF
 hipError_t launch_set_step(const LaunchCfg &c, const Workspace &w, uint64_t step);
 hipError_t launch_pair_hist(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, double r_max,
                             int nbins, int64_t *counts);
-hipError_t launch_real_step(const LaunchCfg &c, const Workspace &w, const ListStep &ls, void *force, void *vel_kick,
-                            uint64_t kick_step = 0);
+// What the force launch of an all-pairs step does besides the forces.
+struct PairsStep {
+    int totals = 0;           // forms the structure-factor totals (see totals_in_force)
+    int draw_next = 0;        // and draws the modes of step draw_step
+    uint64_t draw_step = 0;
+};
+int totals_in_force(const LaunchCfg &c);
+hipError_t launch_real_step(const LaunchCfg &c, const Workspace &w, const ListStep &ls, const PairsStep &ps, void *force,
+                            void *vel_kick, uint64_t kick_step = 0);
 hipError_t launch_real(const LaunchCfg &c, const Workspace &w, void *force, int accumulate, void *vel_kick,
                        uint64_t kick_step = 0);
 hipError_t launch_energy(const LaunchCfg &c, const Workspace &w, const void *q, const void *vel);

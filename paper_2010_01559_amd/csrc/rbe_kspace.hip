@@ -1178,21 +1178,10 @@ static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_fi
                                uint64_t sample_step, const ListStep *ls)
 {
     MidArgs<KM> a;
-    a.sys = w.sys;
-    a.R = c.R;
-    a.max_p = c.max_p;
+    totals_args(a, c, w, sample_next, sample_step, ls);
     a.final_lw = final_waves_log2(c.max_sys_rho_tiles);
     const int final_modes = 16 >> a.final_lw;   // modes per totals block
     a.n_final_blocks = do_final ? (c.R * c.max_p + final_modes - 1) / final_modes : 0;
-    a.single_p = c.R == 1 ? c.max_p : 0;
-    a.single_nt = c.n_rho_tiles;
-    a.partial = w.partial;
-    a.part_off = w.partial_off;
-    a.modes = w.modes;
-    a.mode_w = w.mode_w;
-    a.mcap = c.mcap;
-    a.rho = w.rho;
-    a.km = (KM *)w.kmode;
     a.count = w.cell_count;
     a.start = w.cell_start;
     a.do_scan = do_scan;
@@ -1204,14 +1193,7 @@ static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_fi
     a.packed = w.packed;
     a.cellid = w.cellid;
     a.rank = w.rank;
-    a.n_sample_blocks = sample_next ? c.R : 0;
-    a.sample_step = sample_step;
-    a.cdf = w.cdf;
-    a.table_lds = sample_next && c.max_table <= 6144 ? 1 : 0;
-    a.modes_next = w.modes_alt;
-    a.mode_w_next = w.mode_w_alt;
     a.clear_flag = clear_flag;
-    a.step_base = ls ? ls->step_base : nullptr;
     // a list step: the gated rebuild runs in this launch
     a.reb = ls && bin_gate ? 1 : 0;
     a.n_reb_scatter = a.reb ? std::min(kRebBlocks, (c.n_part_tiles + 3) / 4) : 0;

@@ -499,29 +499,60 @@ __device__ __forceinline__ void wave_lds_order()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Tiles of a system whose totals the force launch of an all-pairs step forms by
+// itself, and modes: see totals_in_force().
+constexpr int kTotalTiles = 8, kTotalModes = 128;
+
 // Fourier force of one particle (record pa) with a mode per lane, summed over
-// the wave.
-template <typename T>
-__device__ __forceinline__ void fourier_lanes(const RealArgs<T> &a, const SysDev &S, const typename RBT<T>::Rec &pa,
-                                              T g[3])
+// the wave.  TOTALS: the lane first adds its modes' tile partials (in the order of the
+// totals launch) and forms their constants; particle 0 stores them.
+template <typename T, bool TOTALS>
+__device__ __forceinline__ void fourier_lanes(const RealArgs<T> &a, const MidArgs<typename KMT<T>::type> *m, int sys,
+                                              int il, const SysDev &S, const typename RBT<T>::Rec &pa, T g[3])
 {
     using KM = typename KMT<T>::type;
     const KM *kk = reinterpret_cast<const KM *>(a.km) + S.moff;
     g[0] = g[1] = g[2] = 0;
+    float h[3], lo[3];
     if constexpr (sizeof(T) == 4) {
-        float h[3], lo[3];
         split_fix(pa.x, S, h[0], lo[0]);
         split_fix(pa.y, S, h[1], lo[1]);
         split_fix(pa.z, S, h[2], lo[2]);
-        for (int l = threadIdx.x & 63; l < S.p; l += 64) {
-            if (S.polar)
-                fourier_term<true>(kk[l], h, lo, g);
-            else
-                fourier_term<false>(kk[l], h, lo, g);
+    }
+    for (int l = threadIdx.x & 63; l < S.p; l += 64) {
+        KM k;
+        if constexpr (TOTALS) {
+            const KModeIn in = kmode_in(S, S.moff, l, m->modes, m->mode_w, m->mcap);
+            const int nt = m->single_p ? m->single_nt : m->part_off[m->R + sys];
+            const double2 *p = reinterpret_cast<const double2 *>(m->partial) + (m->single_p ? 0 : m->part_off[sys]) + l;
+            double2 v[kTotalTiles];
+#pragma unroll
+            for (int t = 0; t < kTotalTiles; ++t) v[t] = t < nt ? p[(int64_t)t * S.p] : make_double2(0.0, 0.0);
+            const double f = force_coefficient(in);
+#pragma unroll
+            for (int w = kTotalTiles / 2; w > 0; w >>= 1)
+                for (int t = 0; t < w; ++t) {
+                    v[t].x += v[t + w].x;
+                    v[t].y += v[t + w].y;
+                }
+            k = kmode_of<KM>(in, f, v[0].x, v[0].y);
+            if (il == 0) {
+                m->rho[2 * in.o] = v[0].x;
+                m->rho[2 * in.o + 1] = v[0].y;
+                m->km[in.o] = k;
+            }
+        } else {
+            k = kk[l];
         }
-    } else {
-        const double s3[3] = {pa.x, pa.y, pa.z};
-        for (int l = threadIdx.x & 63; l < S.p; l += 64) fourier_term(kk[l], s3, g);
+        if constexpr (sizeof(T) == 4) {
+            if (S.polar)
+                fourier_term<true>(k, h, lo, g);
+            else
+                fourier_term<false>(k, h, lo, g);
+        } else {
+            const double s3[3] = {pa.x, pa.y, pa.z};
+            fourier_term(k, s3, g);
+        }
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) g[d] = wave_sum(g[d]);
@@ -538,9 +569,10 @@ __device__ __forceinline__ void fourier_lanes(const RealArgs<T> &a, const SysDev
 // of the 300 ions 105 -> 30 us).  FOURIER adds the Fourier force (a
 // mode per lane).  DIAM compiles the per-particle-diameter LJ (only launches
 // of contexts with diameters).
-template <typename T, bool ENERGY, bool DIAM, bool FOURIER>
+template <typename T, bool ENERGY, bool DIAM, bool FOURIER, bool TOTALS = false>
 __device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, int il, const SysDev &S, double *ev,
-                                              PairQueue<T, DIAM> &qu)
+                                              PairQueue<T, DIAM> &qu, int sys = 0,
+                                              const MidArgs<typename KMT<T>::type> *m = nullptr)
 {
     using Rec = typename RBT<T>::Rec;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -567,10 +599,19 @@ __device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, int il, cons
         fz += qterm(ph * dz);
         if constexpr (ENERGY) ev[2] += 0.5 * (double)(phi * r2);
     };
+    // a round's records are loaded a round ahead, the first ones under the Fourier force
+    Rec pn[kApUnroll];
+#pragma unroll
+    for (int u = 0; u < kApUnroll; ++u) pn[u] = pk[min(64 * u + lane, n - 1)];
+    T g[3];
+    if constexpr (FOURIER) fourier_lanes<T, TOTALS>(a, m, sys, il, S, pa, g);
     for (int j0 = 0; j0 < n; j0 += 64 * kApUnroll) {
         Rec pb[kApUnroll];
 #pragma unroll
-        for (int u = 0; u < kApUnroll; ++u) pb[u] = pk[min(j0 + 64 * u + lane, n - 1)];
+        for (int u = 0; u < kApUnroll; ++u) {
+            pb[u] = pn[u];
+            pn[u] = pk[min(j0 + 64 * (kApUnroll + u) + lane, n - 1)];
+        }
 #pragma unroll
         for (int u = 0; u < kApUnroll; ++u) {
             const int j = j0 + 64 * u + lane;
@@ -600,8 +641,6 @@ __device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, int il, cons
     fx = wave_sum(fx);
     fy = wave_sum(fy);
     fz = wave_sum(fz);
-    T g[3];
-    if constexpr (FOURIER) fourier_lanes<T>(a, S, pa, g);
     if (lane != 0) return;
     if constexpr (sizeof(T) == 4) range_check(fx, fy, fz, a.flag);
     fx *= qscale<T>();
@@ -1251,12 +1290,20 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 7 : 1) void k_real
 
 // Force pass of a time step of a context that has only one-cell systems:
 // Fourier and all-pairs real-space force in one launch (there is no list and
-// nothing to rebuild).
-template <typename T, bool DIAM>
-__global__ __launch_bounds__(RL_BS) void k_pairs_step(RealArgs<T> a, int single_n, int single_p)
+// nothing to rebuild).  With TOTALS it also forms the structure-factor totals, every wave
+// for itself, and blocks behind the particles' draw the next step's modes: a step is
+// then two launches (50 steps and an energy of the 300-ion electrolyte 849 -> 690 us).
+template <typename T, bool DIAM, bool TOTALS>
+__global__ __launch_bounds__(RL_BS) void k_pairs_step(RealArgs<T> a, int n_blocks, int single_n, int single_p,
+                                                      MidArgs<typename KMT<T>::type> m)
 {
+    extern __shared__ double pairs_tab[];
     __shared__ PairQueue<T, DIAM> qu;
     const int b = (int)blockIdx.x;
+    if (TOTALS && b >= n_blocks) {
+        mid_sample(m, b - n_blocks, m.table_lds ? pairs_tab : nullptr);
+        return;
+    }
     // a single system's tile, offsets and mode count come with the launch
     const Tile t = single_n ? Tile{0, b * RL_ALLPAIRS, min(RL_ALLPAIRS, single_n - b * RL_ALLPAIRS), 1} : a.tiles[b];
     SysDev S = a.sys[t.sys];
@@ -1267,7 +1314,7 @@ __global__ __launch_bounds__(RL_BS) void k_pairs_step(RealArgs<T> a, int single_
         S.p = single_p;
     }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (wave < t.count) allpairs_body<T, false, DIAM, true>(a, t.start + wave, S, nullptr, qu);
+    if (wave < t.count) allpairs_body<T, false, DIAM, true, TOTALS>(a, t.start + wave, S, nullptr, qu, t.sys, &m);
 }
 
 // Stand-alone scatter into cell order (force and energy calls; a time step
@@ -1513,11 +1560,19 @@ static void real_step_launch(const LaunchCfg &c, const RealArgs<T> &a, const Lis
 }
 
 template <typename T>
-static void real_step_dispatch(const LaunchCfg &c, const RealArgs<T> &a, const ListArgs &la)
+static void real_step_dispatch(const LaunchCfg &c, const Workspace &w, const ListStep &ls, const PairsStep &ps,
+                               const RealArgs<T> &a, const ListArgs &la)
 {
     if (c.all_pairs) {
-        launch_k(a.diam ? k_pairs_step<T, true> : k_pairs_step<T, false>, c.n_real_tiles, RL_BS, 0, c.stream, a,
-                 la.single_n, la.single_p);
+        MidArgs<typename KMT<T>::type> m{};
+        totals_args(m, c, w, ps.totals && ps.draw_next, ps.draw_step, &ls);
+        // with the partner queues (28 KB at most) the table stays below 64 KB of LDS
+        m.table_lds = m.table_lds && c.max_table <= 4096;
+        const size_t sm = m.table_lds ? sizeof(double) * c.max_table : 0;
+        const auto kernel = ps.totals ? (a.diam ? k_pairs_step<T, true, true> : k_pairs_step<T, false, true>)
+                                      : (a.diam ? k_pairs_step<T, true, false> : k_pairs_step<T, false, false>);
+        launch_k(kernel, c.n_real_tiles + m.n_sample_blocks, RL_BS, sm, c.stream, a, c.n_real_tiles, la.single_n,
+                 la.single_p, m);
         return;
     }
     switch (c.list_lanes) {
@@ -1542,8 +1597,15 @@ static void real_step_dispatch(const LaunchCfg &c, const RealArgs<T> &a, const L
     }
 }
 
-hipError_t launch_real_step(const LaunchCfg &c, const Workspace &w, const ListStep &ls, void *force, void *vel_kick,
-                            uint64_t kick_step)
+// An all-pairs step forms its totals in the force launch while every wave can load
+// a mode's partials at once and has at most two modes per lane.
+int totals_in_force(const LaunchCfg &c)
+{
+    return c.all_pairs && c.max_sys_rho_tiles <= kTotalTiles && c.max_p <= kTotalModes;
+}
+
+hipError_t launch_real_step(const LaunchCfg &c, const Workspace &w, const ListStep &ls, const PairsStep &ps, void *force,
+                            void *vel_kick, uint64_t kick_step)
 {
     ListArgs la;
     la.ls = ls;
@@ -1558,9 +1620,9 @@ hipError_t launch_real_step(const LaunchCfg &c, const Workspace &w, const ListSt
     la.single_n = c.R == 1 ? (int)c.ntot : 0;
     la.single_p = c.R == 1 ? c.max_p : 0;
     if (c.prec == RBE_FP64)
-        real_step_dispatch<double>(c, real_args<double>(c, w, force, 0, vel_kick, nullptr, kick_step), la);
+        real_step_dispatch<double>(c, w, ls, ps, real_args<double>(c, w, force, 0, vel_kick, nullptr, kick_step), la);
     else
-        real_step_dispatch<float>(c, real_args<float>(c, w, force, 0, vel_kick, nullptr, kick_step), la);
+        real_step_dispatch<float>(c, w, ls, ps, real_args<float>(c, w, force, 0, vel_kick, nullptr, kick_step), la);
     return hipGetLastError();
 }
 

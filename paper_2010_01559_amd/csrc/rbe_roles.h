@@ -92,14 +92,11 @@ __device__ __forceinline__ double force_coefficient(const KModeIn &in)
     return in.coulomb * in.w * 2.0 / (in.L * in.L * m2);
 }
 
-// Structure factor totals and force constants of mode in.o, f its
+// Force constants of mode in.o with structure factor c + i s, f its
 // force_coefficient().
 template <typename KM>
-__device__ __forceinline__ void make_kmode(const KModeIn &in, double f, double c, double s, double *rho, KM *km)
+__device__ __forceinline__ KM kmode_of(const KModeIn &in, double f, double c, double s)
 {
-    const int o = in.o;
-    rho[2 * o] = c;
-    rho[2 * o + 1] = s;
     const double mx = in.mx, my = in.my, mz = in.mz;
     KM k;
     if constexpr (sizeof(KM) == sizeof(KModeF)) {
@@ -120,7 +117,16 @@ __device__ __forceinline__ void make_kmode(const KModeIn &in, double f, double c
     k.a[0] = f * mx;
     k.a[1] = f * my;
     k.a[2] = f * mz;
-    km[o] = k;
+    return k;
+}
+
+// Structure factor totals and force constants of mode in.o, stored.
+template <typename KM>
+__device__ __forceinline__ void make_kmode(const KModeIn &in, double f, double c, double s, double *rho, KM *km)
+{
+    rho[2 * in.o] = c;
+    rho[2 * in.o + 1] = s;
+    km[in.o] = kmode_of<KM>(in, f, c, s);
 }
 
 // Gated list rebuild: binning blocks, then scan blocks, then scatter
@@ -614,6 +620,32 @@ __device__ void mid_sample(const MidArgs<KM> &a, int b, double *tab)
         a.modes_next[2 * a.mcap + o] = mz;
         a.mode_w_next[o] = S.S / (double)S.p;
     }
+}
+
+// Arguments of the totals and of the draw of the next step's modes.
+template <typename KM>
+inline void totals_args(MidArgs<KM> &a, const LaunchCfg &c, const Workspace &w, int sample_next, uint64_t sample_step,
+                        const ListStep *ls)
+{
+    a.sys = w.sys;
+    a.R = c.R;
+    a.max_p = c.max_p;
+    a.single_p = c.R == 1 ? c.max_p : 0;
+    a.single_nt = c.n_rho_tiles;
+    a.partial = w.partial;
+    a.part_off = w.partial_off;
+    a.modes = w.modes;
+    a.mode_w = w.mode_w;
+    a.mcap = c.mcap;
+    a.rho = w.rho;
+    a.km = (KM *)w.kmode;
+    a.n_sample_blocks = sample_next ? c.R : 0;
+    a.sample_step = sample_step;
+    a.cdf = w.cdf;
+    a.table_lds = sample_next && c.max_table <= 6144 ? 1 : 0;
+    a.modes_next = w.modes_alt;
+    a.mode_w_next = w.mode_w_alt;
+    a.step_base = ls ? ls->step_base : nullptr;
 }
 
 }  // namespace rbe
