@@ -447,7 +447,7 @@ struct rbe_ctx {
     double prof_ms[K_COUNT] = {};
     int64_t prof_n[K_COUNT] = {};
     // host staging
-    std::vector<double> epart_h;
+    double *energy_h = nullptr;    // pinned: kEnergyOut sums per system, then the error word (first energy call)
     // graphs of steady-state list steps, keyed by everything their
     // kernel arguments were taken from
     bool graphs = false;
@@ -564,6 +564,8 @@ void free_all(rbe_ctx *c)
     c->cap_stream = nullptr;
     for (void *p : c->allocs) (void)hipFree(p);
     c->allocs.clear();
+    if (c->energy_h) (void)hipHostFree(c->energy_h);
+    c->energy_h = nullptr;
 }
 
 // Structure-factor tiles for the current chunk size, their partial offsets
@@ -1064,7 +1066,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     ALLOC(w.gsorted, 4 * esz * ntot);
     ALLOC(w.modes_alt, sizeof(int32_t) * 3 * c->mcap);
     ALLOC(w.mode_w_alt, sizeof(double) * c->mcap);
-    ALLOC(w.energy_part, sizeof(double) * 8 * ((size_t)g.n_cell_tiles + R));
+    ALLOC(w.energy_part, sizeof(double) * 8 * (size_t)g.n_cell_tiles);
     ALLOC(w.flag, sizeof(int32_t) * 4);
     ALLOC(w.lflag, sizeof(int32_t) * 8);
     ALLOC(w.step_base, sizeof(uint64_t));
@@ -1086,7 +1088,6 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         ALLOC(w.nnb, sizeof(int32_t) * nlist);
     }
 #undef ALLOC
-    c->epart_h.resize(8 * (size_t)R);
 
     auto up = [&](void *dst, const void *src, size_t bytes) -> bool {
         return hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice) == hipSuccess;
@@ -1444,7 +1445,8 @@ static rbe_status materialize_sample(rbe_ctx *c)
     return RBE_OK;
 }
 
-static rbe_status kspace_impl(rbe_ctx *c, const void *pos, const void *q, void *force, int accumulate)
+static rbe_status kspace_impl(rbe_ctx *c, const void *pos, const void *q, void *force, int accumulate,
+                              bool *cells = nullptr)
 {
     if (c->cfg.cols.ncols) {
         RUN(c, K_STAGE, launch_col_rho(c->cfg, c->w, pos, q));
@@ -1471,12 +1473,18 @@ static rbe_status kspace_impl(rbe_ctx *c, const void *pos, const void *q, void *
             if (st != RBE_OK) return st;
         }
     }
+    // an energy call's cell list: binned and scanned by the same two launches when no
+    // mode split makes several blocks stage a chunk
+    const bool bin = cells && rq.mode_split == 1;
+    if (cells) *cells = bin;
+    rq.bin = bin ? 1 : 0;
     RUN(c, K_STAGE, launch_stage(c->cfg, c->w, rq));
     // the totals launch also draws the sample of the next step into the
     // alternate mode arrays (one block per system, beside the totals blocks)
     const bool predict = c->cur_drawn && !c->any_mh && !c->fixed &&
                          !(c->next_ready && c->next_step == c->cur_step + 1);
-    RUN(c, K_MID, launch_mid(c->cfg, c->w, 1, 0, nullptr, nullptr, nullptr, predict ? 1 : 0, c->cur_step + 1));
+    RUN(c, K_MID, launch_mid(c->cfg, c->w, 1, bin ? 1 : 0, nullptr, nullptr, nullptr, predict ? 1 : 0,
+                             c->cur_step + 1));
     if (predict) {
         c->next_ready = true;
         c->next_step = c->cur_step + 1;
@@ -1815,60 +1823,49 @@ rbe_status rbe_energy(rbe_ctx *c, const void *pos, const void *q, const void *ve
     if (!c) return RBE_ERR_INVALID;
     if (!pos || !q || !out) return set_err(c, RBE_ERR_INVALID, "pos, q and out must be non-NULL");
     if (!c->modes_valid) return set_err(c, RBE_ERR_STATE, "no active modes: call rbe_sample_k or rbe_set_k first");
-    rbe_status s = kspace_impl(c, pos, q, nullptr, 0);
+    const size_t nout = (size_t)kEnergyOut * c->R + 1;
+    if (!c->energy_h) HIPCHK(c, hipHostMalloc((void **)&c->energy_h, sizeof(double) * nout, hipHostMallocMapped));
+    void *dev = nullptr;
+    HIPCHK(c, hipHostGetDevicePointer(&dev, c->energy_h, 0));
+    bool cells = false;
+    rbe_status s = kspace_impl(c, pos, q, nullptr, 0, &cells);
     if (s != RBE_OK) return s;
-    if ((s = cells_impl(c, pos, q)) != RBE_OK) return s;
+    if (cells) {
+        c->list_valid = false;   // the cell order changes under the list
+        RUN(c, K_SCATTER, launch_scatter(c->cfg, c->w));
+    } else if ((s = cells_impl(c, pos, q)) != RBE_OK) {
+        return s;
+    }
     RUN(c, K_ENERGY, launch_energy(c->cfg, c->w, q, vel));
-    RUN(c, K_ENERGY, launch_energy_sum(c->cfg, c->w));
-    std::vector<double> rho(2 * (size_t)c->mtot), wts(c->mtot);
-    std::vector<int32_t> modes(3 * (size_t)c->mcap);
-    int32_t flag[4] = {0, 0, 0, 0};
-    HIPCHK(c, hipMemcpyAsync(c->epart_h.data(), c->w.energy_part + 8 * (size_t)c->cfg.n_cell_tiles,
-                             sizeof(double) * c->epart_h.size(),
-                             hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(rho.data(), c->w.rho, sizeof(double) * rho.size(), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(wts.data(), c->w.mode_w, sizeof(double) * wts.size(), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(modes.data(), c->w.modes, sizeof(int32_t) * modes.size(), hipMemcpyDeviceToHost,
-                             c->stream));
+    RUN(c, K_ENERGY, launch_energy_sum(c->cfg, c->w, (double *)dev));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    {
-        rbe_status es = take_device_errors(c, &flag[0]);
+    int32_t flag = (int32_t)c->energy_h[nout - 1];
+    if (flag) {
+        rbe_status es = take_device_errors(c, &flag);
         if (es != RBE_OK) return es;
     }
-    const std::vector<double> &acc = c->epart_h;
     rbe_status ret = RBE_OK;
     for (int r = 0; r < c->R; ++r) {
         const SysDev &S = c->sysh[r];
-        double ek = 0.0, wk = 0.0;
-        for (int l = 0; l < S.p; ++l) {
-            const int o = S.moff + l;
-            const double mx = modes[o], my = modes[c->mcap + o], mz = modes[2 * (size_t)c->mcap + o];
-            const double m2 = mx * mx + my * my + mz * mz;
-            const double rr = rho[2 * o] * rho[2 * o] + rho[2 * o + 1] * rho[2 * o + 1];
-            // (2 pi/(V k^2)) |rho|^2 with k = 2 pi m/L  ==  |rho|^2 / (2 pi L |m|^2)
-            const double el = wts[o] * rr / (2.0 * kPi * S.L * m2);
-            ek += el;
-            // lambda dE/dlambda under r -> lambda r, L -> lambda L at fixed alpha
-            wk += el * (2.0 * kPi * kPi * m2 / (S.alpha * S.L * S.L) - 1.0);
-        }
+        const double *acc = c->energy_h + kEnergyOut * (size_t)r;
         rbe_energy_t &e = out[r];
-        e.e_kspace = S.coulomb * ek;
-        e.virial_kspace = S.coulomb * wk;
-        e.e_self = -S.coulomb * std::sqrt(S.alpha / kPi) * acc[8 * r + 4];
-        e.e_real = acc[8 * r + 0];
-        e.e_lj = acc[8 * r + 1];
-        e.virial = acc[8 * r + 2];
-        e.e_kin = vel ? acc[8 * r + 3] : 0.0;
-        e.charge_sum = acc[8 * r + 5];
-        e.nonfinite = (flag[0] & (kFlagNonFinite | kFlagRange)) ? 1 : 0;
-        e.timeout = (flag[0] & (kFlagTimeout | kFlagBounds)) ? 1 : 0;
-        if (std::fabs(acc[8 * r + 5]) > 1e-6 * acc[8 * r + 6] && ret == RBE_OK) {
+        e.e_kspace = acc[8];
+        e.virial_kspace = acc[9];
+        e.e_self = -S.coulomb * std::sqrt(S.alpha / kPi) * acc[4];
+        e.e_real = acc[0];
+        e.e_lj = acc[1];
+        e.virial = acc[2];
+        e.e_kin = vel ? acc[3] : 0.0;
+        e.charge_sum = acc[5];
+        e.nonfinite = (flag & (kFlagNonFinite | kFlagRange)) ? 1 : 0;
+        e.timeout = (flag & (kFlagTimeout | kFlagBounds)) ? 1 : 0;
+        if (std::fabs(acc[5]) > 1e-6 * acc[6] && ret == RBE_OK) {
             ret = set_err(c, RBE_ERR_NOT_NEUTRAL,
-                          fmt("system %d is not neutral: sum q = %.6g, sum |q| = %.6g", r, acc[8 * r + 5],
-                              acc[8 * r + 6]));
+                          fmt("system %d is not neutral: sum q = %.6g, sum |q| = %.6g", r, acc[5],
+                              acc[6]));
         }
     }
-    if (flag[0]) ret = device_error_status(c, flag[0]);
+    if (flag) ret = device_error_status(c, flag);
     return ret;
 }
 

@@ -222,7 +222,7 @@ struct Workspace {
     void *gsorted;         // [Ntot][4] gradient of the forces by cell-sorted slot (adjoint of the real space)
     int32_t *modes_alt;    // the next step's modes and weights when the totals launch draws them
     double *mode_w_alt;
-    double *energy_part;   // [wave tiles][8], then [R][8] sums
+    double *energy_part;   // [wave tiles][8]
     int32_t *flag;         // [4] word 0: kFlag* error bits
     // neighbour list of rbe_step (allocated when some system uses it)
     Tile *list_tiles;      // list-pass tiles (aux 2: cell-sorted slots, 1: all pairs)
@@ -332,7 +332,8 @@ hipError_t launch_real_step(const LaunchCfg &c, const Workspace &w, const ListSt
 hipError_t launch_real(const LaunchCfg &c, const Workspace &w, void *force, int accumulate, void *vel_kick,
                        uint64_t kick_step = 0);
 hipError_t launch_energy(const LaunchCfg &c, const Workspace &w, const void *q, const void *vel);
-hipError_t launch_energy_sum(const LaunchCfg &c, const Workspace &w);
+constexpr int kEnergyOut = 10;   // sums per system that an energy call brings to the host
+hipError_t launch_energy_sum(const LaunchCfg &c, const Workspace &w, double *out);
 // Adjoint of the Fourier part: sums over the modes [l0, l1) of a single system (l1 = 0: all modes of
 // every system), their totals, and the gather; with bin, scan and scatter also the cell list.
 hipError_t launch_vjp_stage(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, const void *gF,

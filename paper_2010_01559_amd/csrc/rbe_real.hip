@@ -1043,16 +1043,40 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? (ENERGY ? 6 : 7) :
     }
 }
 
-// Sums of the wave tiles' energy partials per system, in a fixed order: a
-// block per system, eight lanes per tile and one sum each.
+// Last launch of an energy call, a block per system: the sums of the wave tiles'
+// partials in a fixed order (eight lanes per tile and one sum each), the Fourier
+// energy and its virial from the modes, and the error word, all into memory of the host
+// (kEnergyOut values per system, then the word).  With the sums over the modes on the
+// host, five copies brought their inputs over, each with a wait of its own (energy and
+// pair counts at N = 30001 553 -> 454 us, with two launches fewer).
 __global__ __launch_bounds__(1024) void k_energy_sum(const SysDev *__restrict__ sys, int R, int n_tiles,
-                                                     const double *__restrict__ part, double *__restrict__ out)
+                                                     const double *__restrict__ part, const int32_t *__restrict__ modes,
+                                                     const double *__restrict__ mode_w, int mcap,
+                                                     const double *__restrict__ rho, const int32_t *__restrict__ flag,
+                                                     double *__restrict__ out)
 {
     __shared__ double red[1024];
+    __shared__ double2 wred[16];
     const int r = blockIdx.x, tid = threadIdx.x;
+    const SysDev &S = sys[r];
+    double ek = 0.0, wk = 0.0;
+    for (int l = tid; l < S.p; l += 1024) {
+        const int o = S.moff + l;
+        const double mx = modes[o], my = modes[mcap + o], mz = modes[2 * (int64_t)mcap + o];
+        const double m2 = mx * mx + my * my + mz * mz;
+        const double rr = rho[2 * o] * rho[2 * o] + rho[2 * o + 1] * rho[2 * o + 1];
+        // (2 pi/(V k^2)) |rho|^2 with k = 2 pi m/L  ==  |rho|^2 / (2 pi L |m|^2)
+        const double el = mode_w[o] * rr / (2.0 * kPi * S.L * m2);
+        ek += el;
+        // lambda dE/dlambda under r -> lambda r, L -> lambda L at fixed alpha
+        wk += el * (2.0 * kPi * kPi * m2 / (S.alpha * S.L * S.L) - 1.0);
+    }
+    ek = wave_sum(ek);
+    wk = wave_sum(wk);
+    if ((tid & 63) == 0) wred[tid >> 6] = make_double2(ek, wk);
     const int e1 = r + 1 < R ? sys[r + 1].ctile_off : n_tiles;
     double v = 0.0;
-    int e = sys[r].ctile_off + (tid >> 3);
+    int e = S.ctile_off + (tid >> 3);
     for (; e + 3 * 128 < e1; e += 4 * 128) {
         double x[4];
 #pragma unroll
@@ -1066,7 +1090,18 @@ __global__ __launch_bounds__(1024) void k_energy_sum(const SysDev *__restrict__ 
         __syncthreads();
         if (tid < w) red[tid] += red[tid + w];
     }
-    if (tid < 8) out[8 * r + tid] = red[tid];
+    double *o = out + kEnergyOut * r;
+    if (tid < 8) o[tid] = red[tid];
+    if (tid == 8) {
+        ek = wk = 0.0;
+        for (int w = 0; w < 16; ++w) {
+            ek += wred[w].x;
+            wk += wred[w].y;
+        }
+        o[8] = S.coulomb * ek;
+        o[9] = S.coulomb * wk;
+    }
+    if (r == 0 && tid == 9) out[kEnergyOut * R] = (double)*flag;
 }
 
 // List tile: LPP lanes per cell-sorted slot, U partners per lane and round.
@@ -1635,10 +1670,10 @@ hipError_t launch_energy(const LaunchCfg &c, const Workspace &w, const void *q, 
     return hipGetLastError();
 }
 
-hipError_t launch_energy_sum(const LaunchCfg &c, const Workspace &w)
+hipError_t launch_energy_sum(const LaunchCfg &c, const Workspace &w, double *out)
 {
-    launch_k(k_energy_sum, c.R, 1024, 0, c.stream, w.sys, c.R, c.n_cell_tiles, w.energy_part,
-             w.energy_part + 8 * (int64_t)c.n_cell_tiles);
+    launch_k(k_energy_sum, c.R, 1024, 0, c.stream, w.sys, c.R, c.n_cell_tiles, w.energy_part, w.modes, w.mode_w, c.mcap,
+             w.rho, w.flag, out);
     return hipGetLastError();
 }
 
