@@ -1070,7 +1070,10 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     ALLOC(w.flag, sizeof(int32_t) * 4);
     ALLOC(w.lflag, sizeof(int32_t) * 8);
     ALLOC(w.step_base, sizeof(uint64_t));
-    if (any_diam) ALLOC(w.diam, sizeof(double) * ntot);
+    if (any_diam) {
+        ALLOC(w.diam, sizeof(double) * ntot);
+        ALLOC(w.dsorted, sizeof(double) * ntot);
+    }
     {
         // list-pass tiles: at most one per 32 slots (the 8-lane shape; more lanes
         // are taken only with fewer than 512 tiles), or the all-pairs tiles of

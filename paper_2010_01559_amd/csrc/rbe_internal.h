@@ -242,6 +242,7 @@ struct Workspace {
     int32_t *col_tile;     // ... [tiles of four columns][2] rows and offset in ...
     double *col_coef;      // ... the coefficient matrix of the force pass
     double *diam;          // [Ntot] per-particle diameters (original order), or NULL
+    double *dsorted;       // the same in cell order, written by the list rebuild
 };
 
 struct LaunchCfg {

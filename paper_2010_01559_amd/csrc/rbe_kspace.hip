@@ -1222,6 +1222,8 @@ static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_fi
         r.n_scan = std::min(c.R, kScanBlocks);
         r.poison = ls->poison;
         r.wait_limit = c.wait_limit;
+        r.diam = w.diam;
+        r.dsorted = w.dsorted;
     }
     const size_t sm = a.table_lds ? sizeof(double) * c.max_table : 0;
     const int nb = a.n_final_blocks + a.n_bin_blocks + a.n_sample_blocks + (do_scan ? c.R : 0) +

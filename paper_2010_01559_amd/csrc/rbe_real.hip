@@ -180,6 +180,18 @@ __device__ __forceinline__ double lj_offset(const SysDev &S, double di, double d
     return 4.0 * S.lj_eps * (6.0 * sr6 - 12.0 * sr6 * sr6) / (sv * r);
 }
 
+// Whether r^2 is beyond the reach of lj_offset, whose double-precision root and
+// difference then need not be formed: the reach is R_c around r_off, so of a list of
+// r_c = 40 hardly a pair is inside (with the diameters loaded in cell order beside
+// the records instead of after the indices: step at N = 3101 21.5 -> 20.1 us).  The
+// margin is far above the rounding of a single-precision r^2.
+template <typename T>
+__device__ __forceinline__ bool lj_far(const SysDev &S, double di, double dj, T r2)
+{
+    const T b = (T)(0.5 * (di + dj) + (S.lj_rc - S.lj_sig));
+    return b < (T)0 || r2 > b * b * (T)1.00001;
+}
+
 // |d|^2 of two records in double: exact wrapped integer differences for
 // PackF, the wrapped double difference for PartD.
 __device__ __forceinline__ double r2_double(const PackF &a, const PackF &b, double L)
@@ -287,6 +299,7 @@ struct RealArgs {
     const void *km;          // per-mode force constants (KModeF / KModeD) for the fused Fourier force
     uint64_t kick_step;      // index of the step whose closing half kick is applied (its time step)
     const double *diam;      // per-particle diameters (original order) when some system has them
+    const double *dsorted;   // the same in cell order (list steps)
 };
 
 // Neighbour-list state seen by the real-space pass of a step.
@@ -592,7 +605,10 @@ __device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, int il, cons
         T dx, dy, dz, r2;
         displacement(pa, pb, geo, dx, dy, dz, r2);
         T phi = pair_phi<ENERGY>(pc, (T)pa.q, (T)pb.q, r2, e);
-        if (DIAM && S.diam_on) phi += (T)lj_offset<ENERGY>(S, da, a.diam[S.off + qj[k]], r2_double(pa, pb, S.L), e);
+        if (DIAM && S.diam_on) {
+            const double db = a.diam[S.off + qj[k]];
+            if (!lj_far(S, da, db, r2)) phi += (T)lj_offset<ENERGY>(S, da, db, r2_double(pa, pb, S.L), e);
+        }
         const T ph = qphi(phi);
         fx += qterm(ph * dx);
         fy += qterm(ph * dy);
@@ -968,8 +984,10 @@ __device__ __forceinline__ CellSum cells_body(const RealArgs<T> &a, const ListAr
         T dx, dy, dz, d2;
         displacement(pa, pb, geo, dx, dy, dz, d2);
         T phi = pair_phi<ENERGY>(pc, (T)pa.q, (T)pb.q, d2, e);
-        if (DIAM && S.diam_on)
-            phi += (T)lj_offset<ENERGY>(S, da, a.diam[a.sorted_idx[b]], r2_double(pa, pb, S.L), e);
+        if (DIAM && S.diam_on) {
+            const double db = BUILD ? a.dsorted[b] : a.diam[a.sorted_idx[b]];
+            if (!lj_far(S, da, db, d2)) phi += (T)lj_offset<ENERGY>(S, da, db, r2_double(pa, pb, S.L), e);
+        }
         const T ph = qphi(phi);
         fx += qterm(ph * dx);
         fy += qterm(ph * dy);
@@ -1174,8 +1192,12 @@ __device__ __forceinline__ void list_pairs(const RealArgs<T> &a, const ListArgs 
             // this round's partner records, then the next round's partner
             // slots, so that those loads overlap this round's pairs
             Rec pb[U];
+            double db[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) pb[u] = gs[b[u]];
+            for (int u = 0; u < U; ++u) {
+                pb[u] = gs[b[u]];
+                if constexpr (DIAM) db[u] = S.diam_on ? a.dsorted[b[u]] : 0.0;
+            }
             int bn[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -1188,8 +1210,8 @@ __device__ __forceinline__ void list_pairs(const RealArgs<T> &a, const ListArgs 
                     T dx, dy, dz, r2;
                     displacement(pa, pb[u], geo, dx, dy, dz, r2);
                     T phi = pair_phi<false>(pc, (T)pa.q, (T)pb[u].q, r2, e);
-                    if (DIAM && S.diam_on)
-                        phi += (T)lj_offset<false>(S, da, a.diam[a.sorted_idx[b[u]]], r2_double(pa, pb[u], S.L), e);
+                    if (DIAM && S.diam_on && !lj_far(S, da, db[u], r2))
+                        phi += (T)lj_offset<false>(S, da, db[u], r2_double(pa, pb[u], S.L), e);
                     const T ph = qphi(phi);
                     fx += qterm(ph * dx);
                     fy += qterm(ph * dy);
@@ -1551,6 +1573,7 @@ static RealArgs<T> real_args(const LaunchCfg &c, const Workspace &w, void *force
     a.epart = w.energy_part;
     a.km = w.kmode;
     a.diam = w.diam;
+    a.dsorted = w.dsorted;
     return a;
 }
 

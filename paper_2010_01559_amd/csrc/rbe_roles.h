@@ -155,6 +155,8 @@ struct RebuildArgs {
     int n_scan;             // scan blocks
     int32_t *poison;        // raised when a wait gives up, cleared by a complete scan
     int wait_limit;         // spin bound of every wait
+    const double *diam;     // per-particle diameters, moved along when set
+    double *dsorted;
 };
 
 template <typename KM>
@@ -553,6 +555,7 @@ __device__ void rebuild_scatter(const RebuildArgs &a, int b, int nb)
                 }
                 a.sorted_idx[slot[u]] = idx[u];
                 a.slot_of[idx[u]] = slot[u];
+                if (a.diam) a.dsorted[slot[u]] = a.diam[idx[u]];
 #pragma unroll
                 for (int q = 0; q < W; ++q) {
                     reinterpret_cast<uint4 *>(a.sorted)[(int64_t)slot[u] * W + q] = v[u][q];
