@@ -1557,7 +1557,7 @@ static rbe_status list_step(rbe_ctx *c, void *pos, void *vel, const void *q, voi
     const PairsStep ps{totals_in_force(c->cfg), draw_next ? 1 : 0, ks + 1};
     if (!ps.totals)
         RUN(c, K_MID, launch_mid(c->cfg, c->w, 1, 0, nullptr, c->cfg.list_on ? ls.rebuild : nullptr, ls.rebuild_next,
-                             draw_next ? 1 : 0, ks + 1, &ls));
+                             draw_next ? 1 : 0, ks + 1, &ls, pos, q));
     RUN(c, K_REAL, launch_real_step(c->cfg, c->w, ls, ps, force, (andersen || !last) ? nullptr : vel, s));
     c->list_valid = true;
     ++c->list_gen;

@@ -540,16 +540,16 @@ __device__ __forceinline__ void load_list_ref(const SysDev &S, int64_t i, const 
     }
 }
 
-// Stored record of a particle (original order, and cell order for list
-// systems) and the displacement test against skin/2 since the last build.
+// Stored record of a particle (cell order for list systems, else original order, or
+// `both`) and the displacement test against skin/2 since the last build.
 template <typename T>
 __device__ __forceinline__ bool record_update(const SysDev &S, int64_t i, double sx, double sy, double sz, T qi,
-                                              void *packed, void *sorted, const ListRef &lr)
+                                              void *packed, void *sorted, bool both, const ListRef &lr)
 {
     bool moved = false;
     if constexpr (sizeof(T) == 4) {
         const PackF v{to_fix(sx), to_fix(sy), to_fix(sz), (float)qi};
-        reinterpret_cast<PackF *>(packed)[i] = v;
+        if (both || !S.use_list) reinterpret_cast<PackF *>(packed)[i] = v;
         if (S.use_list) {
             reinterpret_cast<PackF *>(sorted)[lr.slot] = v;
             const uint32_t rx = lr.w[0], ry = lr.w[1], rz = lr.w[2];
@@ -561,7 +561,7 @@ __device__ __forceinline__ bool record_update(const SysDev &S, int64_t i, double
         }
     } else {
         const PartD v{sx, sy, sz, (double)qi};
-        reinterpret_cast<PartD *>(packed)[i] = v;
+        if (both || !S.use_list) reinterpret_cast<PartD *>(packed)[i] = v;
         if (S.use_list) {
             reinterpret_cast<PartD *>(sorted)[lr.slot] = v;
             auto word2 = [&](int k) { return __hiloint2double((int)lr.w[k + 1], (int)lr.w[k]); };

@@ -314,7 +314,7 @@ size_t stage_lds_bytes(const LaunchCfg &c, int sample_in_kernel, int *table_lds,
 hipError_t launch_mid(const LaunchCfg &c, const Workspace &w, int do_final, int do_scan,
                       const int32_t *scan_gate = nullptr, const int32_t *bin_gate = nullptr,
                       int32_t *clear_flag = nullptr, int sample_next = 0, uint64_t sample_step = 0,
-                      const ListStep *ls = nullptr);
+                      const ListStep *ls = nullptr, const void *pos = nullptr, const void *q = nullptr);
 hipError_t launch_kforce(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, void *force,
                          int accumulate, int scatter, int mode_split = 1);
 hipError_t launch_scatter(const LaunchCfg &c, const Workspace &w, const void *gF = nullptr);

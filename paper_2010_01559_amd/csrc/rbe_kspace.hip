@@ -153,7 +153,7 @@ struct StageArgs {
     int single_list;       // and whether it uses the neighbour list
     int tab_max;           // LDS doubles reserved for the table
     // neighbour-list mode of a time step
-    int list_mode;
+    int list_mode;         // 1, or 2: list systems store no records in original order
     ListStep ls;
     const int32_t *slot_of;
     void *sorted;
@@ -188,7 +188,7 @@ template <typename T>
 __device__ __forceinline__ bool list_update(const SysDev &S, int64_t i, double sx, double sy, double sz, T qi,
                                             const StageArgs<T> &a, const ListRef &lr)
 {
-    return record_update<T>(S, i, sx, sy, sz, qi, a.packed, a.sorted, lr);
+    return record_update<T>(S, i, sx, sy, sz, qi, a.packed, a.sorted, a.list_mode == 1, lr);
 }
 
 // LDS record of the structure-factor pass: fractional coordinates in double
@@ -1109,6 +1109,13 @@ static void stage_launch(int block, int var, dim3 g, size_t sm, hipStream_t st, 
         stage_launch_bs<T, 1024, SINGLE>(var, g, sm, st, a);
 }
 
+// Whether the steps of a context also store the records of list systems in original
+// order, where only a rebuild reads them.  A small system's rebuild is a chain of latencies,
+// 0.5 us shorter with the records at hand; a large one forms them from the positions
+// and the step saves the store (five steps at N = 1e6 1324 -> 1257 us, ten of 64 x 20000
+// 1395 -> 1384, twenty at N = 1e5 693 -> 689; N = 3000 350 -> 354).
+static bool step_packs(const LaunchCfg &c) { return c.ntot < 65536; }
+
 template <typename T>
 static hipError_t stage_dispatch(const LaunchCfg &c, const Workspace &w, const StageRequest &rq)
 {
@@ -1138,7 +1145,7 @@ static hipError_t stage_dispatch(const LaunchCfg &c, const Workspace &w, const S
     a.do_sample = rq.sample;
     a.do_rho = rq.rho;
     a.chunk = c.rho_chunk;
-    a.list_mode = rq.list ? 1 : 0;
+    a.list_mode = rq.list ? (step_packs(c) ? 1 : 2) : 0;
     if (rq.list) a.ls = *rq.list;
     a.slot_of = w.slot_of;
     a.sorted = w.sorted;
@@ -1175,7 +1182,7 @@ constexpr int kScanBlocks = 32;   // a batch's systems are shared by up to so ma
 template <typename KM>
 static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_final, int do_scan,
                                const int32_t *gate, const int32_t *bin_gate, int32_t *clear_flag, int sample_next,
-                               uint64_t sample_step, const ListStep *ls)
+                               uint64_t sample_step, const ListStep *ls, const void *pos, const void *q)
 {
     MidArgs<KM> a;
     totals_args(a, c, w, sample_next, sample_step, ls);
@@ -1190,7 +1197,6 @@ static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_fi
     a.n_bin_blocks = bin_gate ? std::min(kRebBlocks, (c.n_part_tiles + 3) / 4) : 0;
     a.part_tiles = w.part_tiles;
     a.n_part_tiles = c.n_part_tiles;
-    a.packed = w.packed;
     a.cellid = w.cellid;
     a.rank = w.rank;
     a.clear_flag = clear_flag;
@@ -1209,7 +1215,10 @@ static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_fi
         r.n_part_tiles = c.n_part_tiles;
         r.cellid = w.cellid;
         r.rank = w.rank;
-        r.packed = w.packed;
+        r.packed = step_packs(c) ? w.packed : nullptr;
+        r.pos = pos;
+        r.q = q;
+        r.ntot = c.ntot;
         r.sorted_idx = w.sorted_idx;
         r.sorted = w.sorted;
         r.slot_of = w.slot_of;
@@ -1239,12 +1248,12 @@ static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_fi
 
 hipError_t launch_mid(const LaunchCfg &c, const Workspace &w, int do_final, int do_scan, const int32_t *gate,
                       const int32_t *bin_gate, int32_t *clear_flag, int sample_next, uint64_t sample_step,
-                      const ListStep *ls)
+                      const ListStep *ls, const void *pos, const void *q)
 {
     return c.prec == RBE_FP64 ? mid_dispatch<KModeD>(c, w, do_final, do_scan, gate, bin_gate, clear_flag,
-                                                     sample_next, sample_step, ls)
+                                                     sample_next, sample_step, ls, pos, q)
                               : mid_dispatch<KModeF>(c, w, do_final, do_scan, gate, bin_gate, clear_flag,
-                                                     sample_next, sample_step, ls);
+                                                     sample_next, sample_step, ls, pos, q);
 }
 
 template <typename T, typename KM, bool SINGLE>

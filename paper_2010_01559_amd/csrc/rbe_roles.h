@@ -142,7 +142,9 @@ struct RebuildArgs {
     int n_part_tiles;
     const int32_t *cellid;
     const int32_t *rank;
-    const void *packed;
+    const void *packed;     // records, or NULL: formed from the positions
+    const void *pos, *q;
+    int64_t ntot;
     int32_t *sorted_idx;
     void *sorted;
     int32_t *slot_of;
@@ -158,6 +160,29 @@ struct RebuildArgs {
     const double *diam;     // per-particle diameters, moved along when set
     double *dsorted;
 };
+
+// Record of particle i, as the staging launch forms it.
+__device__ __forceinline__ void rebuild_record(const RebuildArgs &a, const SysDev &S, int64_t i, PackF &v)
+{
+    if (a.packed) {
+        v = reinterpret_cast<const PackF *>(a.packed)[i];
+        return;
+    }
+    const float *x = reinterpret_cast<const float *>(a.pos) + i;
+    v = PackF{to_fix(frac01((double)x[0] * S.invL)), to_fix(frac01((double)x[a.ntot] * S.invL)),
+              to_fix(frac01((double)x[2 * a.ntot] * S.invL)), reinterpret_cast<const float *>(a.q)[i]};
+}
+
+__device__ __forceinline__ void rebuild_record(const RebuildArgs &a, const SysDev &S, int64_t i, PartD &v)
+{
+    if (a.packed) {
+        v = reinterpret_cast<const PartD *>(a.packed)[i];
+        return;
+    }
+    const double *x = reinterpret_cast<const double *>(a.pos) + i;
+    v = PartD{frac01(x[0] * S.invL), frac01(x[a.ntot] * S.invL), frac01(x[2 * a.ntot] * S.invL),
+              reinterpret_cast<const double *>(a.q)[i]};
+}
 
 template <typename KM>
 struct MidArgs {
@@ -183,7 +208,6 @@ struct MidArgs {
     int n_bin_blocks;
     const Tile *part_tiles;
     int n_part_tiles;
-    const void *packed;
     int32_t *cellid;
     int32_t *rank;
     // the next step's modes (one block per system), and a flag to clear
@@ -207,7 +231,7 @@ struct MidArgs {
 // takes up to kRebBatch tiles at once: it loads all their records, then
 // issues all the counter atomics, then stores the cell ids and ranks, so
 // that the memory latencies of its particles overlap instead of adding up.
-constexpr int kRebBatch = 8;
+constexpr int kRebBatch = 4;
 
 template <typename KM>
 __device__ void mid_bin(const MidArgs<KM> &a, int b)
@@ -230,12 +254,14 @@ __device__ void mid_bin(const MidArgs<KM> &a, int b)
             const int64_t i = S.off + t.start + k;
             int cx, cy, cz;
             if constexpr (sizeof(KM) == sizeof(KModeF)) {
-                const PackF v = reinterpret_cast<const PackF *>(a.packed)[i];
+                PackF v;
+                rebuild_record(a.rb, S, i, v);
                 cx = cell_of_fix(v.x, S.nc);
                 cy = cell_of_fix(v.y, S.nc);
                 cz = cell_of_fix(v.z, S.nc);
             } else {
-                const PartD v = reinterpret_cast<const PartD *>(a.packed)[i];
+                PartD v;
+                rebuild_record(a.rb, S, i, v);
                 cx = cell_of_frac(v.x, S.nc);
                 cy = cell_of_frac(v.y, S.nc);
                 cz = cell_of_frac(v.z, S.nc);
@@ -536,8 +562,9 @@ __device__ void rebuild_scatter(const RebuildArgs &a, int b, int nb)
                     sys[u] = t.sys;
                     cell[u] = a.cellid[i];
                     rk[u] = a.rank[i];
-#pragma unroll
-                    for (int q = 0; q < W; ++q) v[u][q] = reinterpret_cast<const uint4 *>(a.packed)[(int64_t)i * W + q];
+                    Rec p;
+                    rebuild_record(a, a.sys[t.sys], i, p);
+                    __builtin_memcpy(v[u], &p, sizeof p);
                 }
             }
         }
