@@ -175,17 +175,21 @@ int default_rho_chunk(int64_t ntot)
 // - Up to a block of 512 particles per compute unit, one block each: its 512
 //   threads cost less to synchronise than 1024 and cover a 64-particle chunk's
 //   terms (N = 1e4 in double precision 32.2 -> 30.8 us a step), 256 do where the
-//   chunk has fewer than 4096 of them (N = 300, P = 10: 21.4 -> 20.4 us).
+//   chunk has fewer than 4096 of them (N = 300, P = 10: 21.4 -> 20.4 us).  Steps of
+//   all-pairs contexts with few modes take 128 particles at least, so that the force
+//   launch forms the totals of twice the system (see totals_in_force; N = 600, P = 60:
+//   17.1 -> 13.4 us) from half the tiles (N = 300: 12.3 -> 12.0 us; with 100 modes in double
+//   precision the staging launch of a force call is 4 us longer).
 // - Beyond, lists of at least 160 modes, whose sums outweigh the loads, and double
 //   precision take two blocks of 512 threads per compute unit and round (N = 1e6,
 //   P = 200: 331 us a step with 512 particles on 1024 threads, 276 with 984 on
 //   512, 285 with 512 on 256), shorter lists three of 256 (N = 1e6, P = 50: 249 and 214 us
 //   with 1024 / 512, 201 with 512 / 256; 64 x 20000, P = 100: 177, 152, 146 us).
-void default_rho_shape(int64_t ntot, int max_p, int prec, int *chunk, int *block)
+void default_rho_shape(int64_t ntot, int max_p, int prec, int all_pairs, int *chunk, int *block)
 {
     const auto per = [&](int64_t blocks) { return (int)(((ntot + blocks - 1) / blocks + 7) / 8 * 8); };
     if (ntot <= 256 * 512) {
-        *chunk = std::max(64, per(256));
+        *chunk = std::max(all_pairs && max_p * (prec == RBE_FP64 ? 4 : 1) <= 64 ? 128 : 64, per(256));
         *block = (int64_t)*chunk * max_p < 4096 ? 256 : 512;
     } else if (max_p >= 160 || prec == RBE_FP64) {
         *chunk = per(512 * ((ntot + 512 * 1024 - 1) / (512 * 1024)));
@@ -948,7 +952,6 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     g.prec = c->prec;
     g.ntot = ntot;
     g.mcap = c->mcap;
-    default_rho_shape(ntot, c->max_p, c->prec, &g.rho_chunk, &g.rho_block);
     g.force_split = default_force_split(ntot);
     g.real_split = 4;
     g.kmax = std::min((kmax + 7) & ~7, 1024);
@@ -958,6 +961,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         g.list_on |= c->sysh[r].use_list;
         g.all_pairs &= c->sysh[r].nc == 1 ? 1 : 0;
     }
+    default_rho_shape(ntot, c->max_p, c->prec, g.all_pairs, &g.rho_chunk, &g.rho_block);
     g.ncell_tot = cell_off;
     g.max_cells = max_cells;
     g.max_p = c->max_p;
