@@ -2278,3 +2278,18 @@ const char *rbe_profile_name(int32_t id)
 int32_t rbe_profile_count(void) { return K_COUNT; }
 
 }  // extern "C"
+
+// ---------------------------------------------------------------------------
+// Sizes and shapes as host arithmetic, for tests of their bounds without a device.  Not
+// part of the interface.
+// ---------------------------------------------------------------------------
+extern "C" {
+void rbe_plan_pair_hist(int64_t max_n, int32_t R, int32_t *tile, int32_t *jw, int32_t *blocks, int32_t *flush)
+{
+    const PairHistPlan p = pair_hist_plan(max_n, R);
+    *tile = kPairHistTile;
+    *jw = p.jw;
+    *blocks = p.blocks;
+    *flush = p.flush;
+}
+}  // extern "C"

@@ -319,6 +319,14 @@ hipError_t launch_kforce(const LaunchCfg &c, const Workspace &w, const void *pos
                          int accumulate, int scatter, int mode_split = 1);
 hipError_t launch_scatter(const LaunchCfg &c, const Workspace &w, const void *gF = nullptr);
 hipError_t launch_set_step(const LaunchCfg &c, const Workspace &w, uint64_t step);
+// Shape of a pair-count launch: particles j of a job (against kPairHistTile particles i),
+// blocks per system, and the jobs after which a block adds its 32-bit counters to
+// the 64-bit counts.
+constexpr int kPairHistTile = 256;
+struct PairHistPlan {
+    int jw, blocks, flush;
+};
+PairHistPlan pair_hist_plan(int64_t max_n, int R);
 hipError_t launch_pair_hist(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, double r_max,
                             int nbins, int64_t *counts);
 // What the force launch of an all-pairs step does besides the forces.

@@ -1,0 +1,31 @@
+"""Bounds of the library's launch shapes and workspaces, as host arithmetic over the
+whole range of sizes a context accepts (no device)."""
+import ctypes as C
+
+import pytest
+
+import paper_2010_01559_amd.rbe as R
+
+
+def _sizes(limit):
+    out, n = set(), 1
+    while n <= limit:
+        out |= {n - 1, n, n + 1, n + n // 3}
+        n *= 2
+    return sorted(k for k in out | {limit} if 1 <= k <= limit)
+
+
+@pytest.mark.parametrize("nsys", [1, 2, 3, 16, 63, 64, 65, 256, 1000])
+def test_pair_count_counters_do_not_wrap(nsys):
+    """Between two flushes a block adds at most flush * tile * jw to one 32-bit
+    counter; and a block of the largest systems does flush that often."""
+    f = R.lib().rbe_plan_pair_hist
+    f.argtypes = [C.c_int64, C.c_int32] + [C.c_void_p] * 4
+    f.restype = None
+    v = (C.c_int32 * 4)()
+    for n in _sizes(2 ** 31 - 1):
+        f(n, nsys, *(C.addressof(v) + 4 * k for k in range(4)))
+        tile, jw, blocks, flush = v
+        assert jw in (16, 64, 256) and blocks >= 1 and flush >= 1
+        assert flush * tile * jw < 2 ** 32
+        assert (flush + 1) * tile * jw >= 2 ** 32 - 1   # and no more often than it has to
