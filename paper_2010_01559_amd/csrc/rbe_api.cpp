@@ -879,7 +879,15 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
             // particles span several cells anyway and finer ones only add rows.
             const double occ = (double)p.n * std::pow(rlist / p.box, 3.0);
             s.nh = std::min(3, std::max(1, (int)std::cbrt(occ / 6.0)));
-            nc = std::min((int)std::floor(s.nh * p.box / rlist), 128);
+            // Pairs at exactly the radius: their r^2 may round to it from either side. The nh
+            // finer cells on either side reach 1e-6 beyond it, so that such a pair is found
+            // also where it straddles their faces.  Boxes of three radii (to 1e-5) take nh = 3
+            // (eight cells): three cells of one radius reach half a box from their
+            // middle, where the sign of an offset is a matter of its rounding (see
+            // cell_pairs, which needs nc >= 2 nh + 2 for pairs up to the cell side).
+            const double reach = rlist * (1.0 + 1e-6);
+            if (p.box < 3.0 * rlist * (1.0 + 1e-5)) s.nh = 3;
+            nc = std::min((int)std::floor(s.nh * p.box / (s.nh == 1 ? rlist : reach)), 128);
             // a wave takes sixteen particles of one row of cells at a time: at
             // least about eight particles per row of a sparse system
             nc = std::min(nc, std::max(3 * s.nh, (int)std::sqrt(p.n / 8.0)));

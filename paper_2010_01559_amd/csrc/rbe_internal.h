@@ -80,7 +80,8 @@ struct SysDev {
     int32_t cdf_off;    // first entry of this system's cumulative table
     int32_t M;          // table covers m = -M..M
     int32_t nc;         // cells per box side (1 => all-pairs real space)
-    int32_t nh;         // cells that the search radius (cutoff + skin) reaches, 1 to 3: nc >= 3 nh
+    int32_t nh;         // cells that the search radius (cutoff + skin) reaches, 1 to 3: nc >= 2 nh + 2,
+                        // or nc = 3 and nh = 1 where the radius is short of the cell side
     int32_t cell_off;   // first cell of this system
     int32_t lj_on;
     int32_t integrator;

@@ -676,7 +676,11 @@ __device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, int il, cons
 // particle share its candidates.
 //  1. The particles are taken in segments: runs that lie in one row of cells
 //     and span few enough cells that the wrapped offsets from the segment's
-//     centre are minimum images for every pair within the radius.
+//     centre are minimum images for every pair within the radius: they stay below
+//     (nc - 1) / (2 nc) of the box, except with three cells along it, where they reach the
+//     faces at +-1/2 and the rounding of the centre decides the sign.  Such a box has
+//     cells of side above the radius by 1e-5 (see the choice of nh), so that a
+//     candidate there is out of reach on either side.
 //  2. The candidates of a segment, the parts of the rows of cells around it
 //     that come within the radius, are numbered through and staged in LDS in
 //     chunks of kCellChunk: the records, and the offsets (-2u, |u|^2) from
