@@ -592,6 +592,35 @@ void build_rho_tiles(rbe_ctx *c, std::vector<Tile> &tiles, std::vector<int32_t> 
     }
 }
 
+// Doubles held for partial sums: two per row (a tile's mode) for the structure
+// factor, and four for the adjoint, which takes long lists of a single system in
+// slices of the modes.  `twice` holds all of them at once; in any case a slice of one
+// mode fits at the smallest chunk (tiles64 tiles of 64 particles).
+size_t partial_room(int64_t rows, int64_t tiles64, bool twice)
+{
+    return (size_t)std::max<int64_t>(2 * rows * (twice ? 2 : 1), 4 * tiles64);
+}
+
+// Slices of an adjoint over `modes` modes whose partials fit `room` doubles (0: none do).
+int vjp_slices(int64_t tiles, int modes, size_t room)
+{
+    if (4 * tiles > (int64_t)room) return 0;
+    int k = 1;
+    while (4 * tiles * ((modes + k - 1) / k) > (int64_t)room) ++k;
+    return k;
+}
+
+// Whether a context of R systems and ntot particles holds the adjoint's sums of all modes:
+// the chunks of a large single system are at least twice 64, unless the caller sets them.
+bool partial_twice(int R, int64_t ntot) { return R > 1 || ntot < 65536; }
+
+int64_t tiles64(const rbe_ctx *c)
+{
+    int64_t t = 0;
+    for (const SysDev &s : c->sysh) t += (s.n + 63) / 64;
+    return t;
+}
+
 size_t partial_need(rbe_ctx *c, int chunk)
 {
     int64_t run = 0;
@@ -1023,11 +1052,8 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     const size_t km_sz = c->prec == RBE_FP64 ? sizeof(KModeD) : sizeof(KModeF);
     const size_t kv_sz = c->prec == RBE_FP64 ? sizeof(KVjpD) : sizeof(KVjpF);
     // the largest rho tile list is the one for the smallest chunk (64)
-    int64_t max_rho_tiles = 0;
-    for (int r = 0; r < R; ++r) max_rho_tiles += (c->sysh[r].n + 63) / 64;
-    // the adjoint needs twice the partials of the structure factor: the chunks
-    // of a large system are at least twice that small
-    c->partial_cap = partial_need(c, 64) * (R > 1 || ntot < 65536 ? 2 : 1);
+    const int64_t max_rho_tiles = tiles64(c);
+    c->partial_cap = partial_room(partial_need(c, 64) / 2, max_rho_tiles, partial_twice(R, ntot));
     Workspace &w = c->w;
     rbe_status st = RBE_OK;
 #define ALLOC(ptr, bytes)                                   \
@@ -1223,7 +1249,7 @@ rbe_status rbe_reserve_modes(rbe_ctx *c, int32_t cap)
     }
     // sized for the current chunk (a long list at a small chunk would need
     // tiles x cap partials); rbe_set_tiles refuses smaller chunks afterwards
-    c->partial_cap = partial_need(c, c->cfg.rho_chunk);
+    c->partial_cap = partial_room(partial_need(c, c->cfg.rho_chunk) / 2, tiles64(c), false);
     if ((s = swap_alloc((void **)&c->w.partial, sizeof(double) * c->partial_cap)) != RBE_OK) return s;
     if (cap > 1024) {
         // partial forces of mode-split force passes
@@ -1913,10 +1939,8 @@ rbe_status rbe_forces_vjp(rbe_ctx *c, const void *pos, const void *q, const void
         // a pass over the modes needs four sums per tile and mode: all modes
         // at once where the partials have room (as allocated at creation), else a
         // single system's long list in slices
-        const int64_t tiles = c->cfg.n_rho_tiles;
-        int slices = 1;
-        if (c->R == 1)
-            while (slices < c->max_p && 4 * tiles * ((c->max_p + slices - 1) / slices) > (int64_t)c->partial_cap) ++slices;
+        const int slices = c->R == 1 ? vjp_slices(c->cfg.n_rho_tiles, c->max_p, c->partial_cap) : 1;
+        if (slices < 1) return set_err(c, RBE_ERR_STATE, "no room for the partial sums of one mode");
         for (int k = 0; k < slices; ++k) {
             const int l0 = slices == 1 ? 0 : (int)((int64_t)c->max_p * k / slices);
             const int l1 = slices == 1 ? 0 : (int)((int64_t)c->max_p * (k + 1) / slices);
@@ -2299,5 +2323,14 @@ void rbe_plan_pair_hist(int64_t max_n, int32_t R, int32_t *tile, int32_t *jw, in
     *jw = p.jw;
     *blocks = p.blocks;
     *flush = p.flush;
+}
+
+// Single system of n particles and p modes created at any chunk: doubles of its partials, and the
+// adjoint's slices of `modes` modes at `chunk`.
+void rbe_plan_adjoint(int32_t n, int32_t p, int32_t chunk, int32_t modes, int64_t *room, int32_t *slices)
+{
+    const int64_t t64 = ((int64_t)n + 63) / 64;
+    *room = (int64_t)partial_room(t64 * p, t64, partial_twice(1, n));
+    *slices = vjp_slices(((int64_t)n + chunk - 1) / chunk, modes, (size_t)*room);
 }
 }  // extern "C"

@@ -29,3 +29,23 @@ def test_pair_count_counters_do_not_wrap(nsys):
         assert jw in (16, 64, 256) and blocks >= 1 and flush >= 1
         assert flush * tile * jw < 2 ** 32
         assert (flush + 1) * tile * jw >= 2 ** 32 - 1   # and no more often than it has to
+
+
+@pytest.mark.parametrize("p", [1, 2, 3, 17, 100, 512])
+@pytest.mark.parametrize("chunk", [64, 72, 120, 128, 256, 1024])
+def test_adjoint_partials_fit(chunk, p):
+    """Every slice of the modes has room for its four sums per tile and mode, for
+    every mode count up to the capacity and any chunk a caller may set."""
+    f = R.lib().rbe_plan_adjoint
+    f.argtypes = [C.c_int32] * 4 + [C.c_void_p] * 2
+    f.restype = None
+    room, slices = C.c_int64(), C.c_int32()
+    for n in _sizes(2 ** 27) + [65535, 65536, 70001]:
+        tiles = -(-n // chunk)
+        for modes in {1, (p + 1) // 2, p}:
+            f(n, p, chunk, modes, C.addressof(room), C.addressof(slices))
+            k = slices.value
+            assert 1 <= k <= modes
+            widest = max(modes * (i + 1) // k - modes * i // k for i in range(k))
+            assert 4 * tiles * widest <= room.value
+            assert room.value >= 2 * -(-n // 64) * p   # the structure factor's own
