@@ -742,9 +742,10 @@ void build_columns(const int32_t *modes, int nm, int64_t n, ColumnLists &out)
     const int32_t *X = modes, *Y = modes + nm, *Z = modes + 2 * (size_t)nm;
     int R = 0;
     for (int l = 0; l < nm; ++l) {
-        const int m = std::max(std::abs(X[l]), std::abs(Y[l]));
-        if (m > kColumnMaxM || std::abs(Z[l]) > kColumnMaxM) return;
-        R = std::max(R, m);
+        // (before any absolute value: that of -2^31 is undefined)
+        const int lo = std::min(X[l], std::min(Y[l], Z[l])), hi = std::max(X[l], std::max(Y[l], Z[l]));
+        if (lo < -kColumnMaxM || hi > kColumnMaxM) return;
+        R = std::max(R, std::max(std::abs(X[l]), std::abs(Y[l])));
     }
     // of the columns (m_x, m_y) and -(m_x, m_y) the first is the one with m_x > 0, or
     // m_x = 0 and m_y >= 0
@@ -2332,5 +2333,16 @@ void rbe_plan_adjoint(int32_t n, int32_t p, int32_t chunk, int32_t modes, int64_
     const int64_t t64 = ((int64_t)n + 63) / 64;
     *room = (int64_t)partial_room(t64 * p, t64, partial_twice(1, n));
     *slices = vjp_slices(((int64_t)n + chunk - 1) / chunk, modes, (size_t)*room);
+}
+
+// Columns of a list of nm modes for n particles: number (0: summed by mode) and trigonometric slots,
+// particles per block of the two passes, particle groups.
+void rbe_plan_columns(const int32_t *modes, int32_t nm, int64_t n, int32_t *out)
+{
+    ColumnLists cl;
+    build_columns(modes, nm, n, cl);
+    const ColumnSet &s = cl.set;
+    const int32_t v[5] = {s.ncols, s.D, s.rho_nb, s.force_nb, s.groups};
+    std::copy(v, v + 5, out);
 }
 }  // extern "C"

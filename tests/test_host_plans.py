@@ -2,6 +2,7 @@
 whole range of sizes a context accepts (no device)."""
 import ctypes as C
 
+import numpy as np
 import pytest
 
 import paper_2010_01559_amd.rbe as R
@@ -49,3 +50,30 @@ def test_adjoint_partials_fit(chunk, p):
             widest = max(modes * (i + 1) // k - modes * i // k for i in range(k))
             assert 4 * tiles * widest <= room.value
             assert room.value >= 2 * -(-n // 64) * p   # the structure factor's own
+
+
+def _columns(m, n):
+    f = R.lib().rbe_plan_columns
+    f.argtypes = [C.c_void_p, C.c_int32, C.c_int64, C.c_void_p]
+    f.restype = None
+    m = np.ascontiguousarray(m, np.int32)
+    out = np.zeros(5, np.int32)
+    f(m.ctypes.data, m.shape[1], n, out.ctypes.data)
+    return dict(zip(("ncols", "slots", "rho_nb", "force_nb", "groups"), out.tolist()))
+
+
+def _ball(r2):
+    k = int(np.sqrt(r2))
+    ax = np.arange(-k, k + 1)
+    m = np.stack(np.meshgrid(ax, ax, ax, indexing="ij")).reshape(3, -1)
+    s = (m * m).sum(0)
+    return m[:, (s > 0) & (s <= r2)].astype(np.int32)
+
+
+@pytest.mark.parametrize("component", [0, 1, 2])
+@pytest.mark.parametrize("value", [129, -129, 2 ** 31 - 1, -2 ** 31 + 1, -2 ** 31])
+def test_lists_with_a_far_mode_keep_the_sums_by_mode(value, component):
+    m = _ball(40)
+    assert m.shape[1] > 512 and _columns(m, 5000)["ncols"] > 0
+    m[component, 100] = value
+    assert _columns(m, 5000)["ncols"] == 0
