@@ -702,8 +702,18 @@ rbe_status upload_rho_tiles(rbe_ctx *c)
     return RBE_OK;
 }
 
+// By the modes in use, which rbe_set_k and the draws after it change: a call
+// without a context (rbe_kspace_forces_noalloc) goes by its own list.
+void set_polar(rbe_ctx *c)
+{
+    int64_t terms = 0;
+    for (const SysDev &s : c->sysh) terms += (int64_t)s.n * s.p;
+    for (SysDev &s : c->sysh) s.polar = polar_form(terms, c->prec);
+}
+
 rbe_status upload_sys(rbe_ctx *c)
 {
+    set_polar(c);
     HIPCHK(c, hipStreamSynchronize(c->stream));
     HIPCHK(c, hipMemcpy(c->w.sys, c->sysh.data(), c->sysh.size() * sizeof(SysDev), hipMemcpyHostToDevice));
     return RBE_OK;
@@ -880,7 +890,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
 
     // ---- per-system constants ----
     std::vector<double> cdf;
-    int64_t off = 0, terms = 0;
+    int64_t off = 0;
     int moff = 0, cell_off = 0, max_cells = 0, max_table = 0;
     // the neighbour list is used only when every system of the batch asks for it
     bool all_skin = true;
@@ -972,9 +982,8 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         cell_off += (s.ncell + 3) & ~3;
         max_cells = std::max(max_cells, s.ncell);
         max_table = std::max(max_table, 2 * s.M + 1);
-        terms += (int64_t)p.n * p.p;
     }
-    for (SysDev &s : c->sysh) s.polar = polar_form(terms, c->prec);
+    set_polar(c);
     if (c->fixed && R != 1) {
         g_create_error = "the fixed sampler needs a single-system context";
         delete c;
