@@ -138,8 +138,9 @@ typedef struct rbe_tiles {
     int32_t rho_chunk;     /* particles staged per structure-factor block (<= 2048) */
     int32_t rho_block;     /* threads per structure-factor block: 256, 512 or 1024 */
     int32_t force_split;   /* waves sharing one particle in the force pass: 1, 2 or 4 */
-    int32_t real_split;    /* lanes per particle in the neighbour-list pass of rbe_step: 1, 2, 4 or 8 (at the
-                              default of 4 the library takes up to 32 in systems that leave compute units idle) */
+    int32_t real_split;    /* lanes per particle in the neighbour-list pass of rbe_step: 1, 2, 4 or 8 (where
+                              rbe_set_tiles has not set it, the default of 4 stands for 4 to 32, by what
+                              leaves no compute units idle) */
 } rbe_tiles;
 
 /* Normaliser of the importance distribution (Sec. 3.1, eqs. 3.1-3.2):

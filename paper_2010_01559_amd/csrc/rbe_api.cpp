@@ -435,6 +435,7 @@ struct rbe_ctx {
     LaunchCfg cfg{};
     Workspace w{};
     size_t partial_cap = 0;        // doubles allocated for partial
+    bool lanes_set = false;        // rbe_set_tiles gave real_split
     int mean_list = 0;             // expected neighbours of a list particle (largest system)
     void *col_mem = nullptr;       // buffers of a dense mode list (one of allocs)
     size_t col_bytes = 0;
@@ -659,7 +660,7 @@ void build_list_tiles(rbe_ctx *c, int lpp, std::vector<Tile> &out)
     }
 }
 
-// Lanes per particle of the list pass.  real_split as the caller set it; its
+// Lanes per particle of the list pass.  real_split as the caller set it; the
 // default of 4 becomes 8, 16 or 32 while that would leave compute units without a
 // block and the lists are longer than the lanes: the launch then lasts as long as
 // one lane's chain of list rounds (N = 3101, lists of 217: 36 us with 4 lanes,
@@ -672,7 +673,7 @@ void build_list_tiles(rbe_ctx *c, int lpp, std::vector<Tile> &out)
 int list_lanes(const rbe_ctx *c)
 {
     int lanes = c->cfg.real_split;
-    if (lanes != 4) return lanes;
+    if (c->lanes_set || lanes != 4) return lanes;
     const int64_t room = c->prec == RBE_FP64 ? 321 : 256;
     while (lanes < 32 && c->ntot * lanes / 256 < room && 2 * lanes <= c->mean_list) lanes *= 2;
     return lanes;
@@ -2017,6 +2018,7 @@ rbe_status rbe_set_tiles(rbe_ctx *c, const rbe_tiles *t)
     c->cfg.rho_block = n.rho_block;
     c->cfg.force_split = n.force_split;
     c->cfg.real_split = n.real_split;
+    if (t->real_split) c->lanes_set = true;
     rbe_status st = upload_rho_tiles(c);
     if (st != RBE_OK) return st;
     return upload_list_tiles(c);
@@ -2117,7 +2119,12 @@ rbe_status rbe_autotune(rbe_ctx *c, const void *pos, const void *q, int32_t reps
     (void)hipEventDestroy(b);
     c->prof = prof;
     if (s != RBE_OK) return s;
+    const bool lanes_set = c->lanes_set;   // the lanes are not tuned
     if ((s = rbe_set_tiles(c, &win)) != RBE_OK) return s;
+    if (c->lanes_set != lanes_set) {
+        c->lanes_set = lanes_set;
+        if ((s = upload_list_tiles(c)) != RBE_OK) return s;
+    }
     tune_store(tune_key(c->arch.c_str(), c->prec, c->ntot, c->max_p, c->R), win);
     if (best) *best = win;
     return RBE_OK;
@@ -2353,5 +2360,14 @@ void rbe_plan_columns(const int32_t *modes, int32_t nm, int64_t n, int32_t *out)
     const ColumnSet &s = cl.set;
     const int32_t v[5] = {s.ncols, s.D, s.rho_nb, s.force_nb, s.groups};
     std::copy(v, v + 5, out);
+}
+
+// What a context runs: lanes per particle of the list pass, its tiles and the room for them; columns of the
+// active list (0: sums by mode) and the particles per block of their two passes.
+void rbe_plan_of_context(const rbe_ctx *c, int32_t *out)
+{
+    const int32_t v[6] = {c->cfg.list_lanes, c->cfg.n_list_tiles, 0, c->cfg.cols.ncols, c->cfg.cols.rho_nb,
+                          c->cfg.cols.force_nb};
+    std::copy(v, v + 6, out);
 }
 }  // extern "C"
