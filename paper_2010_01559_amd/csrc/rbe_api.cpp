@@ -162,8 +162,9 @@ void pair_constants(SysDev &s)
     c.rlist2_box = (float)(s.rlist2 / (s.L * s.L) * (1.0 + 1e-6));
 }
 
-// Structure-factor shape of the calls without a context: one 1024-thread block
-// per compute unit when the particles allow.
+// Structure-factor chunk of the calls without a context, and the largest for which
+// rbe_reserve_modes leaves room: one (1024-thread) block per compute unit when the
+// particles allow.
 int default_rho_chunk(int64_t ntot)
 {
     return (int)std::min<int64_t>(512, std::max<int64_t>(64, ((ntot + 255) / 256 + 7) / 8 * 8));
@@ -1258,9 +1259,11 @@ rbe_status rbe_reserve_modes(rbe_ctx *c, int32_t cap)
         c->modes_valid = false;
         return s;
     }
-    // sized for the current chunk (a long list at a small chunk would need
-    // tiles x cap partials); rbe_set_tiles refuses smaller chunks afterwards
-    c->partial_cap = partial_room(partial_need(c, c->cfg.rho_chunk) / 2, tiles64(c), false);
+    // sized for the smaller of the current chunk and that of a block per compute unit (a
+    // long list at a smaller one would need tiles x cap partials); rbe_set_tiles refuses
+    // smaller chunks afterwards
+    const int chunk = std::min(c->cfg.rho_chunk, default_rho_chunk(c->ntot));
+    c->partial_cap = partial_room(partial_need(c, chunk) / 2, tiles64(c), false);
     if ((s = swap_alloc((void **)&c->w.partial, sizeof(double) * c->partial_cap)) != RBE_OK) return s;
     if (cap > 1024) {
         // partial forces of mode-split force passes
