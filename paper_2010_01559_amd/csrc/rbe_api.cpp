@@ -671,13 +671,34 @@ void build_list_tiles(rbe_ctx *c, int lpp, std::vector<Tile> &out)
 // blocks, 30.2 -> 32.0; single precision at N = 18000 with 8, 562 blocks, 20.8 -> 22.0).
 // The sums over a particle's list are exact in single
 // precision, so the lanes do not change them.
+int default_lanes(int prec, int64_t ntot, int mean_list)
+{
+    int lanes = 4;
+    const int64_t blocks = prec == RBE_FP64 ? 321 : 256;
+    while (lanes < 32 && ntot * lanes / 256 < blocks && 2 * lanes <= mean_list) lanes *= 2;
+    return lanes;
+}
+
 int list_lanes(const rbe_ctx *c)
 {
-    int lanes = c->cfg.real_split;
-    if (c->lanes_set || lanes != 4) return lanes;
-    const int64_t room = c->prec == RBE_FP64 ? 321 : 256;
-    while (lanes < 32 && c->ntot * lanes / 256 < room && 2 * lanes <= c->mean_list) lanes *= 2;
-    return lanes;
+    const int lanes = c->cfg.real_split;
+    return c->lanes_set || lanes != 4 ? lanes : default_lanes(c->prec, c->ntot, c->mean_list);
+}
+
+// Tiles of one system of n particles in the list pass (see build_list_tiles).
+int64_t list_tiles(int n, bool one_cell, int lanes)
+{
+    const int step = one_cell ? real_allpairs_per_tile() : 256 / lanes;
+    return ((int64_t)n + step - 1) / step;
+}
+
+// Room for the list tiles of a context: up to 8 lanes as a caller sets them, or the default.
+int64_t list_tile_room(const rbe_ctx *c)
+{
+    const int lanes = std::max(8, default_lanes(c->prec, c->ntot, c->mean_list));
+    int64_t n = 0;
+    for (const SysDev &s : c->sysh) n += list_tiles(s.n, s.nc == 1, lanes);
+    return n;
 }
 
 rbe_status upload_list_tiles(rbe_ctx *c)
@@ -686,6 +707,7 @@ rbe_status upload_list_tiles(rbe_ctx *c)
     std::vector<Tile> lt;
     c->cfg.list_lanes = list_lanes(c);
     build_list_tiles(c, c->cfg.list_lanes, lt);
+    if ((int64_t)lt.size() > list_tile_room(c)) return set_err(c, RBE_ERR_STATE, "no room for the list tiles");
     c->cfg.n_list_tiles = (int)lt.size();
     HIPCHK(c, hipMemcpy(c->w.list_tiles, lt.data(), lt.size() * sizeof(Tile), hipMemcpyHostToDevice));
     return RBE_OK;
@@ -1125,16 +1147,8 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         ALLOC(w.dsorted, sizeof(double) * ntot);
     }
     {
-        // list-pass tiles: at most one per 32 slots (the 8-lane shape; more lanes
-        // are taken only with fewer than 512 tiles), or the all-pairs tiles of
-        // a one-cell system
-        int64_t nl = R + 512;
-        for (int r = 0; r < R; ++r) {
-            const int step = c->sysh[r].nc == 1 ? real_allpairs_per_tile() : 32;
-            nl += (c->sysh[r].n + step - 1) / step;
-        }
         const int64_t nlist = g.list_on ? ntot : 1;
-        ALLOC(w.list_tiles, sizeof(Tile) * (g.list_on ? nl : 1));
+        ALLOC(w.list_tiles, sizeof(Tile) * (g.list_on ? list_tile_room(c) : 1));
         ALLOC(w.slot_of, sizeof(int32_t) * nlist);
         ALLOC(w.ref, pack_sz * nlist);
         ALLOC(w.nbr, sizeof(int32_t) * (g.list_on ? (int64_t)g.kmax * ntot : 1));
@@ -2369,7 +2383,7 @@ void rbe_plan_columns(const int32_t *modes, int32_t nm, int64_t n, int32_t *out)
 // active list (0: sums by mode) and the particles per block of their two passes.
 void rbe_plan_of_context(const rbe_ctx *c, int32_t *out)
 {
-    const int32_t v[6] = {c->cfg.list_lanes, c->cfg.n_list_tiles, 0, c->cfg.cols.ncols, c->cfg.cols.rho_nb,
+    const int32_t v[6] = {c->cfg.list_lanes, c->cfg.n_list_tiles, (int32_t)list_tile_room(c), c->cfg.cols.ncols, c->cfg.cols.rho_nb,
                           c->cfg.cols.force_nb};
     std::copy(v, v + 6, out);
 }

@@ -59,3 +59,26 @@ def test_tuning_keeps_the_choice():
         R.rbe_sample_k(ctx, 0)
         R.rbe_autotune(ctx, P, Q, 1)
         assert _lanes(ctx) == lanes
+
+
+@pytest.mark.parametrize("prec", [R.RBE_FP64, R.RBE_FP32])
+@pytest.mark.parametrize("sizes", [[2568], [5130], [5136], [10271], [10272], [20543], [20544], [33] * 40,
+                                   [1, 1, 2500, 4999], [64, 8192, 300]])
+def test_list_tiles_have_room(sizes, prec):
+    """The tiles of every shape of the list pass fit their buffer: sizes around the last
+    that takes 32, 16 and 8 lanes by default, batches with many remainders, and one-cell
+    systems among list systems."""
+    prm = []
+    for k, n in enumerate(sizes):
+        L = (n / 0.1) ** (1 / 3.0) if n > 100 else 30.0
+        prm.append(R.Params(n=n, p=4, box=L, alpha=1.0, r_cut=min(5.0, 0.4 * L), skin=0.3, seed=k, precision=prec))
+    ctx = R.rbe_batch_create(prm)
+    f = R.lib().rbe_plan_of_context
+    f.argtypes = [C.c_void_p, C.c_void_p]
+    v = np.zeros(6, np.int32)
+    for split in (0, 1, 2, 4, 8):
+        R.rbe_set_tiles(ctx, real_split=split)
+        f(ctx.handle, v.ctypes.data)
+        assert 0 < v[1] <= v[2]
+        if len(sizes) == 1:
+            assert v[1] == -(-sizes[0] // (256 // v[0]))
