@@ -770,7 +770,7 @@ struct ColumnLists {
 constexpr int kColumnMinModes = 512;
 constexpr int kColumnMaxM = 128;
 
-void build_columns(const int32_t *modes, int nm, int64_t n, ColumnLists &out)
+void build_columns(const int32_t *modes, int nm, int64_t n, size_t room, ColumnLists &out)
 {
     if (nm <= kColumnMinModes) return;
     const int32_t *X = modes, *Y = modes + nm, *Z = modes + 2 * (size_t)nm;
@@ -832,7 +832,7 @@ void build_columns(const int32_t *modes, int nm, int64_t n, ColumnLists &out)
         if (e >= 0) return;   // a mode listed twice
         e = l;
     }
-    if (!column_shapes(s, n)) return;
+    if (!column_shapes(s, n, room)) return;
     out.set = s;
 }
 
@@ -1336,9 +1336,9 @@ rbe_status rbe_sample_k(rbe_ctx *c, uint64_t step, int32_t *modes_out)
 static rbe_status use_columns(rbe_ctx *c, const int32_t *modes, int nm)
 {
     ColumnLists cl;
-    build_columns(modes, nm, c->ntot, cl);
     // the partial sums share the buffer of the sums by mode
-    if (cl.set.ncols == 0 || 2 * (size_t)cl.set.D * (size_t)cl.set.groups > c->partial_cap) return RBE_OK;
+    build_columns(modes, nm, c->ntot, c->partial_cap, cl);
+    if (cl.set.ncols == 0) return RBE_OK;
     auto pad = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t b0 = pad(cl.cols.size() * sizeof(ColumnDev)), b1 = pad(cl.slot_col.size() * 4),
                  b2 = pad(cl.slot_mode.size() * 4), b3 = pad(cl.tiles.size() * 4), b4 = pad(cl.coef * 8);
@@ -2368,12 +2368,12 @@ void rbe_plan_adjoint(int32_t n, int32_t p, int32_t chunk, int32_t modes, int64_
     *slices = vjp_slices(((int64_t)n + chunk - 1) / chunk, modes, (size_t)*room);
 }
 
-// Columns of a list of nm modes for n particles: number (0: summed by mode) and trigonometric slots,
-// particles per block of the two passes, particle groups.
-void rbe_plan_columns(const int32_t *modes, int32_t nm, int64_t n, int32_t *out)
+// Columns of a list of nm modes for n particles, with room for `room` doubles of partial sums: number (0: summed
+// by mode) and trigonometric slots, particles per block of the two passes, particle groups.
+void rbe_plan_columns(const int32_t *modes, int32_t nm, int64_t n, int64_t room, int32_t *out)
 {
     ColumnLists cl;
-    build_columns(modes, nm, n, cl);
+    build_columns(modes, nm, n, (size_t)room, cl);
     const ColumnSet &s = cl.set;
     const int32_t v[5] = {s.ncols, s.D, s.rho_nb, s.force_nb, s.groups};
     std::copy(v, v + 5, out);

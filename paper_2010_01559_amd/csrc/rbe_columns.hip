@@ -403,8 +403,8 @@ static size_t force_lds(const ColumnSet &s, int nb)
 // 64 where the tables of two blocks fit a compute unit's 160 KB of LDS, 32 for
 // longer columns and, in the force pass, while 64 would give fewer blocks than compute
 // units.  Returns whether the tables of 32 fit (modes up to about 97 in each
-// dimension).
-bool column_shapes(ColumnSet &s, int64_t n)
+// dimension), and the partial sums of one group at least in `room` doubles.
+bool column_shapes(ColumnSet &s, int64_t n, size_t room)
 {
     constexpr size_t most = 160 * 1024, two = 80 * 1024;
     if (std::max(rho_lds(s, 32), force_lds(s, 32)) > most) return false;
@@ -413,7 +413,10 @@ bool column_shapes(ColumnSet &s, int64_t n)
     // about two blocks per compute unit
     const int64_t blocks = (int64_t)((s.ncols + kColsPerBlock - 1) / kColsPerBlock);
     const int64_t chunks = (n + s.rho_nb - 1) / s.rho_nb;
+    const int64_t most_groups = (int64_t)(room / (2 * (size_t)s.D));
+    if (most_groups < 1) return false;
     int64_t groups = std::min<int64_t>(std::max<int64_t>(1, (512 + blocks - 1) / blocks), chunks);
+    groups = std::min(groups, most_groups);
     s.per = (int)((chunks + groups - 1) / groups * s.rho_nb);
     s.groups = (int)((n + s.per - 1) / s.per);
     return true;

@@ -304,7 +304,7 @@ struct StageRequest {
 };
 
 // ---- launchers (rbe_kspace.hip, rbe_real.hip, rbe_columns.hip) ----
-bool column_shapes(ColumnSet &s, int64_t n);
+bool column_shapes(ColumnSet &s, int64_t n, size_t room);
 hipError_t launch_col_rho(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q);
 hipError_t launch_col_final(const LaunchCfg &c, const Workspace &w);
 hipError_t launch_col_force(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, void *force,

@@ -52,13 +52,13 @@ def test_adjoint_partials_fit(chunk, p):
             assert room.value >= 2 * -(-n // 64) * p   # the structure factor's own
 
 
-def _columns(m, n):
+def _columns(m, n, room=1 << 40):
     f = R.lib().rbe_plan_columns
-    f.argtypes = [C.c_void_p, C.c_int32, C.c_int64, C.c_void_p]
+    f.argtypes = [C.c_void_p, C.c_int32, C.c_int64, C.c_int64, C.c_void_p]
     f.restype = None
     m = np.ascontiguousarray(m, np.int32)
     out = np.zeros(5, np.int32)
-    f(m.ctypes.data, m.shape[1], n, out.ctypes.data)
+    f(m.ctypes.data, m.shape[1], n, room, out.ctypes.data)
     return dict(zip(("ncols", "slots", "rho_nb", "force_nb", "groups"), out.tolist()))
 
 
@@ -77,3 +77,17 @@ def test_lists_with_a_far_mode_keep_the_sums_by_mode(value, component):
     assert m.shape[1] > 512 and _columns(m, 5000)["ncols"] > 0
     m[component, 100] = value
     assert _columns(m, 5000)["ncols"] == 0
+
+
+@pytest.mark.parametrize("r2", [30, 40, 150, 33 * 33])
+@pytest.mark.parametrize("n", [64, 97, 1000, 1025, 30000, 10 ** 6])
+def test_column_groups_fit_the_partials(n, r2):
+    """A dense list keeps its columns whatever room the sums by mode left for the
+    partials (two doubles per mode at least): fewer groups share it."""
+    m = _ball(r2)
+    free = _columns(m, n)
+    assert free["ncols"] > 0
+    for room in (2 * m.shape[1], 2 * m.shape[1] * 2, 2 * m.shape[1] * 100, 1 << 40):
+        c = _columns(m, n, room)
+        assert c["ncols"] == free["ncols"] and c["rho_nb"] == free["rho_nb"]
+        assert 1 <= c["groups"] <= free["groups"] and 2 * c["slots"] * c["groups"] <= room
