@@ -133,7 +133,8 @@ typedef struct rbe_energy_t {
     int32_t timeout;   /* non-zero if a list rebuild's bounded wait gave up since the last check */
 } rbe_energy_t;
 
-/* Tile shapes of the kernels; 0 fields mean "library default". */
+/* Tile shapes of the kernels; 0 fields mean "library default".  The default structure-factor shape
+ * (rho_chunk, rho_block) follows the modes in use. */
 typedef struct rbe_tiles {
     int32_t rho_chunk;     /* particles staged per structure-factor block (<= 2048) */
     int32_t rho_block;     /* threads per structure-factor block: 256, 512 or 1024 */

@@ -176,7 +176,9 @@ int default_rho_chunk(int64_t ntot)
 // - Up to a block of 512 particles per compute unit, one block each: its 512
 //   threads cost less to synchronise than 1024 and cover a 64-particle chunk's
 //   terms (N = 1e4 in double precision 32.2 -> 30.8 us a step), 256 do where the
-//   chunk has fewer than 4096 of them (N = 300, P = 10: 21.4 -> 20.4 us).  Steps of
+//   chunk has fewer than 4096 of them (N = 300, P = 10: 21.4 -> 20.4 us), and lists that do not
+//   fit a tile of 512 modes keep 1024 (staging launch at N = 30000 and 600 modes 17.3 us, 20.1 with
+//   512; 1934 modes 36.4, 40.8 with 512 and 52.4 with 256).  Steps of
 //   all-pairs contexts with few modes take 128 particles at least, so that the force
 //   launch forms the totals of twice the system (see totals_in_force; N = 600, P = 60:
 //   17.1 -> 13.4 us) from half the tiles (N = 300: 12.3 -> 12.0 us; with 100 modes in double
@@ -191,7 +193,7 @@ void default_rho_shape(int64_t ntot, int max_p, int prec, int all_pairs, int *ch
     const auto per = [&](int64_t blocks) { return (int)(((ntot + blocks - 1) / blocks + 7) / 8 * 8); };
     if (ntot <= 256 * 512) {
         *chunk = std::max(all_pairs && max_p * (prec == RBE_FP64 ? 4 : 1) <= 64 ? 128 : 64, per(256));
-        *block = (int64_t)*chunk * max_p < 4096 ? 256 : 512;
+        *block = (int64_t)*chunk * max_p < 4096 ? 256 : (max_p <= 512 ? 512 : 1024);
     } else if (max_p >= 160 || prec == RBE_FP64) {
         *chunk = per(512 * ((ntot + 512 * 1024 - 1) / (512 * 1024)));
         *block = 512;
@@ -437,6 +439,7 @@ struct rbe_ctx {
     Workspace w{};
     size_t partial_cap = 0;        // doubles allocated for partial
     bool lanes_set = false;        // rbe_set_tiles gave real_split
+    bool shape_set = false;        // the structure-factor shape comes from rbe_set_tiles or the tile cache
     int mean_list = 0;             // expected neighbours of a list particle (largest system)
     void *col_mem = nullptr;       // buffers of a dense mode list (one of allocs)
     size_t col_bytes = 0;
@@ -743,6 +746,18 @@ rbe_status upload_sys(rbe_ctx *c)
     return RBE_OK;
 }
 
+// The default structure-factor shape follows the modes in use, which rbe_set_k and the
+// draws after it change (a long list on a shape for few modes: 98 -> 112 us a
+// step at N = 30000 with 1934 modes on a context of ten).
+void refresh_shape(rbe_ctx *c)
+{
+    if (c->shape_set) return;
+    int chunk, block;
+    default_rho_shape(c->ntot, c->max_p, c->prec, c->cfg.all_pairs, &chunk, &block);
+    if (partial_need(c, chunk) <= c->partial_cap) c->cfg.rho_chunk = chunk;
+    c->cfg.rho_block = block;
+}
+
 void refresh_cfg_modes(rbe_ctx *c)
 {
     c->mtot = 0;
@@ -753,6 +768,7 @@ void refresh_cfg_modes(rbe_ctx *c)
     }
     c->cfg.max_p = c->max_p;
     c->cfg.mcap = c->mcap;
+    refresh_shape(c);
 }
 
 bool check_device_ptr(const void *p) { return p != nullptr; }
@@ -1192,7 +1208,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
             g.rho_block = t.rho_block;
             g.force_split = t.force_split;
             g.real_split = t.real_split;
-            c->tiles_from_cache = true;
+            c->tiles_from_cache = c->shape_set = true;
         }
     }
     if (ok) ok = upload_rho_tiles(c) == RBE_OK;
@@ -1273,10 +1289,15 @@ rbe_status rbe_reserve_modes(rbe_ctx *c, int32_t cap)
         c->modes_valid = false;
         return s;
     }
-    // sized for the smaller of the current chunk and that of a block per compute unit (a
-    // long list at a smaller one would need tiles x cap partials); rbe_set_tiles refuses
-    // smaller chunks afterwards
-    const int chunk = std::min(c->cfg.rho_chunk, default_rho_chunk(c->ntot));
+    // sized for the smallest of the current chunk, the defaults of short and long lists
+    // and that of a block per compute unit (a long list at a smaller one would need
+    // tiles x cap partials); rbe_set_tiles refuses smaller chunks afterwards
+    int chunk = std::min(c->cfg.rho_chunk, default_rho_chunk(c->ntot));
+    for (int p : {1, cap}) {
+        int ch, block;
+        default_rho_shape(c->ntot, p, c->prec, c->cfg.all_pairs, &ch, &block);
+        chunk = std::min(chunk, ch);
+    }
     c->partial_cap = partial_room(partial_need(c, chunk) / 2, tiles64(c), false);
     if ((s = swap_alloc((void **)&c->w.partial, sizeof(double) * c->partial_cap)) != RBE_OK) return s;
     if (cap > 1024) {
@@ -2036,6 +2057,7 @@ rbe_status rbe_set_tiles(rbe_ctx *c, const rbe_tiles *t)
     c->cfg.force_split = n.force_split;
     c->cfg.real_split = n.real_split;
     if (t->real_split) c->lanes_set = true;
+    if (t->rho_chunk || t->rho_block) c->shape_set = true;
     rbe_status st = upload_rho_tiles(c);
     if (st != RBE_OK) return st;
     return upload_list_tiles(c);
