@@ -786,7 +786,27 @@ struct ColumnLists {
 constexpr int kColumnMinModes = 512;
 constexpr int kColumnMaxM = 128;
 
-void build_columns(const int32_t *modes, int nm, int64_t n, size_t room, ColumnLists &out)
+// Whether D column slots beat nm modes summed one by one for n particles (force
+// call, us by mode and by columns; a whole list has D = nm / 2).
+// - Few particles leave the columns a chain of table, product and tile that grows with the
+//   list, 23 us and 4 us per 1000 modes, while the sums by mode are split over the chip.
+//   Single precision, up to 3500 particles: N = 1000, 2968 modes 40.7 / 36.5, 4168 modes
+//   40.6 / 41.7, 33400 modes 85 / 154; N = 3000, 7808 modes 57.6 / 60.4; N = 5000, 33400
+//   modes 269 / 177.  Double precision: N = 300, 16662 modes 106 / 93, 33400 modes
+//   141 / 156; N = 1000, 33400 modes 181 / 154.
+// - Many particles make single precision's sums by mode cheap for short lists, as the
+//   columns tabulate every particle's factors whatever the list: N = 30000, 514 modes
+//   34 / 54, 1044 modes 50 / 55, 1934 modes 79 / 61, N = 1e5 65 / 107, 123 / 133,
+//   196 / 155; N = 5000, 618 modes 27.5 / 27.1.  By these, .032 us a mode against
+//   36 + .01 a slot.
+bool columns_pay(int prec, int64_t n, int nm, int64_t D)
+{
+    if (prec == RBE_FP64) return n >= 512 || 2 * D <= 24576;
+    if (n < 3500) return 2 * D <= 4096;
+    return n <= 6000 || 10 * (int64_t)nm - 3 * D > 11000;
+}
+
+void build_columns(const int32_t *modes, int nm, int64_t n, int prec, size_t room, ColumnLists &out)
 {
     if (nm <= kColumnMinModes) return;
     const int32_t *X = modes, *Y = modes + nm, *Z = modes + 2 * (size_t)nm;
@@ -813,7 +833,7 @@ void build_columns(const int32_t *modes, int nm, int64_t n, size_t room, ColumnL
             cols.push_back(ColumnDev{a, b, z, 0, 0, 0});
             D += 2 * z + 1;
         }
-    if (D > nm) return;   // a full set of columns and their negatives lists about 2 D modes
+    if (D > nm || !columns_pay(prec, n, nm, D)) return;   // a full set of columns and their negatives lists about 2 D modes
     std::stable_sort(cols.begin(), cols.end(), [](const ColumnDev &p, const ColumnDev &q) { return p.Z > q.Z; });
     ColumnSet s{};
     s.ncols = (int)cols.size();
@@ -1358,7 +1378,7 @@ static rbe_status use_columns(rbe_ctx *c, const int32_t *modes, int nm)
 {
     ColumnLists cl;
     // the partial sums share the buffer of the sums by mode
-    build_columns(modes, nm, c->ntot, c->partial_cap, cl);
+    build_columns(modes, nm, c->ntot, c->prec, c->partial_cap, cl);
     if (cl.set.ncols == 0) return RBE_OK;
     auto pad = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t b0 = pad(cl.cols.size() * sizeof(ColumnDev)), b1 = pad(cl.slot_col.size() * 4),
@@ -2390,12 +2410,12 @@ void rbe_plan_adjoint(int32_t n, int32_t p, int32_t chunk, int32_t modes, int64_
     *slices = vjp_slices(((int64_t)n + chunk - 1) / chunk, modes, (size_t)*room);
 }
 
-// Columns of a list of nm modes for n particles, with room for `room` doubles of partial sums: number (0: summed
+// Columns of a list of nm modes for n particles in the given precision, with room for `room` doubles of partial sums: number (0: summed
 // by mode) and trigonometric slots, particles per block of the two passes, particle groups.
-void rbe_plan_columns(const int32_t *modes, int32_t nm, int64_t n, int64_t room, int32_t *out)
+void rbe_plan_columns(const int32_t *modes, int32_t nm, int64_t n, int32_t prec, int64_t room, int32_t *out)
 {
     ColumnLists cl;
-    build_columns(modes, nm, n, (size_t)room, cl);
+    build_columns(modes, nm, n, prec, (size_t)room, cl);
     const ColumnSet &s = cl.set;
     const int32_t v[5] = {s.ncols, s.D, s.rho_nb, s.force_nb, s.groups};
     std::copy(v, v + 5, out);

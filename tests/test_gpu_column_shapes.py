@@ -41,6 +41,9 @@ def _list(kind, rng):
         m = m[:, rng.random(m.shape[1]) < 0.2]
     elif kind == "wide":        # 32 particles per structure-factor block
         m = _box(30, 1, 5)
+    elif kind == "large":
+        m = _box(7, 7, 7)
+        m = m[:, (m * m).sum(0) <= 60]
     elif kind == "long":        # and per force block
         m = _box(2, 2, 70)
     elif kind == "edge28":
@@ -52,7 +55,7 @@ def _list(kind, rng):
 @pytest.mark.parametrize("kind, n, columns, rho_nb, force_nb", [
     ("ball", 3100, True, 64, 32), ("half", 3100, False, 0, 0), ("holes", 3100, True, 64, 32),
     ("repeated", 3100, False, 0, 0), ("sparse", 3100, False, 0, 0),
-    ("ball", 16384, True, 64, 32), ("ball", 16385, True, 64, 64),
+    ("large", 16384, True, 64, 32), ("large", 16385, True, 64, 64),
     ("edge28", 3100, True, 64, 32), ("wide", 1025, True, 32, 32), ("wide", 3100, True, 32, 32),
     ("wide", 3135, True, 32, 32), ("wide", 16400, True, 32, 64), ("long", 16400, True, 64, 32),
 ])

@@ -15,7 +15,7 @@ import ctypes as C, sys
 import numpy as np
 L = C.CDLL(sys.argv[1], mode=0x1)       # RTLD_LAZY: the kernels' launchers are not linked
 f = L.rbe_plan_columns
-f.argtypes = [C.c_void_p, C.c_int32, C.c_int64, C.c_int64, C.c_void_p]
+f.argtypes = [C.c_void_p, C.c_int32, C.c_int64, C.c_int32, C.c_int64, C.c_void_p]
 f.restype = None
 ax = np.arange(-6, 7)
 m = np.stack(np.meshgrid(ax, ax, ax, indexing="ij")).reshape(3, -1).astype(np.int32)
@@ -25,7 +25,7 @@ for d in range(3):
     for v in (2 ** 31 - 1, -2 ** 31 + 1, -2 ** 31):
         k = m.copy()
         k[d, 700] = v
-        f(k.ctypes.data, k.shape[1], 5000, 1 << 40, out.ctypes.data)
+        f(k.ctypes.data, k.shape[1], 5000, 1, 1 << 40, out.ctypes.data)
         assert out[0] == 0, (d, v, out)
 print("mode range: ok")
 """

@@ -52,13 +52,13 @@ def test_adjoint_partials_fit(chunk, p):
             assert room.value >= 2 * -(-n // 64) * p   # the structure factor's own
 
 
-def _columns(m, n, room=1 << 40):
+def _columns(m, n, room=1 << 40, prec=R.RBE_FP64):
     f = R.lib().rbe_plan_columns
-    f.argtypes = [C.c_void_p, C.c_int32, C.c_int64, C.c_int64, C.c_void_p]
+    f.argtypes = [C.c_void_p, C.c_int32, C.c_int64, C.c_int32, C.c_int64, C.c_void_p]
     f.restype = None
     m = np.ascontiguousarray(m, np.int32)
     out = np.zeros(5, np.int32)
-    f(m.ctypes.data, m.shape[1], n, room, out.ctypes.data)
+    f(m.ctypes.data, m.shape[1], n, prec, room, out.ctypes.data)
     return dict(zip(("ncols", "slots", "rho_nb", "force_nb", "groups"), out.tolist()))
 
 
@@ -79,9 +79,9 @@ def test_lists_with_a_far_mode_keep_the_sums_by_mode(value, component):
     assert _columns(m, 5000)["ncols"] == 0
 
 
-@pytest.mark.parametrize("r2", [30, 40, 150, 33 * 33])
-@pytest.mark.parametrize("n", [64, 97, 1000, 1025, 30000, 10 ** 6])
-def test_column_groups_fit_the_partials(n, r2):
+@pytest.mark.parametrize("r2, n", [(r2, n) for r2 in (30, 40, 150, 33 * 33) for n in (64, 97, 1000, 1025, 30000, 10 ** 6)
+                                   if n >= 512 or r2 <= 150])
+def test_column_groups_fit_the_partials(r2, n):
     """A dense list keeps its columns whatever room the sums by mode left for the
     partials (two doubles per mode at least): fewer groups share it."""
     m = _ball(r2)
@@ -91,3 +91,16 @@ def test_column_groups_fit_the_partials(n, r2):
         c = _columns(m, n, room)
         assert c["ncols"] == free["ncols"] and c["rho_nb"] == free["rho_nb"]
         assert 1 <= c["groups"] <= free["groups"] and 2 * c["slots"] * c["groups"] <= room
+
+
+@pytest.mark.parametrize("prec, n, r2, columns", [
+    (R.RBE_FP32, 64, 80, True), (R.RBE_FP32, 64, 150, False), (R.RBE_FP32, 3499, 150, False),
+    (R.RBE_FP32, 3500, 150, True), (R.RBE_FP32, 6000, 28, True), (R.RBE_FP32, 6001, 28, False),
+    (R.RBE_FP32, 30000, 40, False), (R.RBE_FP32, 30000, 60, True), (R.RBE_FP32, 10 ** 6, 25, False),
+    (R.RBE_FP64, 64, 25, True), (R.RBE_FP64, 511, 250, True), (R.RBE_FP64, 511, 400, False),
+    (R.RBE_FP64, 512, 400, True), (R.RBE_FP64, 10 ** 6, 25, True),
+])
+def test_columns_only_where_they_are_faster(prec, n, r2, columns):
+    """Both sides of each measured line: few particles with long lists, and in single
+    precision many particles with short ones, keep the sums by mode."""
+    assert (_columns(_ball(r2), n, prec=prec)["ncols"] > 0) == columns
