@@ -744,12 +744,16 @@ __device__ __forceinline__ void cell_offset(const PackF &p, const CellOrigin<Pac
     u[1] = (float)(int32_t)(p.y - o.y) * 0x1p-32f;
     u[2] = (float)(int32_t)(p.z - o.z) * 0x1p-32f;
 }
+// (a particle without a position, NaN in its record, is far from everything: its pairs,
+// whose terms would be NaN for the other particle as well, do not pass the test)
+constexpr float kNowhere = 1e10f;
 __device__ __forceinline__ void cell_offset(const PartD &p, const CellOrigin<PartD> &o, float u[3])
 {
     const double x = p.x - o.x, y = p.y - o.y, z = p.z - o.z;
     u[0] = (float)(x - rint(x));
     u[1] = (float)(y - rint(y));
     u[2] = (float)(z - rint(z));
+    for (int d = 0; d < 3; ++d) u[d] = fabsf(u[d]) <= 1.0f ? u[d] : kNowhere;
 }
 
 // Calls pair(record, slot, k) for every partner of the lane's particle pa
@@ -797,7 +801,8 @@ __device__ __forceinline__ int cell_pairs(const SysDev &S, const int32_t *st, co
         // roundings several times over
         const float ex = (0.5f * (float)(cx1 - cx0 + 1) + (float)h) * cell, ey = (0.5f + (float)h) * cell;
         const float r2m = radius2 + 1e-5f * (ex * ex + 2.0f * ey * ey);
-        const float ci = in ? fmaf(ui[0], ui[0], fmaf(ui[1], ui[1], ui[2] * ui[2])) - r2m : 1e30f;
+        float ci = in ? fmaf(ui[0], ui[0], fmaf(ui[1], ui[1], ui[2] * ui[2])) - r2m : 1e30f;
+        if constexpr (sizeof(T) == 8) ci = ci < kNowhere ? ci : 1e30f;
         const f32x4 cop = {ci, ci, ci, ci};
         for (int p0 = 0; p0 < parts; p0 += 64) {
             // candidate ranges: lane l has part p0 + l
