@@ -134,7 +134,8 @@ typedef struct rbe_energy_t {
 } rbe_energy_t;
 
 /* Tile shapes of the kernels; 0 fields mean "library default".  The default structure-factor shape
- * (rho_chunk, rho_block) follows the modes in use. */
+ * (rho_chunk, rho_block) follows the modes in use, and rho_block is then that of a time step: force and
+ * energy calls take the thread count that suits them. */
 typedef struct rbe_tiles {
     int32_t rho_chunk;     /* particles staged per structure-factor block (<= 2048) */
     int32_t rho_block;     /* threads per structure-factor block: 256, 512 or 1024 */

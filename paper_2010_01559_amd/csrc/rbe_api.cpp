@@ -170,15 +170,43 @@ int default_rho_chunk(int64_t ntot)
     return (int)std::min<int64_t>(512, std::max<int64_t>(64, ((ntot + 255) / 256 + 7) / 8 * 8));
 }
 
-// Default structure-factor shape of a context.  The step's block integrates its
-// chunk from memory and then works on the chunk's sums; 512 threads leave room for
-// a second block (256 threads for four more) whose loads run under them.
-// - Up to a block of 512 particles per compute unit, one block each: its 512
+// Rounds that the busiest of a compute unit's four SIMDs spends on a block's sums over
+// P modes: the waves with modes to sum, dealt to the SIMDs in turn, times
+// the rounds of a lane (k_stage_rho).  512 threads and 347 modes are one group of
+// particles on 6 waves, two on two of the SIMDs; 1024 threads two groups on 11.
+int sum_rounds(int chunk, int block, int P, int prec)
+{
+    const bool two = prec == RBE_FP32 && P >= kRhoTwoModes && chunk >= kRhoTwoChunk;
+    const int Pt = std::min(P, block), Pl = two ? (Pt + 1) / 2 : Pt, G = std::min(block / Pl, kRhoGroupsMax);
+    const int per = G * (two ? kRhoUnroll / 2 : kRhoUnroll), rounds = (chunk + per - 1) / per;
+    int total = 0;
+    for (int m0 = 0; m0 < P; m0 += Pt) {
+        int simd[4] = {0, 0, 0, 0};
+        for (int w = 0; w < block / 64; ++w) {
+            bool busy = false;
+            for (int t = 64 * w; t < 64 * (w + 1) && !busy; ++t) busy = t / Pl < G && t % Pl < P - m0;
+            simd[w & 3] += busy ? 1 : 0;
+        }
+        total += rounds * *std::max_element(simd, simd + 4);
+    }
+    return total;
+}
+
+// Default structure-factor shape of a context: particles per block, threads of a step's
+// block and of a call's.  The step's block integrates its chunk from memory and then
+// works on the chunk's sums; 512 threads leave room for a second block (256 threads for
+// four more) whose loads run under them.  A call's block only reads its chunk; what it
+// gains is waves at work.
+// - Up to a block of 512 particles per compute unit, one block each.  A step's 512
 //   threads cost less to synchronise than 1024 and cover a 64-particle chunk's
-//   terms (N = 1e4 in double precision 32.2 -> 30.8 us a step), 256 do where the
-//   chunk has fewer than 4096 of them (N = 300, P = 10: 21.4 -> 20.4 us), and lists that do not
-//   fit a tile of 512 modes keep 1024 (staging launch at N = 30000 and 600 modes 17.3 us, 20.1 with
-//   512; 1934 modes 36.4, 40.8 with 512 and 52.4 with 256).  Steps of
+//   terms (N = 1e4 in double precision 32.2 -> 30.8 us a step); 256 do, in calls as well, where the
+//   chunk has fewer than 4096 of them (N = 300, P = 10: 21.4 -> 20.4 us), and 1024
+//   are better where 512 leave the SIMDs uneven (sum_rounds) or take a second
+//   tile of modes for a few (staging and totals launches, N = 1e5 in double precision:
+//   P = 171 54 and 47 us, P = 347 92 and 77, P = 256 57 and 58; N = 3e4 in single
+//   precision: P = 600 20.1 and 17.3, P = 1934 41 and 36).  Calls take 1024 from 160 modes on
+//   and, in double precision, for chunks that are not short (N = 1e5: P = 110 31 and 28, P = 171 55
+//   and 41, P = 347 91 and 70).  Steps of
 //   all-pairs contexts with few modes take 128 particles at least, so that the force
 //   launch forms the totals of twice the system (see totals_in_force; N = 600, P = 60:
 //   17.1 -> 13.4 us) from half the tiles (N = 300: 12.3 -> 12.0 us; with 100 modes in double
@@ -187,19 +215,33 @@ int default_rho_chunk(int64_t ntot)
 //   precision take two blocks of 512 threads per compute unit and round (N = 1e6,
 //   P = 200: 331 us a step with 512 particles on 1024 threads, 276 with 984 on
 //   512, 285 with 512 on 256), shorter lists three of 256 (N = 1e6, P = 50: 249 and 214 us
-//   with 1024 / 512, 201 with 512 / 256; 64 x 20000, P = 100: 177, 152, 146 us).
-void default_rho_shape(int64_t ntot, int max_p, int prec, int all_pairs, int *chunk, int *block)
+//   with 1024 / 512, 201 with 512 / 256; 64 x 20000, P = 100: 177, 152, 146 us).  1024 here, too, where
+//   512 are uneven by more than what the second block fills (64 x 6105 in double
+//   precision, P = 347: 334 and 284 us) and in calls from 100 modes on (the same call 332 and
+//   247), if the chunk leaves them room in the LDS.
+void default_rho_shape(int64_t ntot, int max_p, int prec, int all_pairs, int *chunk, int *block, int *call)
 {
     const auto per = [&](int64_t blocks) { return (int)(((ntot + blocks - 1) / blocks + 7) / 8 * 8); };
+    const auto uneven = [&](double by) {
+        return sum_rounds(*chunk, 512, max_p, prec) > by * sum_rounds(*chunk, 1024, max_p, prec);
+    };
     if (ntot <= 256 * 512) {
         *chunk = std::max(all_pairs && max_p * (prec == RBE_FP64 ? 4 : 1) <= 64 ? 128 : 64, per(256));
-        *block = (int64_t)*chunk * max_p < 4096 ? 256 : (max_p <= 512 ? 512 : 1024);
+        if ((int64_t)*chunk * max_p < 4096) {
+            *block = *call = 256;
+        } else {
+            *block = max_p > 400 || uneven(1.06) ? 1024 : 512;
+            *call = max_p < 160 && (prec == RBE_FP32 || *chunk < 160) ? 512 : 1024;
+        }
     } else if (max_p >= 160 || prec == RBE_FP64) {
         *chunk = per(512 * ((ntot + 512 * 1024 - 1) / (512 * 1024)));
-        *block = 512;
+        const bool room = *chunk <= 896;   // 1024 threads within 64 KB of LDS
+        *block = room && uneven(1.15) ? 1024 : 512;
+        *call = room && max_p >= 100 ? 1024 : 512;
     } else {
         *chunk = std::min(512, per(768));
         *block = 256;
+        *call = max_p < 100 ? 512 : 1024;
     }
 }
 
@@ -752,10 +794,12 @@ rbe_status upload_sys(rbe_ctx *c)
 void refresh_shape(rbe_ctx *c)
 {
     if (c->shape_set) return;
-    int chunk, block;
-    default_rho_shape(c->ntot, c->max_p, c->prec, c->cfg.all_pairs, &chunk, &block);
-    if (partial_need(c, chunk) <= c->partial_cap) c->cfg.rho_chunk = chunk;
+    int chunk, block, call;
+    default_rho_shape(c->ntot, c->max_p, c->prec, c->cfg.all_pairs, &chunk, &block, &call);
+    if (partial_need(c, chunk) > c->partial_cap) return;
+    c->cfg.rho_chunk = chunk;
     c->cfg.rho_block = block;
+    c->cfg.call_block = call;
 }
 
 void refresh_cfg_modes(rbe_ctx *c)
@@ -1068,7 +1112,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         g.list_on |= c->sysh[r].use_list;
         g.all_pairs &= c->sysh[r].nc == 1 ? 1 : 0;
     }
-    default_rho_shape(ntot, c->max_p, c->prec, g.all_pairs, &g.rho_chunk, &g.rho_block);
+    default_rho_shape(ntot, c->max_p, c->prec, g.all_pairs, &g.rho_chunk, &g.rho_block, &g.call_block);
     g.ncell_tot = cell_off;
     g.max_cells = max_cells;
     g.max_p = c->max_p;
@@ -1225,7 +1269,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         c->arch = prop.gcnArchName;
         if (tune_lookup(tune_key(prop.gcnArchName, c->prec, ntot, c->max_p, R), &t) && tiles_fit(t)) {
             g.rho_chunk = t.rho_chunk;
-            g.rho_block = t.rho_block;
+            g.rho_block = g.call_block = t.rho_block;
             g.force_split = t.force_split;
             g.real_split = t.real_split;
             c->tiles_from_cache = c->shape_set = true;
@@ -1314,8 +1358,8 @@ rbe_status rbe_reserve_modes(rbe_ctx *c, int32_t cap)
     // tiles x cap partials); rbe_set_tiles refuses smaller chunks afterwards
     int chunk = std::min(c->cfg.rho_chunk, default_rho_chunk(c->ntot));
     for (int p : {1, cap}) {
-        int ch, block;
-        default_rho_shape(c->ntot, p, c->prec, c->cfg.all_pairs, &ch, &block);
+        int ch, block, call;
+        default_rho_shape(c->ntot, p, c->prec, c->cfg.all_pairs, &ch, &block, &call);
         chunk = std::min(chunk, ch);
     }
     c->partial_cap = partial_room(partial_need(c, chunk) / 2, tiles64(c), false);
@@ -1564,6 +1608,8 @@ static rbe_status kspace_impl(rbe_ctx *c, const void *pos, const void *q, void *
         if (force) RUN(c, K_KFORCE, launch_col_force(c->cfg, c->w, pos, q, force, accumulate));
         return RBE_OK;
     }
+    LaunchCfg cfg = c->cfg;
+    cfg.rho_block = c->cfg.call_block;
     StageRequest rq{const_cast<void *>(pos), nullptr, nullptr, q, 0, 0, 0, 0, 0, 1};
     rq.mode_split = mode_split(c->cfg.n_rho_tiles, c->max_p, 256);
     if (c->sample_pending) {
@@ -1571,7 +1617,7 @@ static rbe_status kspace_impl(rbe_ctx *c, const void *pos, const void *q, void *
         // fused when the launch has at most two blocks per CU: every block
         // draws the modes it needs, which costs more than one sampling
         // launch once there are many blocks
-        if (c->cfg.n_rho_tiles <= 512 && stage_lds_bytes(c->cfg, 1, &table_lds, &tab_max) <= 64 * 1024) {
+        if (c->cfg.n_rho_tiles <= 512 && stage_lds_bytes(cfg, 1, &table_lds, &tab_max) <= 64 * 1024) {
             // the staging launch draws the recorded sample (every block the
             // modes it needs; the first tile of each system stores them)
             rq.sample = 1;
@@ -1588,7 +1634,7 @@ static rbe_status kspace_impl(rbe_ctx *c, const void *pos, const void *q, void *
     const bool bin = cells && rq.mode_split == 1;
     if (cells) *cells = bin;
     rq.bin = bin ? 1 : 0;
-    RUN(c, K_STAGE, launch_stage(c->cfg, c->w, rq));
+    RUN(c, K_STAGE, launch_stage(cfg, c->w, rq));
     // the totals launch also draws the sample of the next step into the
     // alternate mode arrays (one block per system, beside the totals blocks)
     const bool predict = c->cur_drawn && !c->any_mh && !c->fixed &&
@@ -2078,6 +2124,7 @@ rbe_status rbe_set_tiles(rbe_ctx *c, const rbe_tiles *t)
     c->cfg.real_split = n.real_split;
     if (t->real_split) c->lanes_set = true;
     if (t->rho_chunk || t->rho_block) c->shape_set = true;
+    if (c->shape_set) c->cfg.call_block = n.rho_block;
     rbe_status st = upload_rho_tiles(c);
     if (st != RBE_OK) return st;
     return upload_list_tiles(c);

@@ -257,6 +257,7 @@ struct LaunchCfg {
     int cell_ppw;            // most particles of a wave tile: 16 or 8
     int max_sys_rho_tiles;   // most structure-factor tiles of one system
     int rho_chunk, rho_block, force_split, real_split;
+    int call_block;          // threads of the structure-factor blocks of force and energy calls
     int ncell_tot;
     int max_cells;   // largest cell count of one system
     int max_p;
@@ -302,6 +303,20 @@ struct StageRequest {
     int kick = 0;          // integrate: first apply the previous step's closing half kick (deferred)
     int mode_split = 1;    // no integration/binning/sampling: split the modes over this many blocks per chunk
 };
+
+// Structure-factor blocks: a lane has one of the block's groups of particles, in rounds of 8.
+// The groups are capped so that the zero-charge padding of a chunk (up to 8 records per
+// group) stays small.
+constexpr int kRhoGroupsMax = 32;
+constexpr int kRhoUnroll = 8;
+// A lane takes two modes of lists of at least kRhoTwoModes in chunks of at least
+// kRhoTwoChunk particles: every record it reads serves two terms, and the 32-byte
+// reads of 64 lanes bound the one-mode loop (64 x 20000, P = 100: 151 -> 144 us
+// a step; N = 3e5, P = 200: 101 -> 95 us).  The second mode's sum over the groups costs
+// a round more, which short chunks do not win back (N = 3000: 21.1 instead of
+// 20.6 us).  Double precision is bound by its sines and takes one.
+constexpr int kRhoTwoModes = 64;
+constexpr int kRhoTwoChunk = 256;
 
 // ---- launchers (rbe_kspace.hip, rbe_real.hip, rbe_columns.hip) ----
 bool column_shapes(ColumnSet &s, int64_t n, size_t room);

@@ -243,20 +243,6 @@ __device__ __forceinline__ void rho_term(const PartD &v, double mx, double my, d
     s = fma(v.q, sn, s);
 }
 
-// Particle groups per block are capped so that the zero-charge padding of a
-// chunk (up to 8 records per group) stays small.
-constexpr int kRhoGroupsMax = 32;
-constexpr int kRhoUnroll = 8;
-
-// A lane takes two modes of lists of at least kRhoTwoModes in chunks of at least
-// kRhoTwoChunk particles: every record it reads serves two terms, and the 32-byte
-// reads of 64 lanes bound the one-mode loop (64 x 20000, P = 100: 151 -> 144 us
-// a step; N = 3e5, P = 200: 101 -> 95 us).  The second mode's sum over the groups costs
-// a round more, which short chunks do not win back (N = 3000: 21.1 instead of
-// 20.6 us).  Double precision is bound by its sines and takes one.
-constexpr int kRhoTwoModes = 64;
-constexpr int kRhoTwoChunk = 256;
-
 // VAR = 0 compiles a lean variant for launches that only stage the
 // particles and compute structure factors (force calls, energies, long
 // Ewald lists): without the integrator, binning, sampling and list code it
@@ -448,8 +434,14 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
             } else {
                 for (int j0 = g; j0 < cpad; j0 += kRhoUnroll * G) {
                     T c8 = 0, s8 = 0;
+                    // (two records at a time: one by one, double precision waited for each
+                    // read; calls at N = 1e5, P = 256 47.1 -> 43.9 us, N = 3e4, P = 100 10.4 -> 10.0)
 #pragma unroll
-                    for (int u = 0; u < kRhoUnroll; ++u) rho_term(sp[j0 + u * G], mx, my, mz, c8, s8);
+                    for (int u = 0; u < kRhoUnroll; u += 2) {
+                        const RR v = sp[j0 + u * G], w = sp[j0 + (u + 1) * G];
+                        rho_term(v, mx, my, mz, c8, s8);
+                        rho_term(w, mx, my, mz, c8, s8);
+                    }
                     C += (double)c8;
                     Sn += (double)s8;
                 }

@@ -28,7 +28,9 @@ def _modes(nm, rng):
 @pytest.mark.parametrize("prec", [R.RBE_FP64, R.RBE_FP32])
 @pytest.mark.parametrize("n, p, first, nm, then", [
     (300, 10, (128, 256), 513, (64, 1024)),      # one cell: also the chunk
-    (300, 10, (128, 256), 512, (64, 512)),
+    (300, 10, (128, 256), 401, (64, 1024)),
+    (300, 10, (128, 256), 400, (64, 512)),
+    (30000, 100, (120, 512), 300, (120, 1024)),
     (5000, 10, (64, 256), 63, (64, 256)),
     (5000, 10, (64, 256), 64, (64, 512)),
     (5000, 10, (64, 256), 700, (64, 1024)),
