@@ -434,13 +434,18 @@ __global__ __launch_bounds__(BS, VAR == 2 ? 1 : 8) void k_stage_rho(StageArgs<T>
             } else {
                 for (int j0 = g; j0 < cpad; j0 += kRhoUnroll * G) {
                     T c8 = 0, s8 = 0;
-                    // (two records at a time: one by one, double precision waited for each
-                    // read; calls at N = 1e5, P = 256 47.1 -> 43.9 us, N = 3e4, P = 100 10.4 -> 10.0)
+                    if constexpr (sizeof(T) == 4) {
 #pragma unroll
-                    for (int u = 0; u < kRhoUnroll; u += 2) {
-                        const RR v = sp[j0 + u * G], w = sp[j0 + (u + 1) * G];
-                        rho_term(v, mx, my, mz, c8, s8);
-                        rho_term(w, mx, my, mz, c8, s8);
+                        for (int u = 0; u < kRhoUnroll; ++u) rho_term(sp[j0 + u * G], mx, my, mz, c8, s8);
+                    } else {
+                        // (two records at a time: one by one it waited for each read; calls at
+                        // N = 1e5, P = 256 47.1 -> 43.9 us, N = 3e4, P = 100 10.4 -> 10.0)
+#pragma unroll
+                        for (int u = 0; u < kRhoUnroll; u += 2) {
+                            const RR v = sp[j0 + u * G], w = sp[j0 + (u + 1) * G];
+                            rho_term(v, mx, my, mz, c8, s8);
+                            rho_term(w, mx, my, mz, c8, s8);
+                        }
                     }
                     C += (double)c8;
                     Sn += (double)s8;
