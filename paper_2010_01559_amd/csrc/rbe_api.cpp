@@ -693,6 +693,34 @@ void build_real_tiles(rbe_ctx *c, std::vector<Tile> &out)
     }
 }
 
+// Whether the force and energy calls of a context take the cell pass of sparse systems
+// (sparse_body): cells of one radius with few particles each, in every system.  The
+// lines (launch times of the two, us): up to 1000 particles the rows of cells are
+// short, and the pass by waves needs many (N = 300 with 4.7 a cell 11.8 / 8.2, 11
+// a cell 13.3 / 18.0; in double precision 16.1 / 15.6 and 18 / 31); beyond, with the chip to fill,
+// N = 4000 with 3.0 8.2 / 7.3 and 5.5 8.0 / 8.3, N = 4e4 with 2.0 12.7 / 11.6 and 3.3
+// 14 / 14.3, N = 1.5e5 with 1.0 23 / 20.5 and 2.0 24 / 29.5; double precision,
+// whose tests are dearer, N = 1.2e4 with 1.1 9.4 / 7.8 and 2.1 10.2 / 11.2, N = 1.5e5
+// with 0.5 39 / 27 and 1.0 41 / 43.
+bool sparse_pass(const rbe_ctx *c)
+{
+    const bool fp64 = c->prec == RBE_FP64;
+    bool any = false;
+    for (const SysDev &s : c->sysh) {
+        if (s.nc == 1) continue;
+        double most = fp64 ? 4.0 : 4.8;
+        if (s.n >= 1000) {
+            if (fp64)
+                most = c->ntot < 65536 ? 1.5 : 0.8;
+            else
+                most = c->ntot < 16384 ? 4.0 : (c->ntot < 65536 ? 2.5 : 1.5);
+        }
+        if (s.nh != 1 || s.n > most * s.ncell) return false;
+        any = true;
+    }
+    return any;
+}
+
 // List-pass tiles: runs of 256/LPP cell-sorted slots (aux = 2) for list
 // systems, all-pairs runs (aux = 1) for one-cell systems.
 void build_list_tiles(rbe_ctx *c, int lpp, std::vector<Tile> &out)
@@ -1157,6 +1185,19 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         nct = (nct + 3) & ~(int64_t)3;
         if (any_pairs) ctiles.resize(nct, Tile{r, 0, 0, 0});
     }
+    // a context of sparse systems has fixed wave tiles for its force and energy calls
+    std::vector<Tile> sptiles;
+    if (sparse_pass(c)) {
+        for (int r = 0; r < R; ++r) {
+            SysDev &s = c->sysh[r];
+            s.stile_off = (int32_t)sptiles.size();
+            const int step = s.nc == 1 ? 1 : sparse_per_tile();
+            for (int k = 0; k < s.n; k += step)
+                sptiles.push_back(Tile{r, k, std::min(step, s.n - k), s.nc == 1 ? 1 : 0});
+            sptiles.resize((sptiles.size() + 3) & ~(size_t)3, Tile{r, 0, 0, 0});
+        }
+    }
+    g.n_sparse_tiles = (int)sptiles.size();
     g.n_cell_tiles = (int)nct;
     g.n_row_tiles = (int)rowtiles.size();
 
@@ -1184,9 +1225,9 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     // the tile lists that never change shape: one allocation, one upload
     std::vector<Tile> tiles;
     // (the wave tiles start as zeros, but for the entries of all-pairs systems)
-    Tile **const lists[] = {&w.force_tiles, &w.part_tiles, &w.real_tiles, &w.row_tiles};
-    size_t at[4], nt = 0;
-    for (const std::vector<Tile> *v : {&ftiles, &ptiles, &rtiles, &rowtiles}) {
+    Tile **const lists[] = {&w.force_tiles, &w.part_tiles, &w.real_tiles, &w.row_tiles, &w.sparse_tiles};
+    size_t at[5], nt = 0;
+    for (const std::vector<Tile> *v : {&ftiles, &ptiles, &rtiles, &rowtiles, &sptiles}) {
         at[nt++] = tiles.size();
         tiles.insert(tiles.end(), v->begin(), v->end());
     }
@@ -1194,7 +1235,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     if (any_pairs) tiles.insert(tiles.end(), ctiles.begin(), ctiles.end());
     Tile *tile_base = nullptr;
     ALLOC(tile_base, sizeof(Tile) * (n_up + (size_t)g.n_cell_tiles));
-    for (int k = 0; k < 4; ++k) *lists[k] = tile_base + at[k];
+    for (int k = 0; k < 5; ++k) *lists[k] = tile_base + at[k];
     w.cell_tiles = tile_base + n_up;
     ALLOC(w.modes, sizeof(int32_t) * 3 * c->mcap);
     ALLOC(w.mode_w, sizeof(double) * c->mcap);
@@ -1218,7 +1259,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     ALLOC(w.gsorted, 4 * esz * ntot);
     ALLOC(w.modes_alt, sizeof(int32_t) * 3 * c->mcap);
     ALLOC(w.mode_w_alt, sizeof(double) * c->mcap);
-    ALLOC(w.energy_part, sizeof(double) * 8 * (size_t)g.n_cell_tiles);
+    ALLOC(w.energy_part, sizeof(double) * 8 * (size_t)std::max(g.n_cell_tiles, g.n_sparse_tiles));
     ALLOC(w.flag, sizeof(int32_t) * 4);
     ALLOC(w.lflag, sizeof(int32_t) * 8);
     ALLOC(w.step_base, sizeof(uint64_t));
@@ -2476,4 +2517,7 @@ void rbe_plan_of_context(const rbe_ctx *c, int32_t *out)
                           c->cfg.cols.force_nb};
     std::copy(v, v + 6, out);
 }
+
+// Wave tiles of the sparse cell pass (0: the context does not take it).
+int32_t rbe_plan_sparse(const rbe_ctx *c) { return c->cfg.n_sparse_tiles; }
 }  // extern "C"

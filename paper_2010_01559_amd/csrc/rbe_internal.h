@@ -91,6 +91,7 @@ struct SysDev {
     int32_t hi_bits;       // FP32 phases: box fractions split as hi (multiple of 2^-hi_bits) + lo
     float hi_scale, hi_inv;  // 2^hi_bits, 2^-hi_bits
     int32_t ctile_off;     // first wave tile of this system (Workspace::cell_tiles)
+    int32_t stile_off;     // the same in Workspace::sparse_tiles
     int32_t polar;         // FP32: the mode constants hold the structure factor in polar form
     int32_t n_fixed;       // particles 0 .. n_fixed-1 never move
     int32_t diam_on;       // per-particle diameters: LJ with r_off = (d_i + d_j)/2 - sigma
@@ -203,6 +204,7 @@ struct Workspace {
     Tile *real_tiles;      // real-space tiles of a step (aux 0: cell-sorted slots, 1: all pairs)
     Tile *cell_tiles;      // wave tiles of force, energy and adjoint calls (see write_row_tiles)
     Tile *row_tiles;       // runs of up to 256 rows of cells of one system
+    Tile *sparse_tiles;    // wave tiles of force and energy calls of sparse contexts
     int32_t *modes;        // [3][Mcap]
     double *mode_w;        // [Mcap] weights (S/p or explicit)
     double *partial;       // structure-factor tile partials
@@ -254,6 +256,7 @@ struct LaunchCfg {
     int mcap;
     int n_rho_tiles, n_force_tiles, n_part_tiles, n_real_tiles, n_row_tiles;
     int n_cell_tiles;        // wave tiles (a multiple of four)
+    int n_sparse_tiles;      // sparse wave tiles (a multiple of four), 0: not a sparse context
     int cell_ppw;            // most particles of a wave tile: 16 or 8
     int max_sys_rho_tiles;   // most structure-factor tiles of one system
     int rho_chunk, rho_block, force_split, real_split;
@@ -333,6 +336,7 @@ hipError_t launch_mid(const LaunchCfg &c, const Workspace &w, int do_final, int 
                       const ListStep *ls = nullptr, const void *pos = nullptr, const void *q = nullptr);
 hipError_t launch_kforce(const LaunchCfg &c, const Workspace &w, const void *pos, const void *q, void *force,
                          int accumulate, int scatter, int mode_split = 1);
+int sparse_per_tile();
 hipError_t launch_scatter(const LaunchCfg &c, const Workspace &w, const void *gF = nullptr);
 hipError_t launch_set_step(const LaunchCfg &c, const Workspace &w, uint64_t step);
 // Shape of a pair-count launch: particles j of a job (against kPairHistTile particles i),

@@ -284,6 +284,7 @@ struct RealArgs {
     const SysDev *sys;
     const Tile *tiles;       // steps: block tiles (aux = 0: RL_PPB sorted slots; 1: all pairs); calls: wave tiles
     const Tile *wave_tiles;
+    const Tile *sparse_tiles;   // calls of sparse systems: wave tiles of kSparsePPW slots, in any cells
     int single;              // single-system context
     const int32_t *start;
     const int32_t *sorted_idx;
@@ -1070,13 +1071,131 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? (ENERGY ? 6 : 7) :
     }
 }
 
+// ---------------------------------------------------------------------------
+// Cell pass of sparse systems (sparse_pass): seven particles per wave, each on nine lanes,
+// a lane per row of three cells.  A lane tests its row's few candidates one by one
+// into a mask and evaluates those that pass.  With a candidate or two per
+// row the chain of cell_pairs (ranges, staging, products, hit lists) costs more
+// than the tests it saves: launch of 64 x 60 particles 10.3 us with it and 4.8 here,
+// 64 x 461 17.6 and 8.2, 64 x 3679 at density 0.013 52 and 26.
+// ---------------------------------------------------------------------------
+constexpr int kSparsePPW = 7;
+int sparse_per_tile() { return kSparsePPW; }
+
+// Sum over the nine lanes of a particle, on its first lane.
+__device__ __forceinline__ double row_sum(double v, int lane, int r)
+{
+    const double last = __shfl(v, lane + 8, 64);
+    if (r == 0) v += last;
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) {
+        const double w = __shfl(v, lane + o, 64);
+        if (r < o) v += w;
+    }
+    return v;
+}
+
+template <typename T, bool ENERGY, bool DIAM>
+__device__ __forceinline__ void sparse_body(const RealArgs<T> &a, const Tile &t, const SysDev &S, double *ev)
+{
+    using Rec = typename RBT<T>::Rec;
+    Geo geo = make_geo<T>(S);
+    geo.rmax2u *= 1.00001f;   // the terms test the cutoffs, as on the other paths
+    geo.rmax2 *= 1.00001;
+    const auto pc = pair_consts<T>(S);
+    const int lane = threadIdx.x & 63, p = lane / 9, r = lane - 9 * p;
+    const bool act = p < t.count;
+    const int slot = S.off + t.start + min(p, t.count - 1);
+    const Rec *gs = reinterpret_cast<const Rec *>(a.sorted);
+    const Rec pa = gs[slot];
+    const int64_t iorig = a.sorted_idx[slot];
+    const double da = DIAM && S.diam_on ? a.diam[iorig] : 0.0;
+    const int nc = S.nc, slo = S.off, shi = S.off + S.n;
+    const int32_t *st = a.start + S.cell_off + t.sys;
+    int cx, cy, cz;
+    cell_coords<T>(pa, nc, cx, cy, cz);
+    int yy = cy + r % 3 - 1, zz = cz + r / 3 - 1;
+    yy += yy < 0 ? nc : (yy >= nc ? -nc : 0);
+    zz += zz < 0 ? nc : (zz >= nc ? -nc : 0);
+    // cells cx - 1 .. cx + 1, and the one across the face; the starts clamped as in cell_pairs
+    const int base = (zz * nc + yy) * nc, x0 = max(cx - 1, 0), x1 = min(cx + 2, nc);
+    const int w = base + (cx == 0 ? nc - 1 : 0);
+    const bool wrap = cx == 0 || cx == nc - 1;
+    const int b0 = min(max(st[base + x0], slo), shi), n0 = min(max(st[base + x1], b0), shi) - b0;
+    const int b1 = min(max(st[w], slo), shi), n1 = wrap ? min(max(st[w + 1], b1), shi) - b1 : 0;
+    const int n = act ? n0 + n1 : 0;
+    auto at = [&](int k) { return k < n0 ? b0 + k : b1 + k - n0; };
+    double fx = 0, fy = 0, fz = 0, vir = 0;
+    PairE e{0, 0};
+    for (int c = 0; c < n; c += 64) {
+        const int end = min(n, c + 64);
+        uint64_t m = 0;
+        for (int k = c; k < end; k += 2) {
+            const int s0 = at(k), s1 = at(min(k + 1, n - 1));
+            const Rec p0 = gs[s0], p1 = gs[s1];
+            const uint32_t h0 = near_test(pa, p0, geo) && s0 != slot;
+            const uint32_t h1 = near_test(pa, p1, geo) && s1 != slot && k + 1 < end;
+            m |= (uint64_t)(h0 | h1 << 1) << (k - c);
+        }
+        while (m) {
+            const int b = at(c + __builtin_ctzll(m));
+            m &= m - 1;
+            const Rec pb = gs[b];
+            T dx, dy, dz, d2;
+            displacement(pa, pb, geo, dx, dy, dz, d2);
+            T phi = pair_phi<ENERGY>(pc, (T)pa.q, (T)pb.q, d2, e);
+            if (DIAM && S.diam_on) {
+                const double db = a.diam[a.sorted_idx[b]];
+                if (!lj_far(S, da, db, d2)) phi += (T)lj_offset<ENERGY>(S, da, db, r2_double(pa, pb, S.L), e);
+            }
+            const T ph = qphi(phi);
+            fx += qterm(ph * dx);
+            fy += qterm(ph * dy);
+            fz += qterm(ph * dz);
+            if constexpr (ENERGY) vir += 0.5 * (double)(phi * d2);
+        }
+    }
+    if constexpr (sizeof(T) == 4) range_check(fx, fy, fz, a.flag);
+    fx = row_sum(fx, lane, r);
+    fy = row_sum(fy, lane, r);
+    fz = row_sum(fz, lane, r);
+    if constexpr (ENERGY) {
+        ev[0] += e.e_real;
+        ev[1] += e.e_lj;
+        ev[2] += vir;
+    }
+    if (!act || r != 0) return;
+    if constexpr (sizeof(T) == 4) range_check(fx, fy, fz, a.flag);
+    finish_particle<T, ENERGY>(a, S, iorig, fx * qscale<T>(), fy * qscale<T>(), fz * qscale<T>(), ev);
+}
+
+template <typename T, bool ENERGY, bool DIAM>
+__global__ __launch_bounds__(RL_BS) void k_real_sparse(RealArgs<T> a)
+{
+    __shared__ PairQueue<T, DIAM> pairs;
+    const int wt = wave_tile((int)gridDim.x);
+    const Tile t = a.tiles[wt];
+    const SysDev S = a.sys[a.single ? 0 : t.sys];
+    double ev[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (t.aux == 1)
+        allpairs_body<T, ENERGY, DIAM, false>(a, t.start, S, ev, pairs);
+    else if (t.count > 0)
+        sparse_body<T, ENERGY, DIAM>(a, t, S, ev);
+    if constexpr (ENERGY) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) ev[k] = wave_sum(ev[k]);
+        if ((threadIdx.x & 63) == 0)
+            for (int k = 0; k < 8; ++k) a.epart[8 * (int64_t)wt + k] = ev[k];
+    }
+}
+
 // Last launch of an energy call, a block per system: the sums of the wave tiles'
 // partials in a fixed order (eight lanes per tile and one sum each), the Fourier
 // energy and its virial from the modes, and the error word, all into memory of the host
 // (kEnergyOut values per system, then the word).  With the sums over the modes on the
 // host, five copies brought their inputs over, each with a wait of its own (energy and
 // pair counts at N = 30001 553 -> 454 us, with two launches fewer).
-__global__ __launch_bounds__(1024) void k_energy_sum(const SysDev *__restrict__ sys, int R, int n_tiles,
+__global__ __launch_bounds__(1024) void k_energy_sum(const SysDev *__restrict__ sys, int R, int n_tiles, int sparse,
                                                      const double *__restrict__ part, const int32_t *__restrict__ modes,
                                                      const double *__restrict__ mode_w, int mcap,
                                                      const double *__restrict__ rho, const int32_t *__restrict__ flag,
@@ -1101,9 +1220,10 @@ __global__ __launch_bounds__(1024) void k_energy_sum(const SysDev *__restrict__ 
     ek = wave_sum(ek);
     wk = wave_sum(wk);
     if ((tid & 63) == 0) wred[tid >> 6] = make_double2(ek, wk);
-    const int e1 = r + 1 < R ? sys[r + 1].ctile_off : n_tiles;
+    const auto first = [&](int k) { return k == R ? n_tiles : (sparse ? sys[k].stile_off : sys[k].ctile_off); };
+    const int e1 = first(r + 1);
     double v = 0.0;
-    int e = S.ctile_off + (tid >> 3);
+    int e = first(r) + (tid >> 3);
     for (; e + 3 * 128 < e1; e += 4 * 128) {
         double x[4];
 #pragma unroll
@@ -1568,6 +1688,7 @@ static RealArgs<T> real_args(const LaunchCfg &c, const Workspace &w, void *force
     a.sys = w.sys;
     a.tiles = w.real_tiles;
     a.wave_tiles = w.cell_tiles;
+    a.sparse_tiles = w.sparse_tiles;
     a.single = c.R == 1;
     a.start = w.cell_start;
     a.sorted_idx = w.sorted_idx;
@@ -1591,6 +1712,12 @@ static void real_rows_launch(const LaunchCfg &c, RealArgs<T> a)
 {
     // the per-particle-diameter LJ only in launches that need it: it costs
     // the others registers (and with them resident blocks)
+    if (c.n_sparse_tiles) {
+        a.tiles = a.sparse_tiles;
+        launch_k(a.diam ? k_real_sparse<T, ENERGY, true> : k_real_sparse<T, ENERGY, false>, c.n_sparse_tiles / 4, RL_BS, 0,
+                 c.stream, a);
+        return;
+    }
     a.tiles = a.wave_tiles;
     const int nb = c.n_cell_tiles / 4;
     if (c.cell_ppw == 8)
@@ -1704,7 +1831,8 @@ hipError_t launch_energy(const LaunchCfg &c, const Workspace &w, const void *q, 
 
 hipError_t launch_energy_sum(const LaunchCfg &c, const Workspace &w, double *out)
 {
-    launch_k(k_energy_sum, c.R, 1024, 0, c.stream, w.sys, c.R, c.n_cell_tiles, w.energy_part, w.modes, w.mode_w, c.mcap,
+    const int sparse = c.n_sparse_tiles ? 1 : 0;
+    launch_k(k_energy_sum, c.R, 1024, 0, c.stream, w.sys, c.R, sparse ? c.n_sparse_tiles : c.n_cell_tiles, sparse, w.energy_part, w.modes, w.mode_w, c.mcap,
              w.rho, w.flag, out);
     return hipGetLastError();
 }
