@@ -35,6 +35,8 @@
 
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "rbe_device.h"
 #include "rbe_internal.h"
 #include "rbe_roles.h"
@@ -1427,7 +1429,7 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 7 : 1) void k_real
     } else {
         t = rebuild ? a.tiles[ti] : la.list_tiles[ti];
     }
-    SysDev S = a.sys[t.sys];
+    typename std::conditional<SINGLE, SysDev, const SysDev &>::type S = a.sys[SINGLE ? 0 : __builtin_amdgcn_readfirstlane(t.sys)];
     if constexpr (SINGLE) {
         S.off = 0;
         S.moff = 0;
