@@ -411,7 +411,9 @@ using Four = T (*)[FT_MAX][3];
 // small tiles, whose particles would leave lanes idle, walk a half or a quarter of the
 // modes each (step at N = 3000 with 16 particles per tile 18.6 -> 17.5 us, N = 10001 in
 // double precision with 32 30.3 -> 29.6).  With one lane per particle the mode constants
-// are wave-uniform (scalar loads).
+// are wave-uniform (scalar loads), and double precision, whose sums need not agree to the
+// bit between tile shapes, has one sum and two modes at a time: the constants of four
+// overflow the scalar registers (launch at N = 3e4, P = 1600 106 -> 113 us with them).
 template <int SUBS, typename KM, typename Term>
 __device__ __forceinline__ void fourier_subs(const KM *kk0, int l0, int l1, decltype(KM::m[0] + 0) f[3], Term &&term)
 {
@@ -425,12 +427,17 @@ __device__ __forceinline__ void fourier_subs(const KM *kk0, int l0, int l1, decl
         l0 = __builtin_amdgcn_readfirstlane(l0);
         l1 = __builtin_amdgcn_readfirstlane(l1);
         int l = l0;
-        for (; l + 4 <= l1; l += 4)
+        if constexpr (sizeof(T) == 8) {
+#pragma unroll 2
+            for (; l < l1; ++l) term(load_mode(kk, l), s[0]);
+        } else {
+            for (; l + 4 <= l1; l += 4)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) term(load_mode(kk, l + j), s[j]);
+                for (int j = 0; j < 4; ++j) term(load_mode(kk, l + j), s[j]);
 #pragma unroll
-        for (int j = 0; j < 3; ++j)
-            if (l + j < l1) term(load_mode(kk, l + j), s[j]);
+            for (int j = 0; j < 3; ++j)
+                if (l + j < l1) term(load_mode(kk, l + j), s[j]);
+        }
     } else {
         const int g = ((int)threadIdx.x & 63) / (64 / SUBS);
 #pragma unroll 4
@@ -1398,8 +1405,13 @@ __device__ __forceinline__ int wave_slot() { return __builtin_amdgcn_s_getreg((4
 // pass waits on its gathers, and 1792 blocks at once take N = 1e5 (1563) without a
 // second round (N = 1e6 step 267 -> 263 us against six; eight spill into the list
 // pass, 271 us).
+// Double precision asks for two and reaches three (157 to 169 registers, no accumulation
+// registers beside them): with three asked for, the compiler runs the two modes of the
+// Fourier loop one after the other (launch at N = 3e4, P = 1000 70 -> 84 us), with one it
+// takes 12 accumulation registers more and two waves (64 systems of 3000, P = 300
+// 134 -> 151 us).
 template <typename T, int LPP, bool DIAM, bool SINGLE>
-__global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 7 : 1) void k_real_step(RealArgs<T> a, ListArgs la)
+__global__ __launch_bounds__(RL_BS, sizeof(T) == 8 ? 2 : (DIAM ? 1 : 7)) void k_real_step(RealArgs<T> a, ListArgs la)
 {
     __shared__ union {
         T s4[4][FT_MAX][3];
@@ -1429,7 +1441,10 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? 7 : 1) void k_real
     } else {
         t = rebuild ? a.tiles[ti] : la.list_tiles[ti];
     }
-    typename std::conditional<SINGLE, SysDev, const SysDev &>::type S = a.sys[SINGLE ? 0 : __builtin_amdgcn_readfirstlane(t.sys)];
+    // (a copy of a batch's constants crowds the modes out of the scalar registers, in single
+    // precision; a reference costs double precision vector registers)
+    using Sys = typename std::conditional<SINGLE || sizeof(T) == 8, SysDev, const SysDev &>::type;
+    Sys S = a.sys[SINGLE ? 0 : __builtin_amdgcn_readfirstlane(t.sys)];
     if constexpr (SINGLE) {
         S.off = 0;
         S.moff = 0;
