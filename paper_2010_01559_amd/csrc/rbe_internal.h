@@ -91,10 +91,10 @@ struct SysDev {
     int32_t hi_bits;       // FP32 phases: box fractions split as hi (multiple of 2^-hi_bits) + lo
     float hi_scale, hi_inv;  // 2^hi_bits, 2^-hi_bits
     int32_t ctile_off;     // first wave tile of this system (Workspace::cell_tiles)
-    int32_t stile_off;     // the same in Workspace::sparse_tiles
     int32_t polar;         // FP32: the mode constants hold the structure factor in polar form
     int32_t n_fixed;       // particles 0 .. n_fixed-1 never move
     int32_t diam_on;       // per-particle diameters: LJ with r_off = (d_i + d_j)/2 - sigma
+    int32_t stile_off;     // first wave tile of this system in Workspace::sparse_tiles (fills the pad)
     double L, invL;
     double alpha, beta;     // beta = sqrt(alpha)
     double rc2;             // r_cut^2

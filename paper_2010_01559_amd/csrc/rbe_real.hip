@@ -285,8 +285,8 @@ template <typename T>
 struct RealArgs {
     const SysDev *sys;
     const Tile *tiles;       // steps: block tiles (aux = 0: RL_PPB sorted slots; 1: all pairs); calls: wave tiles
+                             // (k_real_sparse: of kSparsePPW slots, in any cells)
     const Tile *wave_tiles;
-    const Tile *sparse_tiles;   // calls of sparse systems: wave tiles of kSparsePPW slots, in any cells
     int single;              // single-system context
     const int32_t *start;
     const int32_t *sorted_idx;
@@ -1705,7 +1705,6 @@ static RealArgs<T> real_args(const LaunchCfg &c, const Workspace &w, void *force
     a.sys = w.sys;
     a.tiles = w.real_tiles;
     a.wave_tiles = w.cell_tiles;
-    a.sparse_tiles = w.sparse_tiles;
     a.single = c.R == 1;
     a.start = w.cell_start;
     a.sorted_idx = w.sorted_idx;
@@ -1725,12 +1724,12 @@ static RealArgs<T> real_args(const LaunchCfg &c, const Workspace &w, void *force
 }
 
 template <typename T, bool ENERGY>
-static void real_rows_launch(const LaunchCfg &c, RealArgs<T> a)
+static void real_rows_launch(const LaunchCfg &c, const Workspace &w, RealArgs<T> a)
 {
     // the per-particle-diameter LJ only in launches that need it: it costs
     // the others registers (and with them resident blocks)
     if (c.n_sparse_tiles) {
-        a.tiles = a.sparse_tiles;
+        a.tiles = w.sparse_tiles;
         launch_k(a.diam ? k_real_sparse<T, ENERGY, true> : k_real_sparse<T, ENERGY, false>, c.n_sparse_tiles / 4, RL_BS, 0,
                  c.stream, a);
         return;
@@ -1747,9 +1746,9 @@ hipError_t launch_real(const LaunchCfg &c, const Workspace &w, void *force, int 
                        uint64_t kick_step)
 {
     if (c.prec == RBE_FP64)
-        real_rows_launch<double, false>(c, real_args<double>(c, w, force, accumulate, vel_kick, nullptr, kick_step));
+        real_rows_launch<double, false>(c, w, real_args<double>(c, w, force, accumulate, vel_kick, nullptr, kick_step));
     else
-        real_rows_launch<float, false>(c, real_args<float>(c, w, force, accumulate, vel_kick, nullptr, kick_step));
+        real_rows_launch<float, false>(c, w, real_args<float>(c, w, force, accumulate, vel_kick, nullptr, kick_step));
     return hipGetLastError();
 }
 
@@ -1840,9 +1839,9 @@ hipError_t launch_real_step(const LaunchCfg &c, const Workspace &w, const ListSt
 hipError_t launch_energy(const LaunchCfg &c, const Workspace &w, const void *q, const void *vel)
 {
     if (c.prec == RBE_FP64)
-        real_rows_launch<double, true>(c, real_args<double>(c, w, nullptr, 0, (void *)vel, q));
+        real_rows_launch<double, true>(c, w, real_args<double>(c, w, nullptr, 0, (void *)vel, q));
     else
-        real_rows_launch<float, true>(c, real_args<float>(c, w, nullptr, 0, (void *)vel, q));
+        real_rows_launch<float, true>(c, w, real_args<float>(c, w, nullptr, 0, (void *)vel, q));
     return hipGetLastError();
 }
 
