@@ -410,7 +410,11 @@ using Four = T (*)[FT_MAX][3];
 // wave share a particle (64 / SUBS apart), each with 4 / SUBS of the sums, so that
 // small tiles, whose particles would leave lanes idle, walk a half or a quarter of the
 // modes each (step at N = 3000 with 16 particles per tile 18.6 -> 17.5 us, N = 10001 in
-// double precision with 32 30.3 -> 29.6).  With one lane per particle the mode constants
+// double precision with 32 30.3 -> 29.6).  Halves load four modes at a time whatever is
+// left of the list, where an unrolled loop takes its remainder one load latency after the
+// other (launch at N = 15000 with 8 lanes, P = 50 7.1 us with that, 6.6 now, 6.1 with 4
+// lanes; in double precision 12.0 -> 11.3); for quarters that was no better (step at
+// N = 10001 in double precision 27.9 -> 28.3 us).  With one lane per particle the mode constants
 // are wave-uniform (scalar loads), and double precision, whose sums need not agree to the
 // bit between tile shapes, has one sum and two modes at a time: the constants of four
 // overflow the scalar registers (launch at N = 3e4, P = 1600 106 -> 113 us with them).
@@ -438,13 +442,20 @@ __device__ __forceinline__ void fourier_subs(const KM *kk0, int l0, int l1, decl
             for (int j = 0; j < 3; ++j)
                 if (l + j < l1) term(load_mode(kk, l + j), s[j]);
         }
+    } else if constexpr (SUBS == 2) {
+        const int g = ((int)threadIdx.x & 63) / (64 / SUBS);
+        for (int l = l0 + NS * g; l < l1; l += 8) {
+            KM k[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) k[u] = kk0[min(l + 4 * (u >> 1) + (u & 1), l1 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (l + 4 * (u >> 1) + (u & 1) < l1) term(k[u], s[u & 1]);
+        }
     } else {
         const int g = ((int)threadIdx.x & 63) / (64 / SUBS);
 #pragma unroll 4
-        for (int l = l0 + NS * g; l < l1; l += 4)
-#pragma unroll
-            for (int j = 0; j < NS; ++j)
-                if (l + j < l1) term(kk0[l + j], s[j]);
+        for (int l = l0 + g; l < l1; l += 4) term(kk0[l], s[0]);
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
