@@ -695,9 +695,10 @@ void build_real_tiles(rbe_ctx *c, std::vector<Tile> &out)
 
 // Whether the force and energy calls of a context take the cell pass of sparse systems
 // (sparse_body): cells of one radius with few particles each, in every system.  The
-// lines (launch times of the two, us): up to 1000 particles the rows of cells are
-// short, and the pass by waves needs many (N = 300 with 4.7 a cell 11.8 / 8.2, 11
-// a cell 13.3 / 18.0; in double precision 16.1 / 15.6 and 18 / 31); beyond, with the chip to fill,
+// lines (launch times by waves / here, us): up to 1000 particles the rows of cells are
+// short, and the pass by waves needs many (N = 300 with 4.7 a cell 11.8 / 8.2, 64 systems
+// of 130 with 4.8 14.9 / 9.8, N = 300 with 11 a cell 13.3 / 18.0; in double precision
+// N = 300 with 4.7 16.1 / 15.6 and 11 a cell 18 / 31); beyond, with the chip to fill,
 // N = 4000 with 3.0 8.2 / 7.3 and 5.5 8.0 / 8.3, N = 4e4 with 2.0 12.7 / 11.6 and 3.3
 // 14 / 14.3, N = 1.5e5 with 1.0 23 / 20.5 and 2.0 24 / 29.5; double precision,
 // whose tests are dearer, N = 1.2e4 with 1.1 9.4 / 7.8 and 2.1 10.2 / 11.2, N = 1.5e5
@@ -708,7 +709,7 @@ bool sparse_pass(const rbe_ctx *c)
     bool any = false;
     for (const SysDev &s : c->sysh) {
         if (s.nc == 1) continue;
-        double most = fp64 ? 4.0 : 4.8;
+        double most = fp64 ? 5.0 : 6.5;
         if (s.n >= 1000) {
             if (fp64)
                 most = c->ntot < 65536 ? 1.5 : 0.8;
