@@ -1024,7 +1024,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     // ---- per-system constants ----
     std::vector<double> cdf;
     int64_t off = 0;
-    int moff = 0, cell_off = 0, max_cells = 0, max_table = 0;
+    int moff = 0, cell_off = 0, max_table = 0;
     // the neighbour list is used only when every system of the batch asks for it
     bool all_skin = true;
     for (int r = 0; r < R; ++r) all_skin = all_skin && params[r].skin > 0.0;
@@ -1113,7 +1113,6 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
         off += p.n;
         moff += p.p;
         cell_off += (s.ncell + 3) & ~3;
-        max_cells = std::max(max_cells, s.ncell);
         max_table = std::max(max_table, 2 * s.M + 1);
     }
     set_polar(c);
@@ -1143,7 +1142,6 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     }
     default_rho_shape(ntot, c->max_p, c->prec, g.all_pairs, &g.rho_chunk, &g.rho_block, &g.call_block);
     g.ncell_tot = cell_off;
-    g.max_cells = max_cells;
     g.max_p = c->max_p;
     g.max_n = 0;
     for (int r = 0; r < R; ++r) g.max_n = std::max(g.max_n, c->sysh[r].n);
@@ -1254,9 +1252,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     ALLOC(w.rank, sizeof(int32_t) * ntot);
     ALLOC(w.sorted_idx, sizeof(int32_t) * ntot);
     ALLOC(w.packed, pack_sz * ntot);
-    // one padding record after the last slot: the cell pass's row scan reads
-    // candidates two at a time and may read one past a segment's end
-    ALLOC(w.sorted, pack_sz * (ntot + 1));
+    ALLOC(w.sorted, pack_sz * ntot);
     ALLOC(w.gsorted, 4 * esz * ntot);
     ALLOC(w.modes_alt, sizeof(int32_t) * 3 * c->mcap);
     ALLOC(w.mode_w_alt, sizeof(double) * c->mcap);

@@ -185,17 +185,6 @@ __device__ __forceinline__ double frac01(double x)
     return f >= 1.0 ? 0.0 : f;
 }
 
-// Single precision: the hardware sine/cosine take revolutions directly
-// (measured absolute error below 1.3e-7 on [-1/2, 1/2]).
-__device__ __forceinline__ void sincos_rev(double r, float *s, float *c)
-{
-    const float rf = (float)r;
-    *s = __builtin_amdgcn_sinf(rf);
-    *c = __builtin_amdgcn_cosf(rf);
-}
-
-__device__ __forceinline__ void sincos_rev(double r, double *s, double *c) { sincospi(2.0 * r, s, c); }
-
 // ---------------------------------------------------------------------------
 // Particle records.
 // PartD: fractional coordinates (double) and charge, for the Fourier passes

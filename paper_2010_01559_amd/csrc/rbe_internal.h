@@ -262,7 +262,6 @@ struct LaunchCfg {
     int rho_chunk, rho_block, force_split, real_split;
     int call_block;          // threads of the structure-factor blocks of force and energy calls
     int ncell_tot;
-    int max_cells;   // largest cell count of one system
     int max_p;
     int max_n;       // particles of the largest system
     int max_table;   // largest cumulative table (2M + 1)

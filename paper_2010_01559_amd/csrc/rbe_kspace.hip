@@ -1204,7 +1204,6 @@ static hipError_t mid_dispatch(const LaunchCfg &c, const Workspace &w, int do_fi
         RebuildArgs &r = a.rb;
         r.sys = w.sys;
         r.R = c.R;
-        r.gate = bin_gate;
         r.ready = ls->ready;
         r.count = w.cell_count;
         r.start = w.cell_start;

@@ -134,7 +134,6 @@ __device__ __forceinline__ void make_kmode(const KModeIn &in, double f, double c
 struct RebuildArgs {
     const SysDev *sys;
     int R;
-    const int32_t *gate;
     int32_t *ready;
     int32_t *count;
     int32_t *start;
