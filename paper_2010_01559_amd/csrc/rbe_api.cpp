@@ -362,10 +362,11 @@ void tune_store(const TuneKey &k, const rbe_tiles &v)
     }
 }
 
-// Whether a tile shape fits the kernels' dynamic LDS: the adjoint
-// reduction stages 48 bytes per particle and 16 per thread, the staging
-// kernel 32 per particle (plus 256 padding records) and 28 per thread (its
-// table falls back to global memory when it does not fit).
+// Whether a tile shape fits the kernels' dynamic LDS, 64 KB as the staging kernel is
+// launched: 32 bytes per particle (plus 256 padding records) and 28 per thread (its
+// table falls back to global memory when it does not fit).  The adjoint reduction stages
+// 48 bytes per particle, 56 in double precision, and 16 per thread; its launch takes more
+// than 64 KB where double precision needs it (launch_lds; at most 74 KB of the 160 here).
 bool tiles_fit(const rbe_tiles &n)
 {
     return n.rho_chunk >= 64 && n.rho_chunk <= 2048 && n.rho_chunk % 8 == 0 &&

@@ -4,8 +4,9 @@
 // eq. (2.9) and the second term of eq. (2.11); the shifted Lennard-Jones
 // repulsion of eq. (4.1), with r_off = 0 or, from per-particle diameters,
 // r_off = (d_i + d_j)/2 - sigma (Sec. 4.2).  The paper leaves the neighbour
-// search open; here it is a cell list with cells of side >= the largest
-// cutoff (+ skin), rebuilt for every stand-alone evaluation, and inside
+// search open; here it is a cell list with cells of side >= 1/nh of the search
+// radius (the largest cutoff, + skin; nh = 1 to 3 by the particles within it), rebuilt
+// for every stand-alone evaluation, and inside
 // rbe_step a Verlet list of the pairs within cutoff + skin, rebuilt on the
 // device whenever some particle has moved more than skin/2 since the last
 // build (the rebuild step evaluates the forces on the cell list and writes
@@ -17,12 +18,14 @@
 // with beta = sqrt(alpha); the Coulomb part acts for r <= r_c.
 //
 // Work decomposition of the cell pass (cell_pairs): a wave takes sixteen
-// cell-sorted particles; the cells around them are nine rows of consecutive
-// cells, contiguous ranges of the cell-sorted array (two where a row wraps in
-// x).  The squared distances of the sixteen to their candidates come from the
+// cell-sorted particles (eight in small systems); the cells around them are
+// (2 nh + 1)^2 = 9, 25 or 49 rows of consecutive cells, contiguous ranges of the
+// cell-sorted array (two where a row wraps in x, so up to 98).  The squared
+// distances of the particles to their candidates come from the
 // matrix cores (a conservative test in single precision); the partners that
-// pass are listed in LDS and evaluated by four lanes per particle from the
-// exact records, so the pair terms do not diverge on the distance test.  Each
+// pass are listed in LDS and evaluated by four lanes per particle (eight) from the
+// exact records, so the pair terms do not diverge on the distance test.  Calls of
+// sparse systems test their few candidates one by one (sparse_body).  Each
 // lane accumulates its FP32 pair terms exactly (on a fixed grid, see qterm),
 // so the result does not depend on the order of the particles inside a cell
 // (which comes from atomic counters) nor on the path (cell or list pass).
@@ -600,7 +603,7 @@ __device__ __forceinline__ void fourier_lanes(const RealArgs<T> &a, const MidArg
 // all partners alone, two blocks at N = 300) the launch lasted as long as N
 // dependent loads and pair terms of one lane: 79 us at N = 300 in single and
 // 122 us at N = 200 in double precision, against about 5 us each now (a step
-// of the 300 ions 105 -> 30 us).  FOURIER adds the Fourier force (a
+// of the 300 ions 105 -> 30 us then, 12 now in two launches).  FOURIER adds the Fourier force (a
 // mode per lane).  DIAM compiles the per-particle-diameter LJ (only launches
 // of contexts with diameters).
 template <typename T, bool ENERGY, bool DIAM, bool FOURIER, bool TOTALS = false>
