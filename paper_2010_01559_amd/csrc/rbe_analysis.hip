@@ -18,7 +18,8 @@
 // evaluated: the counts are those of the definition for every pair.  Measured
 // at N = 30001, 200 bins, r_max = 0.499 L: 9.7 ms with the definition for every
 // pair (three divisions and a square root in FP64) on one block per 256
-// particles, 425 us now (33 VALU instructions per 64 pairs and a square root).
+// particles, 430 us now (28 VALU instructions per 64 pairs by the counters, one of them a
+// square root, and two LDS accesses).
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
