@@ -1026,6 +1026,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     std::vector<double> cdf;
     int64_t off = 0;
     int moff = 0, cell_off = 0, max_table = 0;
+    bool edge = false;
     // the neighbour list is used only when every system of the batch asks for it
     bool all_skin = true;
     for (int r = 0; r < R; ++r) all_skin = all_skin && params[r].skin > 0.0;
@@ -1055,12 +1056,18 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
             s.nh = std::min(3, std::max(1, (int)std::cbrt(occ / 6.0)));
             // Pairs at exactly the radius: their r^2 may round to it from either side. The nh
             // finer cells on either side reach 1e-6 beyond it, so that such a pair is found
-            // also where it straddles their faces.  Boxes of three radii (to 1e-5) take nh = 3
-            // (eight cells): three cells of one radius reach half a box from their
-            // middle, where the sign of an offset is a matter of its rounding (see
-            // cell_pairs, which needs nc >= 2 nh + 2 for pairs up to the cell side).
+            // also where it straddles their faces.  Boxes of three radii (to 1e-5) would have
+            // five cells with nh = 2, which reach half a box from their middle, where the sign
+            // of an offset is a matter of its rounding (cell_pairs needs nc >= 2 nh + 2, or
+            // three cells).  They take nh = 3, eight cells, or without a list three cells up
+            // to 120 particles in each (real-space call with three and with eight: N = 420
+            // 33 and 106 us, N = 2500 113 and 142, N = 4000 170 and 117; 16 systems of 2500 191
+            // and 245, of 4000 376 and 325; double precision N = 420 45 and 143, N = 4000 292 and 198).
             const double reach = rlist * (1.0 + 1e-6);
-            if (p.box < 3.0 * rlist * (1.0 + 1e-5)) s.nh = 3;
+            if (p.box < 3.0 * rlist * (1.0 + 1e-5)) {
+                s.nh = occ < 120.0 && !all_skin ? 1 : 3;
+                edge |= s.nh == 1;
+            }
             nc = std::min((int)std::floor(s.nh * p.box / (s.nh == 1 ? rlist : reach)), 128);
             // a wave takes sixteen particles of one row of cells at a time: at
             // least about eight particles per row of a sparse system
@@ -1146,6 +1153,7 @@ rbe_status rbe_batch_create(const rbe_params *params, int32_t R, void *stream, r
     g.max_p = c->max_p;
     g.max_n = 0;
     for (int r = 0; r < R; ++r) g.max_n = std::max(g.max_n, c->sysh[r].n);
+    g.cell_edge = edge ? 1 : 0;
     g.max_table = max_table;
     g.wait_limit = kWaitLimit;
 

@@ -81,7 +81,7 @@ struct SysDev {
     int32_t M;          // table covers m = -M..M
     int32_t nc;         // cells per box side (1 => all-pairs real space)
     int32_t nh;         // cells that the search radius (cutoff + skin) reaches, 1 to 3: nc >= 2 nh + 2,
-                        // or nc = 3 and nh = 1 where the radius is short of the cell side
+                        // or nc = 3 and nh = 1
     int32_t cell_off;   // first cell of this system
     int32_t lj_on;
     int32_t integrator;
@@ -258,6 +258,7 @@ struct LaunchCfg {
     int n_cell_tiles;        // wave tiles (a multiple of four)
     int n_sparse_tiles;      // sparse wave tiles (a multiple of four), 0: not a sparse context
     int cell_ppw;            // most particles of a wave tile: 16 or 8
+    int cell_edge;           // some system has three cells of one search radius along its box (cell_pairs)
     int max_sys_rho_tiles;   // most structure-factor tiles of one system
     int rho_chunk, rho_block, force_split, real_split;
     int call_block;          // threads of the structure-factor blocks of force and energy calls

@@ -702,9 +702,11 @@ __device__ __forceinline__ void allpairs_body(const RealArgs<T> &a, int il, cons
 //     and span few enough cells that the wrapped offsets from the segment's
 //     centre are minimum images for every pair within the radius: they stay below
 //     (nc - 1) / (2 nc) of the box, except with three cells along it, where they reach the
-//     faces at +-1/2 and the rounding of the centre decides the sign.  Such a box has
-//     cells of side above the radius by 1e-5 (see the choice of nh), so that a
-//     candidate there is out of reach on either side.
+//     faces at +-1/2 and the rounding of the centre decides the sign.  If the cells are one
+//     radius wide, such a candidate can be within reach on either side: it enters the test
+//     by a bound of both (EDGE, a variant of its own: three more registers, which the step's
+//     force launch would pay, N = 1e6 steps 1303 -> 1331 us for five.  Contexts with
+//     lists have eight cells there).
 //  2. The candidates of a segment, the parts of the rows of cells around it
 //     that come within the radius, are numbered through and staged in LDS in
 //     chunks of kCellChunk: the records, and the offsets (-2u, |u|^2) from
@@ -780,12 +782,18 @@ __device__ __forceinline__ void cell_offset(const PartD &p, const CellOrigin<Par
     for (int d = 0; d < 3; ++d) u[d] = fabsf(u[d]) <= 1.0f ? u[d] : kNowhere;
 }
 
+// An offset of half the box, to within the roundings of the centre and of the offset.  The
+// nearer image of such a candidate is 1/2 - a away from a particle at +-a of the
+// centre, a <= 1/6, and (1/2 - a)^2 is at least a^2 + 1/12, whatever the sign.
+constexpr float kCellEdge = 4e-6f;
+__device__ __forceinline__ bool cell_edge(float u) { return fabsf(fabsf(u) - 0.5f) < kCellEdge; }
+
 // Calls pair(record, slot, k) for every partner of the lane's particle pa
 // (slot, active when act) that may lie within the search radius, split over
 // the particle's lanes; k numbers the particle's partners from 0.
 // Returns their number (the same on those lanes).  radius2: the search
 // radius squared in box units; st: the system's cell starts.
-template <typename T, int PPW, typename F>
+template <typename T, int PPW, bool EDGE, typename F>
 __device__ __forceinline__ int cell_pairs(const SysDev &S, const int32_t *st, const typename RBT<T>::Rec *gs,
                                           const typename RBT<T>::Rec &pa, int slot, bool act, float radius2,
                                           CellLds<typename RBT<T>::Rec> &w, F &&pair)
@@ -894,14 +902,21 @@ __device__ __forceinline__ int cell_pairs(const SysDev &S, const int32_t *st, co
                 }
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    float x[3];
+                    float x[3], edge2 = 0.0f;
                     cell_offset(pb[u], o, x);
+                    if (EDGE && nc == 3)
+                        for (int d = 0; d < 3; ++d)
+                            if (cell_edge(x[d])) {
+                                x[d] = 0.0f;
+                                edge2 += 1.0f / 12.0f - kCellEdge;
+                            }
                     const int k = lane + 64 * u;
                     const bool ok = sl[u] >= 0;
                     w.c[0][k] = ok ? -2.0f * x[0] : 0.0f;
                     w.c[1][k] = ok ? -2.0f * x[1] : 0.0f;
                     w.c[2][k] = ok ? -2.0f * x[2] : 0.0f;
-                    w.c[3][k] = ok ? fmaf(x[0], x[0], fmaf(x[1], x[1], x[2] * x[2])) : 1e30f;
+                    const float x2 = fmaf(x[0], x[0], fmaf(x[1], x[1], x[2] * x[2]));
+                    w.c[3][k] = ok ? (EDGE ? x2 + edge2 : x2) : 1e30f;
                     w.rec[k] = pb[u];
                     w.slot[k] = sl[u];
                 }
@@ -990,7 +1005,7 @@ struct CellSum {
     bool first;   // the lane that finishes its particle
 };
 
-template <typename T, int PPW, bool ENERGY, bool BUILD, bool DIAM>
+template <typename T, int PPW, bool ENERGY, bool BUILD, bool DIAM, bool EDGE>
 __device__ __forceinline__ CellSum cells_body(const RealArgs<T> &a, const ListArgs *la, int sys, int slot0, int cnt,
                                               const SysDev &S, double *ev, CellLds<typename RBT<T>::Rec> &lds, typename RBT<T>::Rec &pa)
 {
@@ -1009,7 +1024,7 @@ __device__ __forceinline__ CellSum cells_body(const RealArgs<T> &a, const ListAr
     double fx = 0, fy = 0, fz = 0, vir = 0;
     PairE e{0, 0};
     const float r2 = BUILD ? S.pair.rlist2_box : S.pair.rsearch2_box;
-    const int n = cell_pairs<T, PPW>(S, a.start + S.cell_off + sys, gs, pa, slot, act, r2, lds,
+    const int n = cell_pairs<T, PPW, EDGE>(S, a.start + S.cell_off + sys, gs, pa, slot, act, r2, lds,
                                 [&](const Rec &pb, int b, int k) {
         if constexpr (BUILD)
             if (k < la->kmax) la->nbr[(int64_t)k * a.ntot + slot] = b;
@@ -1066,7 +1081,7 @@ __device__ __forceinline__ int wave_tile(int nblocks)
 // trace times: N = 1e5 at density 0.1 48.5 -> 28 us, N = 3e4 23 -> 15 us,
 // N = 3e4 with r_c = 13.6 (1060 partners) 778 -> 179 us; the step that builds the
 // lists at N = 1e5 68 -> 45 us.
-template <typename T, int PPW, bool ENERGY, bool DIAM>
+template <typename T, int PPW, bool ENERGY, bool DIAM, bool EDGE>
 __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? (ENERGY ? 6 : 7) : 1) void k_real_rows(RealArgs<T> a)
 {
     // a wave runs one of the two bodies on its own part of either member
@@ -1082,8 +1097,8 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 4 && !DIAM ? (ENERGY ? 6 : 7) :
         allpairs_body<T, ENERGY, DIAM, false>(a, t.start, S, ev, lds.pairs);
     } else if (t.count > 0) {
         typename RBT<T>::Rec pa;
-        const CellSum c = cells_body<T, PPW, ENERGY, false, DIAM>(a, nullptr, t.sys, S.off + t.start, t.count, S, ev,
-                                                                  lds.cells[threadIdx.x >> 6], pa);
+        const CellSum c = cells_body<T, PPW, ENERGY, false, DIAM, EDGE>(a, nullptr, t.sys, S.off + t.start, t.count, S, ev,
+                                                                        lds.cells[threadIdx.x >> 6], pa);
         if (c.first) finish_particle<T, ENERGY>(a, S, c.iorig, c.fx, c.fy, c.fz, ev);
     }
     if constexpr (ENERGY) {
@@ -1494,7 +1509,7 @@ __global__ __launch_bounds__(RL_BS, sizeof(T) == 8 ? 2 : (DIAM ? 1 : 7)) void k_
     typename RBT<T>::Rec pa;
     CellSum c{0, 0, 0, 0, false};
     if (16 * wave < t.count)
-        c = cells_body<T, 16, false, true, DIAM>(a, &la, t.sys, S.off + t.start + 16 * wave, min(16, t.count - 16 * wave), S,
+        c = cells_body<T, 16, false, true, DIAM, false>(a, &la, t.sys, S.off + t.start + 16 * wave, min(16, t.count - 16 * wave), S,
                                                  nullptr, lds.cells[wave], pa);
     __syncthreads();
     fourier_tile<T, 1>(a, S, a.sorted, S.off + t.start, t.count, s4);
@@ -1600,7 +1615,7 @@ __device__ __forceinline__ void vjp_pair(const SysDev &S, T qi, T qj, T dx, T dy
     rz -= (double)(dphi_r * GD * dz + phi * Gz);
 }
 
-template <typename T, int PPW>
+template <typename T, int PPW, bool EDGE>
 __global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__restrict__ gF,
                                                     const T *__restrict__ gsorted, T *__restrict__ gpos,
                                                     T *__restrict__ gq, int accumulate)
@@ -1661,7 +1676,7 @@ __global__ __launch_bounds__(RL_BS) void k_vjp_real(RealArgs<T> a, const T *__re
     T Gix, Giy, Giz;
     load4(gsorted, slot, Gix, Giy, Giz);
     double dq = 0, rx = 0, ry = 0, rz = 0;
-    cell_pairs<T, PPW>(S, a.start + S.cell_off + t.sys, gs, pa, slot, act, S.pair.rsearch2_box, lds[tid >> 6],
+    cell_pairs<T, PPW, EDGE>(S, a.start + S.cell_off + t.sys, gs, pa, slot, act, S.pair.rsearch2_box, lds[tid >> 6],
                        [&](const Rec &pb, int b, int) {
         T dx, dy, dz, r2;
         displacement(pa, pb, geo, dx, dy, dz, r2);
@@ -1750,10 +1765,19 @@ static void real_rows_launch(const LaunchCfg &c, const Workspace &w, RealArgs<T>
     }
     a.tiles = a.wave_tiles;
     const int nb = c.n_cell_tiles / 4;
-    if (c.cell_ppw == 8)
-        launch_k(a.diam ? k_real_rows<T, 8, ENERGY, true> : k_real_rows<T, 8, ENERGY, false>, nb, RL_BS, 0, c.stream, a);
+    const auto go = [&](auto edge) {
+        constexpr bool E = decltype(edge)::value;
+        if (c.cell_ppw == 8)
+            launch_k(a.diam ? k_real_rows<T, 8, ENERGY, true, E> : k_real_rows<T, 8, ENERGY, false, E>, nb, RL_BS, 0,
+                     c.stream, a);
+        else
+            launch_k(a.diam ? k_real_rows<T, 16, ENERGY, true, E> : k_real_rows<T, 16, ENERGY, false, E>, nb, RL_BS, 0,
+                     c.stream, a);
+    };
+    if (c.cell_edge)
+        go(std::true_type{});
     else
-        launch_k(a.diam ? k_real_rows<T, 16, ENERGY, true> : k_real_rows<T, 16, ENERGY, false>, nb, RL_BS, 0, c.stream, a);
+        go(std::false_type{});
 }
 
 hipError_t launch_real(const LaunchCfg &c, const Workspace &w, void *force, int accumulate, void *vel_kick,
@@ -1872,7 +1896,9 @@ static void vjp_real_launch(const LaunchCfg &c, RealArgs<T> a, const void *gF, c
                             int accumulate)
 {
     a.tiles = a.wave_tiles;
-    launch_k(c.cell_ppw == 8 ? k_vjp_real<T, 8> : k_vjp_real<T, 16>, c.n_cell_tiles / 4, RL_BS, 0, c.stream, a,
+    const auto kernel = c.cell_edge ? (c.cell_ppw == 8 ? k_vjp_real<T, 8, true> : k_vjp_real<T, 16, true>)
+                                    : (c.cell_ppw == 8 ? k_vjp_real<T, 8, false> : k_vjp_real<T, 16, false>);
+    launch_k(kernel, c.n_cell_tiles / 4, RL_BS, 0, c.stream, a,
              (const T *)gF, (const T *)gsorted, (T *)gpos, (T *)gq, accumulate);
 }
 
