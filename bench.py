@@ -72,13 +72,13 @@ PEAK_HBM_GBS = 8000.0
 # of the N = 1e5 run holds no rebuild); the staging launches of steps after
 # the first of a call; the Fourier-only launches at N = 1e5.
 TRAFFIC = {
-    "real": {"src": "b32e33c0d2874489", "fetch_kib": 8611.9, "write_kib": 6163.3, "fetch_scale": 2.000,
+    "real": {"src": "49b9cdf151ce3d57", "fetch_kib": 8602.9, "write_kib": 6163.3, "fetch_scale": 2.000,
              "write_scale": 1.000},
-    "stage": {"src": "148040d006564950", "fetch_kib": 3176.8, "write_kib": 5673.9, "fetch_scale": 2.000,
+    "stage": {"src": "ff4ff002048073b8", "fetch_kib": 3176.8, "write_kib": 5674.7, "fetch_scale": 2.000,
               "write_scale": 1.000},
-    "stage_fourier": {"src": "148040d006564950", "fetch_kib": 884.2, "write_kib": 400.0, "fetch_scale": 2.000,
+    "stage_fourier": {"src": "ff4ff002048073b8", "fetch_kib": 884.2, "write_kib": 400.0, "fetch_scale": 2.000,
                       "write_scale": 1.000},
-    "kforce": {"src": "148040d006564950", "fetch_kib": 851.3, "write_kib": 1171.9, "fetch_scale": 2.000,
+    "kforce": {"src": "ff4ff002048073b8", "fetch_kib": 851.3, "write_kib": 1171.9, "fetch_scale": 2.000,
                "write_scale": 1.000},
 }
 
